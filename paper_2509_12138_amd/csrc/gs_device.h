@@ -119,6 +119,11 @@ __device__ __forceinline__ float splat_p2_row(const Splat& s, float adx2, float 
   return __fmaf_rn(dy, t, adx2);                 // A dx^2 + B dx dy + C dy^2
 }
 
+// p2 at the offset (dx, dy) of a pixel centre from the mean.
+__device__ __forceinline__ float splat_p2(const Splat& s, float dx, float dy) {
+  return __fmaf_rn(dy, __fmaf_rn(s.C, dy, splat_bdx(s, dx)), splat_adx2(s, dx));
+}
+
 template <int PX>
 __device__ __forceinline__ void splat_p2_column(const Splat& s, float dx, const float* fy,
                                                 float* p2) {
@@ -130,6 +135,23 @@ __device__ __forceinline__ void splat_p2_column(const Splat& s, float dx, const 
 // Entry passes the skip tests: falloff exponent <= 0 and alpha >= 1/255.
 __device__ __forceinline__ bool splat_pass(const Splat& s, float p2) {
   return (p2 <= 0.0f) && (p2 >= s.thr);
+}
+
+// The lanes of the wave that pass the skip tests, as a lane mask, and those
+// whose list position has not passed their last one.  Compares that write a
+// scalar mask directly: combining them and testing for "any lane" then costs
+// no vector instruction (a ballot of a combined condition costs two).
+__device__ __forceinline__ uint64_t splat_pass_lanes(const Splat& s, float p2) {
+  constexpr int kOle = 5, kOge = 3;                       // ordered <=, >=
+  return __builtin_amdgcn_fcmpf(p2, 0.0f, kOle) & __builtin_amdgcn_fcmpf(p2, s.thr, kOge);
+}
+__device__ __forceinline__ uint64_t lanes_le(int a, int b) {
+  constexpr int kSle = 41;                                // signed <=
+  return __builtin_amdgcn_sicmp(a, b, kSle);
+}
+// Whether the calling lane is in a wave-uniform lane mask.
+__device__ __forceinline__ bool lane_in(uint64_t lanes) {
+  return __builtin_amdgcn_inverse_ballot_w64(lanes);
 }
 
 // Conservative cull of a splat against the pixel centres of the box

@@ -14,8 +14,8 @@
 //
 // The backward recovers each pixel's transmittance by dividing T_final by
 // (1 - alpha) in reverse order (STORED) or first replays the forward for its
-// tile (RECOMPUTE).  Per (tile, Gaussian) the 9 gradient components are
-// summed over the wave with DPP and added with one FP32 atomic each.
+// blocks (RECOMPUTE).  The 9 gradient components of an entry are summed over
+// the wave with lane swaps and DPP and added with one FP32 atomic each.
 #include <algorithm>
 
 #include "gs_device.h"
@@ -26,9 +26,8 @@ constexpr int kRasterWave = 64;
 
 // XCD-aware tile order: work-group i runs on XCD (i mod 8); give each XCD a
 // contiguous range of tiles.
-__device__ __forceinline__ int64_t tile_of_block(int64_t n_tiles) {
+__device__ __forceinline__ int64_t tile_of_block(int64_t i, int64_t n_tiles) {
   const int64_t chunk = (n_tiles + 7) / 8;
-  const int64_t i = blockIdx.x;
   return (i & 7) * chunk + (i >> 3);
 }
 
@@ -318,20 +317,25 @@ struct ChunkDev {
   float4* ck;
 };
 
-template <typename F>
+// Calls body(tile, b) for the work-group's tiles; NB work-groups, b = 0 ..
+// NB-1, share a tile (adjacent launches, or adjacent queue items).
+template <int NB = 1, typename F>
 __device__ __forceinline__ void for_each_tile(const TileSched& sch, int64_t n_tiles, F&& body) {
   if (sch.queue) {
     for (;;) {
       uint32_t item = 0;
       if (threadIdx.x == 0) item = atomicAdd(sch.queue, 1u);
       item = __builtin_amdgcn_readfirstlane(item);
-      if ((int64_t)item >= n_tiles) break;
-      body((int64_t)(sch.order ? sch.order[item] : item));
+      if ((int64_t)item >= n_tiles * NB) break;
+      body((int64_t)(sch.order ? sch.order[item / NB] : item / NB), (int)(item % NB));
     }
+  } else if (sch.order) {
+    const uint32_t i = blockIdx.x / NB;
+    if ((int64_t)i < n_tiles) body((int64_t)sch.order[i], (int)(blockIdx.x % NB));
   } else {
-    const int64_t tile = sch.order ? ((int64_t)blockIdx.x < n_tiles ? (int64_t)sch.order[blockIdx.x] : n_tiles)
-                                   : tile_of_block(n_tiles);
-    if (tile < n_tiles) body(tile);
+    // consecutive work-groups of one XCD (ids 8 apart) share a tile
+    const int64_t tile = tile_of_block((blockIdx.x >> 3) / NB * 8 + (blockIdx.x & 7), n_tiles);
+    if (tile < n_tiles) body(tile, (int)((blockIdx.x >> 3) % NB));
   }
 }
 
@@ -420,7 +424,7 @@ void k_raster_fwd(RasterDev a, TileSched sch,
   __shared__ Splat s_splat[kRasterWave * NW];
   // wave-uniform base (scalar), so per-entry LDS addresses stay scalar too
   Splat* mine = s_splat + __builtin_amdgcn_readfirstlane(threadIdx.x / kRasterWave) * kRasterWave;
-  for_each_tile(sch, a.n_tiles, [&](int64_t tile) {
+  for_each_tile(sch, a.n_tiles, [&](int64_t tile, int) {
     fwd_tile<TW, TH, NW>(a, ch, tile, mine, image, T_final, n_contrib);
   });
 }
@@ -455,9 +459,9 @@ __device__ __forceinline__ Scatter9 scatter9_setup() {
   const int u = b2 == 0 ? (b3 ? 2 : 0) : (b3 ? -1 : 1);           // after stage 2
   const int w = u < 0 ? -1 : (first16 ? u : (u + 3 <= 4 ? u + 3 : -1));   // after stage 1
   const int v = w < 0 ? -1 : (first32 ? w : (w + 5 <= 8 ? w + 5 : -1));  // component
-  // d mean2d (x2) carry -ln2, d Q11 and d Q22 -1/2, d Q12 -1 (log2-scaled
-  // falloff); opacity and colour 1
-  const float sc[9] = {-kLn2, -kLn2, -0.5f, -1.0f, -0.5f, 1.0f, 1.0f, 1.0f, 1.0f};
+  // d mean2d carry -2 ln2 (the log2-scaled falloff), d Q11 and d Q22 -1/2,
+  // d Q12 -1; opacity and colour 1
+  const float sc[9] = {-2.0f * kLn2, -2.0f * kLn2, -0.5f, -1.0f, -0.5f, 1.0f, 1.0f, 1.0f, 1.0f};
   Scatter9 r;
   r.slot = ((lane & 3) == 0) ? v : -1;
   r.scale = v >= 0 ? sc[v] : 0.0f;
@@ -506,205 +510,243 @@ __device__ __forceinline__ float reduce_scatter9(const float (&v)[9]) {
   return z;
 }
 
+// ---------------------------------------------------------------- backward
+
+// The backward walks 8x8 blocks of pixels, one pixel of each block per lane
+// (lane l: column l mod 8, row l / 8).  A wave owns NK blocks, side by side
+// in rows of BX: the blocks of a whole tile, or one of them.
+template <int BX, int NK>
+struct BwdPixels {
+  float fx, fy;                   // the lane's pixel centre in block 0
+  float T[NK], dIacc[NK];         // transmittance behind the walk's position; dI . colour behind it
+  float dI[NK][3];
+  int last[NK];                   // list position after the last blended entry (0: takes no part)
+  bool inside[NK];
+  int64_t o0, HW;                 // offset of the block-0 pixel in a plane; pixels per plane
+  int W;
+  // The pixels of the blocks from pixel (x0, y0).
+  __device__ __forceinline__ BwdPixels(const RasterDev& a, int x0, int y0) {
+    const int lane = threadIdx.x & (kRasterWave - 1);
+    const int px = x0 + (lane & 7), py = y0 + (lane >> 3);
+    W = a.W;
+    HW = (int64_t)a.H * a.W;
+    o0 = (int64_t)py * a.W + px;
+    fx = (float)px + 0.5f;
+    fy = (float)py + 0.5f;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) inside[k] = px + 8 * (k % BX) < a.W && py + 8 * (k / BX) < a.H;
+  }
+  __device__ __forceinline__ int64_t offset(int k) const {
+    return o0 + (int64_t)(8 * (k / BX)) * W + 8 * (k % BX);
+  }
+  // Loads the image gradients (dimg: the slot's planes) after last is set; a
+  // pixel whose gradient is zero (a masked one) adds exactly zero to every
+  // gradient and takes no part.  Returns the wave's largest last position.
+  __device__ __forceinline__ int load_gradient(const float* __restrict__ dimg) {
+    int lmax = 0;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const int64_t o = offset(k);
+      dI[k][0] = inside[k] ? dimg[o] : 0.0f;
+      dI[k][1] = inside[k] ? dimg[HW + o] : 0.0f;
+      dI[k][2] = inside[k] ? dimg[2 * HW + o] : 0.0f;
+      if (dI[k][0] == 0.0f && dI[k][1] == 0.0f && dI[k][2] == 0.0f) last[k] = 0;
+      lmax = max(lmax, last[k]);
+    }
+    return __builtin_amdgcn_readfirstlane(wave_max_int(lmax));
+  }
+  // State behind the whole list: dI . (I - C) = dI . bg T_final.
+  __device__ __forceinline__ void final_state(int k, float T_fin, const RasterDev& a) {
+    T[k] = T_fin;
+    dIacc[k] = T_fin * (dI[k][0] * a.bg0 + dI[k][1] * a.bg1 + dI[k][2] * a.bg2);
+  }
+};
+
 // Reverse replay of list positions (lo, hi] of one tile (entries start+lo ..
-// start+hi-1, last first).  Per pixel k on entry: T[k] = transmittance after
-// position hi, dIacc[k] = dI . (colour blended behind position hi + bg T_final).
-// With a.dup_grads the entry's components go to its emission slot (s_id then
-// holds the slot index), else they are added atomically to d_rec.
-template <int TW, int TH>
+// start+hi-1, last first) for the wave's blocks, the first of which starts at
+// pixel (x0, y0).  With a.dup_grads (the wave owns the whole tile) an entry's
+// components go to its emission slot, else they are added atomically to
+// d_rec.
+// The walk is bound by vector instruction issue.  A footprint reaches 1.3 of
+// a 16x16 tile's four blocks on average (28 of 256 pixels blend at 1080p), so
+// staging tests every block's box and a visit evaluates only the blocks that
+// the entry may reach (a wave-uniform branch per block); the lanes then sum
+// their blocks and one reduction over the wave serves the whole tile.
+template <int BX, int NK>
 __device__ __forceinline__ void reverse_pass(const RasterDev& a, uint32_t start, int lo, int hi,
-                                             const float fx, const float* fy, const int* last,
-                                             float* T, float (*dI)[3], float* dIacc,
-                                             Splat* s_splat, uint32_t* s_id,
-                                             float* __restrict__ d_rec, const Scatter9& red) {
-  constexpr int PX = TileGeom<TW, TH>::PX;
-  const int lane = threadIdx.x;
+                                             int x0, int y0, BwdPixels<BX, NK>& p, Splat* s_splat,
+                                             float* __restrict__ d_rec) {
+  const int lane = threadIdx.x & (kRasterWave - 1);
   const bool det = a.dup_grads != nullptr;
   float* const gbase = det ? a.dup_grads : d_rec;
-  // the tile's pixel box
-  const float bx0 = fx - (float)(lane % TW), by0 = fy[0] - (float)(lane / TW);
-  const float bx1 = bx0 + (float)(TW - 1), by1 = by0 + (float)(TH - 1);
+  const Scatter9 red = scatter9_setup();
+  const float bx = (float)x0 + 0.5f, by = (float)y0 + 0.5f;
   for (int top = hi; top > lo; top -= kRasterWave) {
     const int bot = max(lo, top - kRasterWave);
     const int n = top - bot;
-    __syncthreads();
-    bool hit = false;
+    wave_sync();
+    uint32_t reach = 0;               // blocks the lane's entry may reach
+    uint32_t eid = 0;                 // its pair, or gradient slot
     if (lane < n) {
       const uint32_t id = a.ids[start + bot + lane];
-      const uint32_t e = det ? a.emit[start + bot + lane] : id;
-      s_id[lane] = e;
-      const Splat s = load_splat(a.rec, id);
-      hit = splat_may_hit(s, bx0, bx1, by0, by1);
+      eid = det ? a.emit[start + bot + lane] : id;
+      Splat s = load_splat(a.rec, id);
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        const float gx = bx + (float)(8 * (k % BX)), gy = by + (float)(8 * (k / BX));
+        if (splat_may_hit(s, gx, gx + 7.0f, gy, gy + 7.0f)) reach |= 1u << k;
+      }
+      s.pad1 = __builtin_amdgcn_rcpf(s.o);
+      s.pad2 = 0.5f * s.B;
       s_splat[lane] = s;
       // an entry that cannot reach the tile gets zero gradients
-      if (!hit && det && (int64_t)e < a.dup_cap) {
-        float* g = gbase + (int64_t)e * GS_DREC_STRIDE;
+      if (det && !reach && (int64_t)eid < a.dup_cap) {
+        float* g = gbase + (int64_t)eid * GS_DREC_STRIDE;
 #pragma unroll
         for (int c = 0; c < GS_DREC_STRIDE; ++c) g[c] = 0.0f;
       }
     }
-    uint64_t todo = __ballot(hit);
-    __syncthreads();
+    uint64_t todo = __ballot(reach != 0);
+    wave_sync();
     while (todo) {
-      const int j = 63 - (int)__builtin_clzll(todo);         // last first
+      const int j = 63 - (int)__builtin_clzll(todo);
       todo &= ~(1ull << j);
+      const uint32_t blocks = __builtin_amdgcn_readlane(reach, j);
+      const uint32_t entry = __builtin_amdgcn_readlane(eid, j);
       const Splat sp = s_splat[j];
       const int pos = bot + j + 1;
-      const float dx = __fsub_rn(fx, sp.mx);
-      float p2[PX];
-      splat_p2_column<PX>(sp, dx, fy, p2);
-      bool pass[PX], any = false;
+      // sums over the lane's pixels of G = dL/d(exponent) times 1, dx, dy,
+      // dx^2, dx dy, dy^2 and of the blend weight times dI
+      float sG = 0.f, sGx = 0.f, sGy = 0.f, sGxx = 0.f, sGxy = 0.f, sGyy = 0.f;
+      float sr = 0.f, sg = 0.f, sb = 0.f;
+      uint64_t hit = 0;
 #pragma unroll
-      for (int k = 0; k < PX; ++k) {
-        pass[k] = (pos <= last[k]) && splat_pass(sp, p2[k]);
-        any = any || pass[k];
-      }
-      if (!__any(any)) {
-        if (det && red.slot >= 0 && (int64_t)s_id[j] < a.dup_cap)
-          gbase[(int64_t)s_id[j] * GS_DREC_STRIDE + red.slot] = 0.0f;
-        continue;
-      }
-      // per-lane sums over the lane's pixels; the geometric gradients of the
-      // lane follow from sG = sum G, sGdy = sum G dy, sGdy2 = sum G dy^2 with
-      // G = dL/d(power) (dx is shared by the lane's column)
-      float sG = 0.f, sGdy = 0.f, sGdy2 = 0.f, so = 0.f, sr = 0.f, sg = 0.f, sb = 0.f;
-#pragma unroll
-      for (int k = 0; k < PX; ++k) {
-        if (!pass[k]) continue;
-        const float gss = splat_gauss(p2[k]);
-        const float aa = sp.o * gss;
-        const float alpha = fminf(kAlphaMax, aa);
-        const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
-        const float Tb = T[k] * inv;                 // transmittance in front of it
-        const float w = alpha * Tb;
-        const float dIc = fmaf(dI[k][2], sp.b, fmaf(dI[k][1], sp.g, dI[k][0] * sp.r));
-        const float dLda = fmaf(Tb, dIc, -inv * dIacc[k]);
-        dIacc[k] = fmaf(w, dIc, dIacc[k]);
-        T[k] = Tb;
-        sr = fmaf(dI[k][0], w, sr);
-        sg = fmaf(dI[k][1], w, sg);
-        sb = fmaf(dI[k][2], w, sb);
-        if (aa < kAlphaMax) {
-          const float G = dLda * alpha;
-          const float dy = __fsub_rn(fy[k], sp.my);
-          const float Gdy = G * dy;
-          so = fmaf(dLda, gss, so);
+      for (int k = 0; k < NK; ++k) {
+        if (NK > 1 && !(blocks & (1u << k))) continue;
+        const float dx = __fsub_rn(p.fx + (float)(8 * (k % BX)), sp.mx);
+        const float dy = __fsub_rn(p.fy + (float)(8 * (k / BX)), sp.my);
+        const float p2 = splat_p2(sp, dx, dy);
+        const uint64_t pass = splat_pass_lanes(sp, p2) & lanes_le(pos, p.last[k]);
+        hit |= pass;
+        if (lane_in(pass)) {
+          const float gss = splat_gauss(p2);
+          const float aa = sp.o * gss;
+          const float alpha = fminf(kAlphaMax, aa);
+          const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
+          const float Tb = p.T[k] * inv;                 // transmittance in front of it
+          const float w = alpha * Tb;
+          const float dIc = fmaf(p.dI[k][2], sp.b, fmaf(p.dI[k][1], sp.g, p.dI[k][0] * sp.r));
+          const float dLda = fmaf(Tb, dIc, -inv * p.dIacc[k]);
+          p.dIacc[k] = fmaf(w, dIc, p.dIacc[k]);
+          p.T[k] = Tb;
+          sr = fmaf(p.dI[k][0], w, sr);
+          sg = fmaf(p.dI[k][1], w, sg);
+          sb = fmaf(p.dI[k][2], w, sb);
+          // (the derivative through a clamped alpha is zero)
+          const float G = aa < kAlphaMax ? dLda * alpha : 0.0f;
+          const float Gx = G * dx, Gy = G * dy;
           sG += G;
-          sGdy += Gdy;
-          sGdy2 = fmaf(Gdy, dy, sGdy2);
+          sGx += Gx;
+          sGy += Gy;
+          sGxx = fmaf(Gx, dx, sGxx);
+          sGxy = fmaf(Gx, dy, sGxy);
+          sGyy = fmaf(Gy, dy, sGyy);
         }
       }
-      const float bdx = sp.B * dx;
-      // geometric gradients of the lane (constant factors applied per
-      // component after the reduction)
-      const float comp[9] = {fmaf(2.0f * sp.A * dx, sG, sp.B * sGdy),   // d mx / -ln2
-                             fmaf(2.0f * sp.C, sGdy, bdx * sG),         // d my / -ln2
-                             dx * dx * sG,                              // d Q11 / -1/2
-                             dx * sGdy,                                 // d Q12 / -1
-                             sGdy2,                                     // d Q22 / -1/2
-                             so, sr, sg, sb};
+      if (!hit) {
+        if (det && lane < GS_DREC_STRIDE && (int64_t)entry < a.dup_cap)
+          gbase[(int64_t)entry * GS_DREC_STRIDE + lane] = 0.0f;
+        continue;
+      }
+      // (constant factors applied per component after the reduction)
+      const float comp[9] = {fmaf(sp.A, sGx, sp.pad2 * sGy),    // d mx / -2 ln2
+                             fmaf(sp.C, sGy, sp.pad2 * sGx),    // d my / -2 ln2
+                             sGxx,                              // d Q11 / -1/2
+                             sGxy,                              // d Q12 / -1
+                             sGyy,                              // d Q22 / -1/2
+                             sG * sp.pad1,                      // d o
+                             sr, sg, sb};
       const float tot = reduce_scatter9(comp);
       if (red.slot >= 0) {
-        float* dst = gbase + (int64_t)s_id[j] * GS_DREC_STRIDE + red.slot;
+        float* dst = gbase + (int64_t)entry * GS_DREC_STRIDE + red.slot;
         if (!det) atomicAdd(dst, red.scale * tot);
-        else if ((int64_t)s_id[j] < a.dup_cap) *dst = red.scale * tot;
+        else if ((int64_t)entry < a.dup_cap) *dst = red.scale * tot;
       }
     }
   }
 }
 
-// Pixel geometry of one tile for the calling lane.
-template <int TW, int TH>
-struct LanePixels {
-  static constexpr int PX = TileGeom<TW, TH>::PX, RSTEP = TileGeom<TW, TH>::RSTEP;
-  int slot, px, py0, tx, ty;
-  float fx, fy[PX];
-  bool inside[PX];
-  __device__ __forceinline__ LanePixels(const RasterDev& a, int64_t tile) {
-    slot = (int)(tile / a.tiles_per_slot);
-    const int t = (int)(tile - (int64_t)slot * a.tiles_per_slot);
-    ty = t / a.tiles_x;
-    tx = t - ty * a.tiles_x;
-    const int lane = threadIdx.x;
-    px = tx * TW + (lane % TW);
-    py0 = ty * TH + lane / TW;
-    fx = (float)px + 0.5f;
-#pragma unroll
-    for (int k = 0; k < PX; ++k) {
-      const int py = py0 + k * RSTEP;
-      fy[k] = (float)py + 0.5f;
-      inside[k] = (px < a.W) && (py < a.H);
-    }
-  }
-  __device__ __forceinline__ int64_t offset(const RasterDev& a, int k) const {
-    return (int64_t)(py0 + k * RSTEP) * a.W + px;
+// Tile coordinates of a tile index.
+struct TilePos {
+  int slot, tx, ty;
+  __device__ __forceinline__ TilePos(const RasterDev& a, int64_t tile) {
+    slot = (int)((uint32_t)tile / (uint32_t)a.tiles_per_slot);
+    const uint32_t t = (uint32_t)tile - (uint32_t)slot * (uint32_t)a.tiles_per_slot;
+    ty = (int)(t / (uint32_t)a.tiles_x);
+    tx = (int)(t - (uint32_t)ty * (uint32_t)a.tiles_x);
   }
 };
 
-template <int TW, int TH, bool RECOMPUTE>
-__device__ __forceinline__ void bwd_tile(const RasterDev& a, int64_t tile, Splat* s_splat,
-                                         uint32_t* s_id, const float* __restrict__ T_final,
-                                         const int32_t* __restrict__ n_contrib,
-                                         const float* __restrict__ d_image,
-                                         float* __restrict__ d_rec) {
-  constexpr int PX = TileGeom<TW, TH>::PX;
-  const LanePixels<TW, TH> L(a, tile);
+// Whole-list backward of NK blocks of a tile from its block b.
+template <int TW, int TH, int NK, bool RECOMPUTE>
+__device__ __forceinline__ void bwd_blocks(const RasterDev& a, int64_t tile, int b, Splat* s_splat,
+                                           const float* __restrict__ T_final,
+                                           const int32_t* __restrict__ n_contrib,
+                                           const float* __restrict__ d_image,
+                                           float* __restrict__ d_rec) {
+  constexpr int BX = TW / 8;
+  static_assert(NK == 1 || NK == TW * TH / 64, "a block or the whole tile");
   const uint32_t start = a.ranges[2 * tile], end = a.ranges[2 * tile + 1];
   if (start >= end) return;
-  const int64_t HW = (int64_t)a.H * a.W;
-  float T[PX];
-  int last[PX];
-  if (RECOMPUTE) {
-    const PixBox box{(float)(L.tx * TW) + 0.5f, (float)(L.tx * TW + TW - 1) + 0.5f,
-                     (float)(L.ty * TH) + 0.5f, (float)(L.ty * TH + TH - 1) + 0.5f};
-    tile_forward<TW, TH, PX, false>(a.rec, a.ids, start, end, L.fx, L.fy, L.inside, s_splat, T,
-                                    nullptr, last, box);
+  const TilePos tp(a, tile);
+  const int x0 = tp.tx * TW + (b % BX) * 8, y0 = tp.ty * TH + (b / BX) * 8;
+  BwdPixels<BX, NK> p(a, x0, y0);
+  float T_fin[NK];
+  if constexpr (RECOMPUTE) {
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const float kx = (float)(8 * (k % BX)), ky = (float)(8 * (k / BX));
+      const PixBox box{(float)x0 + kx + 0.5f, (float)x0 + kx + 7.5f, (float)y0 + ky + 0.5f,
+                       (float)y0 + ky + 7.5f};
+      const float fy = p.fy + ky;
+      tile_forward<TW, TH, 1, false>(a.rec, a.ids, start, end, p.fx + kx, &fy, &p.inside[k],
+                                     s_splat, &T_fin[k], nullptr, &p.last[k], box);
+    }
   } else {
 #pragma unroll
-    for (int k = 0; k < PX; ++k) {
-      const int64_t o = (int64_t)L.slot * HW + L.offset(a, k);
-      T[k] = L.inside[k] ? T_final[o] : 1.0f;
-      last[k] = L.inside[k] ? n_contrib[o] : 0;
+    for (int k = 0; k < NK; ++k) {
+      const int64_t o = (int64_t)tp.slot * p.HW + p.offset(k);
+      T_fin[k] = p.inside[k] ? T_final[o] : 1.0f;
+      p.last[k] = p.inside[k] ? n_contrib[o] : 0;
     }
   }
-  // dIacc = dI . (sum of the colour blended behind + bg T_final), per pixel
-  float dI[PX][3], dIacc[PX];
-  const float* dimg = d_image + (int64_t)L.slot * 3 * HW;
+  const int lmax = min(p.load_gradient(d_image + (int64_t)tp.slot * 3 * p.HW), (int)(end - start));
 #pragma unroll
-  for (int k = 0; k < PX; ++k) {
-    const int64_t o = L.offset(a, k);
-    dI[k][0] = L.inside[k] ? dimg[o] : 0.0f;
-    dI[k][1] = L.inside[k] ? dimg[HW + o] : 0.0f;
-    dI[k][2] = L.inside[k] ? dimg[2 * HW + o] : 0.0f;
-    dIacc[k] = T[k] * (dI[k][0] * a.bg0 + dI[k][1] * a.bg1 + dI[k][2] * a.bg2);
-    // a pixel with a zero image gradient (a masked one) adds exactly zero
-    // to every gradient: it takes no part in the reverse pass
-    if (dI[k][0] == 0.0f && dI[k][1] == 0.0f && dI[k][2] == 0.0f) last[k] = 0;
-  }
-  int lmax = 0;
-#pragma unroll
-  for (int k = 0; k < PX; ++k) lmax = max(lmax, last[k]);
-  lmax = min(wave_max_int(lmax), (int)(end - start));
-  reverse_pass<TW, TH>(a, start, 0, lmax, L.fx, L.fy, last, T, dI, dIacc, s_splat, s_id, d_rec,
-                       scatter9_setup());
+  for (int k = 0; k < NK; ++k) p.final_state(k, T_fin[k], a);
+  reverse_pass<BX, NK>(a, start, 0, lmax, x0, y0, p, s_splat, d_rec);
   if (a.dup_grads) zero_dup_slots(a, start, lmax, (int)(end - start));
 }
 
-template <int TW, int TH, bool RECOMPUTE>
+// Whole-list backward.  Without chunks a tile's list is one serial walk, and
+// the call takes as long as its longest lists; in the atomic form every block
+// of a tile therefore has its own wave (NK = 1; the NB waves of a tile are
+// adjacent launches).  The deterministic form stores an entry's sums over the
+// whole tile, so one wave takes the tile (NK = NB).
+template <int TW, int TH, int NK, bool RECOMPUTE>
 __global__ __launch_bounds__(kRasterWave) void k_raster_bwd(RasterDev a, TileSched sch,
                                                             const float* __restrict__ T_final,
                                                             const int32_t* __restrict__ n_contrib,
                                                             const float* __restrict__ d_image,
                                                             float* __restrict__ d_rec) {
+  constexpr int NB = TW * TH / 64 / NK;
   __shared__ Splat s_splat[kRasterWave];
-  __shared__ uint32_t s_id[kRasterWave];
-  for_each_tile(sch, a.n_tiles, [&](int64_t tile) {
-    bwd_tile<TW, TH, RECOMPUTE>(a, tile, s_splat, s_id, T_final, n_contrib, d_image, d_rec);
+  for_each_tile<NB>(sch, a.n_tiles, [&](int64_t tile, int b) {
+    bwd_blocks<TW, TH, NK, RECOMPUTE>(a, tile, b, s_splat, T_final, n_contrib, d_image, d_rec);
   });
 }
 
-// Chunked backward: one work-group per (tile, chunk) item.  Chunk c covers
-// list positions (c*chunk, min((c+1)*chunk, len)]; the state after its last
+// Chunked backward: one wave per (tile, chunk) item.  Chunk c covers list
+// positions (c*chunk, min((c+1)*chunk, len)]; the state after its last
 // position is the forward's final state for pixels whose last blended entry
 // lies at or before it, else the checkpoint (T_c, U_c) the forward stored
 // there (dI . acc = T_c dI . U_c).
@@ -715,55 +757,41 @@ void k_raster_bwd_chunked(
     RasterDev a, ChunkDev ch, const float* __restrict__ T_final,
     const int32_t* __restrict__ n_contrib, const float* __restrict__ d_image,
     float* __restrict__ d_rec) {
-  constexpr int PX = TileGeom<TW, TH>::PX;
+  constexpr int BX = TW / 8, NK = TW * TH / 64;
   __shared__ Splat s_splat[kRasterWave];
-  __shared__ uint32_t s_id[kRasterWave];
   const uint32_t item = blockIdx.x;
   if (item >= ch.offset[a.n_tiles]) return;
   const int64_t tile = ch.items[item];
-  const int c = (int)(item - ch.offset[tile]);
+  const uint32_t c0 = ch.offset[tile];
+  const int c = (int)(item - c0);
   const uint32_t start = a.ranges[2 * tile], end = a.ranges[2 * tile + 1];
   const int len = (int)(end - start);
   const int lo = c * ch.chunk, hi_pos = min(lo + ch.chunk, len);
-  const LanePixels<TW, TH> L(a, tile);
-  const int64_t HW = (int64_t)a.H * a.W;
-  int last[PX];
-  float T[PX], dI[PX][3], dIacc[PX];
-  const float* dimg = d_image + (int64_t)L.slot * 3 * HW;
-  int lmax = 0;
+  const TilePos tp(a, tile);
+  const int x0 = tp.tx * TW, y0 = tp.ty * TH;
+  BwdPixels<BX, NK> p(a, x0, y0);
 #pragma unroll
-  for (int k = 0; k < PX; ++k) {
-    const int64_t o = L.offset(a, k);
-    last[k] = L.inside[k] ? n_contrib[(int64_t)L.slot * HW + o] : 0;
-    dI[k][0] = L.inside[k] ? dimg[o] : 0.0f;
-    dI[k][1] = L.inside[k] ? dimg[HW + o] : 0.0f;
-    dI[k][2] = L.inside[k] ? dimg[2 * HW + o] : 0.0f;
-    // a pixel with a zero image gradient (a masked one) adds exactly zero
-    // to every gradient: it takes no part in the reverse pass
-    if (dI[k][0] == 0.0f && dI[k][1] == 0.0f && dI[k][2] == 0.0f) last[k] = 0;
-    lmax = max(lmax, last[k]);
-  }
-  const int hi = min(wave_max_int(lmax), hi_pos);
+  for (int k = 0; k < NK; ++k)
+    p.last[k] = p.inside[k] ? n_contrib[(int64_t)tp.slot * p.HW + p.offset(k)] : 0;
+  const int hi = min(p.load_gradient(d_image + (int64_t)tp.slot * 3 * p.HW), hi_pos);
   if (hi <= lo) {
     if (a.dup_grads) zero_dup_slots(a, start, lo, hi_pos);
     return;
   }
-  const float4* ck = ch.ck + ((int64_t)ch.offset[tile] + c) * (TW * TH);
+  const int lane = threadIdx.x;
+  const float4* ck = ch.ck + ((int64_t)c0 + c) * (TW * TH) + (lane >> 3) * TW + (lane & 7);
 #pragma unroll
-  for (int k = 0; k < PX; ++k) {
-    const int64_t o = L.offset(a, k);
-    if (!L.inside[k] || last[k] <= hi_pos) {
-      // nothing blended after this chunk: final state, I - C_final = bg T_final
-      T[k] = L.inside[k] ? T_final[(int64_t)L.slot * HW + o] : 1.0f;
-      dIacc[k] = T[k] * (dI[k][0] * a.bg0 + dI[k][1] * a.bg1 + dI[k][2] * a.bg2);
+  for (int k = 0; k < NK; ++k) {
+    if (!p.inside[k] || p.last[k] <= hi_pos) {
+      // nothing blended after this chunk: final state
+      p.final_state(k, p.inside[k] ? T_final[(int64_t)tp.slot * p.HW + p.offset(k)] : 1.0f, a);
     } else {
-      const float4 s = ck[threadIdx.x + k * kRasterWave];   // (T_c, U_c)
-      T[k] = s.x;
-      dIacc[k] = s.x * (dI[k][0] * s.y + dI[k][1] * s.z + dI[k][2] * s.w);
+      const float4 s = ck[8 * (k / BX) * TW + 8 * (k % BX)];   // (T_c, U_c)
+      p.T[k] = s.x;
+      p.dIacc[k] = s.x * (p.dI[k][0] * s.y + p.dI[k][1] * s.z + p.dI[k][2] * s.w);
     }
   }
-  reverse_pass<TW, TH>(a, start, lo, hi, L.fx, L.fy, last, T, dI, dIacc, s_splat, s_id, d_rec,
-                       scatter9_setup());
+  reverse_pass<BX, NK>(a, start, lo, hi, x0, y0, p, s_splat, d_rec);
   if (a.dup_grads) zero_dup_slots(a, start, hi, hi_pos);
 }
 
@@ -972,6 +1000,34 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_bwd_chunked_q(
 
 // ---------------------------------------------------------------- split forward
 
+// Pixel geometry of one tile for the calling lane.
+template <int TW, int TH>
+struct LanePixels {
+  static constexpr int PX = TileGeom<TW, TH>::PX, RSTEP = TileGeom<TW, TH>::RSTEP;
+  int slot, px, py0, tx, ty;
+  float fx, fy[PX];
+  bool inside[PX];
+  __device__ __forceinline__ LanePixels(const RasterDev& a, int64_t tile) {
+    slot = (int)(tile / a.tiles_per_slot);
+    const int t = (int)(tile - (int64_t)slot * a.tiles_per_slot);
+    ty = t / a.tiles_x;
+    tx = t - ty * a.tiles_x;
+    const int lane = threadIdx.x;
+    px = tx * TW + (lane % TW);
+    py0 = ty * TH + lane / TW;
+    fx = (float)px + 0.5f;
+#pragma unroll
+    for (int k = 0; k < PX; ++k) {
+      const int py = py0 + k * RSTEP;
+      fy[k] = (float)py + 0.5f;
+      inside[k] = (px < a.W) && (py < a.H);
+    }
+  }
+  __device__ __forceinline__ int64_t offset(const RasterDev& a, int k) const {
+    return (int64_t)(py0 + k * RSTEP) * a.W + px;
+  }
+};
+
 // Forward of long tile lists in parallel (stored mode with chunk items).
 // Part 1: one wave per chunk item (tile, c) composites the chunk's entries
 // for the tile's pixels from a local transmittance of 1, ignoring the stop
@@ -1073,7 +1129,7 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
   constexpr int PX = TileGeom<TW, TH>::PX, NP = TW * TH;
   constexpr int D = PX >= 4 ? 1 : 4 / PX;
   __shared__ Splat s_splat[kRasterWave];
-  for_each_tile(sch, a.n_tiles, [&](int64_t tile) {
+  for_each_tile(sch, a.n_tiles, [&](int64_t tile, int) {
     const LanePixels<TW, TH> L(a, tile);
     const int lane = threadIdx.x;
     const uint32_t start = a.ranges[2 * tile], end = a.ranges[2 * tile + 1];
@@ -1438,12 +1494,20 @@ static void launch_bwd(const RasterDev& a, const Launch& L, const float* T_final
   else if (mode == GS_BWD_STORED && L.ch.chunk > 0)
     hipLaunchKernelGGL((k_raster_bwd_chunked<TW, TH>), dim3((unsigned)L.max_items),
                        dim3(kRasterWave), 0, s, a, L.ch, T_final, n_contrib, d_image, d_rec);
-  else if (mode == GS_BWD_RECOMPUTE)
-    hipLaunchKernelGGL((k_raster_bwd<TW, TH, true>), dim3(L.blocks), dim3(kRasterWave), 0, s, a,
-                       L.sch, T_final, n_contrib, d_image, d_rec);
-  else
-    hipLaunchKernelGGL((k_raster_bwd<TW, TH, false>), dim3(L.blocks), dim3(kRasterWave), 0, s, a,
-                       L.sch, T_final, n_contrib, d_image, d_rec);
+  else {
+    // whole lists: a wave per 8x8 block, or per tile where gradients are stored
+    constexpr int NB = TW * TH / 64;
+    const bool rec = mode == GS_BWD_RECOMPUTE;
+    const dim3 blocks(a.dup_grads || L.sch.queue ? L.blocks : L.blocks * NB);
+#define GS_BWD_LAUNCH(NK, REC)                                                                \
+  hipLaunchKernelGGL((k_raster_bwd<TW, TH, NK, REC>), blocks, dim3(kRasterWave), 0, s, a,     \
+                     L.sch, T_final, n_contrib, d_image, d_rec)
+    if (a.dup_grads && rec) GS_BWD_LAUNCH(NB, true);
+    else if (a.dup_grads) GS_BWD_LAUNCH(NB, false);
+    else if (rec) GS_BWD_LAUNCH(1, true);
+    else GS_BWD_LAUNCH(1, false);
+#undef GS_BWD_LAUNCH
+  }
 }
 
 // Tile shapes with a compiled rasteriser.
