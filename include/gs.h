@@ -225,10 +225,11 @@ gs_status gs_bin_sort(const gs_projected* proj, const gs_views* views,
  * and the backward starts each item from them.
  *   chunk_offset [n_tiles + 1], chunk_items [max_items]: from gs_chunk_items
  *   after gs_bin_sort (the same plan must be passed to both raster calls).
- * fwd_waves: waves per tile in the forward (0 or 1 = one wave per tile; 2 or
- * 4 split the tile's pixels over that many waves of one work-group, which
- * shortens the longest tiles; must divide tile_w * tile_h / 64; not with a
- * queue).
+ * fwd_waves: waves per tile in the forward (2 or 4 split the tile's pixels
+ * over that many waves of one work-group, which shortens the longest tiles;
+ * must divide tile_w * tile_h / 64; not with a queue).  0 or 1 leave the
+ * choice to the library (one wave with a queue, else the most of 4 that the
+ * tile's pixels allow); images do not depend on it.
  * Split forward (fwd_split = 1, chunked STORED mode only): the forward
  * composites every chunk item in parallel from a local transmittance of 1
  * (one wave per item; chunk_last [max_items][tile_w*tile_h] u16 device

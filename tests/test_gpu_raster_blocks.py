@@ -2,7 +2,8 @@
 the last tiles hold blocks that are partly or wholly outside the image, in
 every launch form of the backward (whole lists by block, whole lists by tile
 with stored sums, chunks, recomputed transmittance; default, longest-first and
-queue order), against the oracle under the bound the other raster tests use."""
+queue order), against the oracle under the bound the other raster tests use;
+and the forward's own choice of waves per tile against one wave per tile."""
 import numpy as np
 import pytest
 
@@ -60,3 +61,20 @@ def test_backward_by_blocks_matches_oracle(inputs, tile, form):
         ref = np.concatenate([o["d_mean2d"], o["d_conic"], o["d_opacity"][None], o["d_rgb"]]).T
         ok, worst = grad_tolerance_check(got, ref, o["term_mass"].T, o["amb_mass"].T)
         assert ok, worst
+
+
+@pytest.mark.parametrize("tile", TILES, ids=lambda t: "%dx%d" % t)
+def test_forward_choice_of_waves_gives_identical_results(inputs, tile):
+    from paper_2509_12138_amd import ops
+    say("forward waves", tile)
+    cams, _, refs = inputs
+    rec, tb, nt, _ = refs[tile]
+    views = ops.Views.single(N, cams)
+    out = []
+    for sched in ("default", "persistent"):                 # a queue runs one wave per tile
+        bufs = ops.RasterBuffers(views, W, H, tile)
+        bufs.set_schedule(sched)
+        raster_records(bufs, rec, tb, nt, BG, torch)
+        out.append([t.cpu().numpy() for t in (bufs.image, bufs.T_final, bufs.n_contrib)])
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(a, b)
