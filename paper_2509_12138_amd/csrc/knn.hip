@@ -3,19 +3,25 @@
 // the learned initialisation reads 16-NN features).
 //
 // Device pipeline (sizes that depend on the data stay on the device):
-//   k_bbox_partial / k_grid_params   bounding box -> uniform grid (cell edge
-//                                    (volume / n)^(1/3), capped cell count)
-//   k_cell_count                     cell of each point, per-cell counts
-//   k_scan_*                         exclusive scan of the counts
+//   k_bbox_partial / k_grid_params   bounding box -> uniform grid whose cell
+//                                    edge suits the points' occupancy
+//   k_cell_zero, k_cell_count        cell of each point, its rank there and
+//                                    the per-cell counts
+//   k_knn_scan_*                     exclusive scan of the counts
 //   k_cell_scatter                   points grouped by cell (float4 x,y,z,id)
 //   k_query                          one thread per point, in cell order for
-//                                    cache locality: cells in growing
-//                                    Chebyshev shells until the k-th best
-//                                    distance is within the distance to the
-//                                    searched box (exact); the K best
-//                                    (distance^2, index) pairs stay sorted in
-//                                    registers, ties broken by index.
+//                                    cache locality: the 3x3x3 box around the
+//                                    point's cell, then growing Chebyshev
+//                                    shells (of cells, then of blocks of
+//                                    cells), until the k-th best distance is
+//                                    within the distance to the searched box
+//                                    (exact); the K best (distance^2, index)
+//                                    pairs stay sorted in registers, ties
+//                                    broken by index.
 #include <math.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "gs_device.h"
 
@@ -23,49 +29,96 @@ namespace gsmi {
 
 constexpr int kKnnThreads = 256;
 constexpr int kKnnScanPer = 8;
+constexpr int kBlockShift = 2, kBlock = 1 << kBlockShift;   // cells per block edge
 constexpr int kKnnScanItems = kKnnThreads * kKnnScanPer;
 
 struct GridParams {
   float lo[3];
   float h, inv_h;
   int g[3];
-  int64_t n_cells;
+  int bg[3];            // blocks of kBlock^3 cells per axis
+  int64_t n_cells, n_blocks;
+  uint32_t n_far;       // points left to k_query_far
 };
 
 static inline size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// Sample points for the choice of the grid: of the array's 256-point spans
+// every `span`-th gives those of its points whose place is a multiple of
+// 1 << shift, at most kSample in all.  Written together by the blocks that
+// read them (a work-group gathering them afterwards took 35 us).
+constexpr int kSample = 8192;
+
+struct KnnSample {
+  uint32_t span;
+  int shift;
+};
+
+static KnnSample knn_sample(int64_t nb_pts) {
+  KnnSample S{1u, 8};
+  if (nb_pts >= kSample) S.span = (uint32_t)ceil_div(nb_pts, kSample);
+  else
+    while (S.shift > 0 && nb_pts << (8 - S.shift + 1) <= kSample) --S.shift;
+  return S;
+}
+
+// Cells per point that the grid may have.  Isosurface points fill few of a
+// volume's cells: with one cell per point 4M points of a closed surface put
+// 60 into each occupied cell, and a query compared some 600 of them.  16
+// cells per point (64 bytes of counts) leave 10 there: the 16-NN search of
+// those points took 22.2 ms, and takes 1.48 ms (250 us more for the larger
+// table); 1M points of a volume 5.4 -> 0.67 ms.
+constexpr int64_t kCellsPerPoint = 16;
+constexpr int64_t kMaxBboxBlocks = 1024;
+
 struct KnnLayout {
-  int64_t max_cells, nb_pts, nb_scan;
-  size_t off_part, off_params, off_cell, off_count, off_cursor, off_sorted, off_bsum, total;
+  int64_t max_cells, nb_pts, nb_bbox, nb_scan;
+  size_t off_part, off_sample, off_params, off_cell, off_rank, off_count, off_block, off_sorted, off_bsum,
+      total;
 };
 
 static KnnLayout knn_layout(int64_t n) {
   KnnLayout L;
-  L.max_cells = 2 * (n > 0 ? n : 1) + 1024;
-  L.nb_pts = ceil_div(n > 0 ? n : 1, kKnnThreads);
+  const int64_t m = n > 0 ? n : 1;
+  L.max_cells = std::min<int64_t>(kCellsPerPoint * m + 1024, int64_t(1) << 31);
+  L.nb_pts = ceil_div(m, kKnnThreads);
+  L.nb_bbox = std::min(L.nb_pts, kMaxBboxBlocks);
   L.nb_scan = ceil_div(L.max_cells + 1, kKnnScanItems);
   size_t o = 0;
-  L.off_part = o; o += a256(sizeof(float) * 6 * (size_t)L.nb_pts);
+  L.off_part = o; o += a256(sizeof(float) * 6 * (size_t)L.nb_bbox);
+  L.off_sample = o; o += a256(sizeof(float) * 3 * kSample);
   L.off_params = o; o += a256(sizeof(GridParams));
-  L.off_cell = o; o += a256(sizeof(uint32_t) * (size_t)(n > 0 ? n : 1));
+  L.off_cell = o; o += a256(sizeof(uint32_t) * (size_t)m);
+  L.off_rank = o; o += a256(sizeof(uint32_t) * (size_t)m);
   L.off_count = o; o += a256(sizeof(uint32_t) * (size_t)(L.max_cells + 1));
-  L.off_cursor = o; o += a256(sizeof(uint32_t) * (size_t)L.max_cells);
-  L.off_sorted = o; o += a256(sizeof(float4) * (size_t)(n > 0 ? n : 1));
+  // (thin grids have up to a block per kBlock cells)
+  L.off_block = o; o += a256((size_t)(L.max_cells / kBlock + 1024));
+  L.off_sorted = o; o += a256(sizeof(float4) * (size_t)m);
   L.off_bsum = o; o += a256(sizeof(uint32_t) * (size_t)L.nb_scan);
   L.total = o;
   return L;
 }
 
+// Block bounding boxes part[block][6] and the sample [3][kSample] (NaN past
+// the last point).
 __global__ __launch_bounds__(kKnnThreads) void k_bbox_partial(const float* __restrict__ pts,
-                                                              int64_t n, float* __restrict__ part) {
+                                                              int64_t n, KnnSample smp,
+                                                              float* __restrict__ part,
+                                                              float* __restrict__ sample) {
   __shared__ float sm[6][kKnnThreads / 64];
-  const int64_t i = (int64_t)blockIdx.x * kKnnThreads + threadIdx.x;
-  float v[6];
+  float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  for (int64_t u = blockIdx.x; u * kKnnThreads < n; u += gridDim.x) {
+    const int64_t i = u * kKnnThreads + threadIdx.x;
+    const uint32_t su = (uint32_t)u / smp.span;
+    const bool take = su * smp.span == (uint32_t)u && (threadIdx.x & ((1u << smp.shift) - 1)) == 0;
+    const uint32_t slot = (su << (8 - smp.shift)) + (threadIdx.x >> smp.shift);
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const float x = i < n ? pts[a * n + i] : 0.0f;
-    v[a] = i < n ? x : INFINITY;
-    v[3 + a] = i < n ? x : -INFINITY;
+    for (int a = 0; a < 3; ++a) {
+      const float x = i < n ? pts[a * n + i] : __builtin_nanf("");
+      v[a] = fminf(v[a], x);
+      v[3 + a] = fmaxf(v[3 + a], x);
+      if (take) sample[a * kSample + slot] = x;
+    }
   }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1)
@@ -86,51 +139,150 @@ __global__ __launch_bounds__(kKnnThreads) void k_bbox_partial(const float* __res
   }
 }
 
-__global__ void k_grid_params(const float* __restrict__ part, int64_t nb, int64_t n,
-                              int64_t max_cells, GridParams* __restrict__ P) {
-  if (threadIdx.x != 0) return;
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int64_t b = 0; b < nb; ++b)
-    for (int a = 0; a < 3; ++a) {
-      lo[a] = fminf(lo[a], part[b * 6 + a]);
-      hi[a] = fmaxf(hi[a], part[b * 6 + 3 + a]);
-    }
-  float ext[3], vol = 1.0f, emax = 0.0f;
-  for (int a = 0; a < 3; ++a) {
-    ext[a] = fmaxf(hi[a] - lo[a], 0.0f);
-    emax = fmaxf(emax, ext[a]);
-  }
-  if (!(emax > 0.0f)) emax = 1.0f;
-  for (int a = 0; a < 3; ++a) vol *= fmaxf(ext[a], emax * 1e-3f);
-  float h = cbrtf(vol / (float)(n > 0 ? n : 1));
-  h = fmaxf(h, emax * 1e-6f);
-  int g[3];
+__device__ __forceinline__ int cell_coord(float x, float lo, float inv_h, int g) {
+  return min(max((int)floorf((x - lo) * inv_h), 0), g - 1);
+}
+
+// Sets the grid's edge and dimensions (at most max_cells cells) for a wanted
+// edge h.
+__device__ __forceinline__ void grid_dims(const float (&ext)[3], float h, int64_t max_cells,
+                                          GridParams& G) {
   for (int it = 0; it < 64; ++it) {
     int64_t cells = 1;
     for (int a = 0; a < 3; ++a) {
-      g[a] = max(1, (int)ceilf(ext[a] / h) + 1);
-      cells *= g[a];
+      G.g[a] = max(1, (int)ceilf(ext[a] / h) + 1);
+      cells *= G.g[a];
     }
     if (cells <= max_cells) break;
     h *= 1.25f;
   }
-  for (int a = 0; a < 3; ++a) {
-    P->lo[a] = lo[a];
-    P->g[a] = g[a];
-  }
-  P->h = h;
-  P->inv_h = 1.0f / h;
-  P->n_cells = (int64_t)g[0] * g[1] * g[2];
+  G.h = h;
+  G.inv_h = 1.0f / h;
+  G.n_cells = (int64_t)G.g[0] * G.g[1] * G.g[2];
+  for (int a = 0; a < 3; ++a) G.bg[a] = ((G.g[a] - 1) >> kBlockShift) + 1;
+  G.n_blocks = (int64_t)G.bg[0] * G.bg[1] * G.bg[2];
 }
 
-__device__ __forceinline__ int cell_coord(float x, float lo, float inv_h, int g) {
-  return min(max((int)floorf((x - lo) * inv_h), 0), g - 1);
+// One work-group: bounding box of the block boxes, then the grid.  A grid of
+// one cell per point suits points that fill the volume.  How the points lie
+// is measured on the sample (ns points, NaN ones aside): with h0 the edge of a
+// grid of one cell per sample point, N2 and N4 cells of edge 2 h0 and 4 h0
+// hold points.  In a volume N2 / N4 is near 8; where it is near 4 the points
+// lie on a surface, the number of occupied cells grows as 1 / h^2, and the
+// edge is taken that gives `per_cell` points of all n to an occupied cell.
+// (The search is exact for any edge.)
+constexpr float kSurfaceRatio = 5.5f;
+constexpr int kParamThreads = 1024;
+
+__global__ __launch_bounds__(kParamThreads) void k_grid_params(
+    const float* __restrict__ part, int64_t nb, const float* __restrict__ sample, int ns, int64_t n,
+    int64_t max_cells, float per_cell, GridParams* __restrict__ P) {
+  constexpr int kWords = (kSample + 1024) / 32;
+  __shared__ float sm[6][kParamThreads / 64];
+  __shared__ uint32_t bits[2][kWords];
+  __shared__ GridParams G;
+  __shared__ float s_ext[3];
+  __shared__ int occupied[2];
+  const int t = threadIdx.x;
+  float v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  for (int64_t b = t; b < nb; b += kParamThreads)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      v[a] = fminf(v[a], part[b * 6 + a]);
+      v[3 + a] = fmaxf(v[3 + a], part[b * 6 + 3 + a]);
+    }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      v[a] = fminf(v[a], __shfl_xor(v[a], d, 64));
+      v[3 + a] = fmaxf(v[3 + a], __shfl_xor(v[3 + a], d, 64));
+    }
+  if ((t & 63) == 0)
+#pragma unroll
+    for (int a = 0; a < 6; ++a) sm[a][t >> 6] = v[a];
+  for (int i = t; i < kWords; i += kParamThreads) bits[0][i] = bits[1][i] = 0u;
+  constexpr int kPer = kSample / kParamThreads;
+  float sx[kPer], sy[kPer], sz[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int k = min(t + q * kParamThreads, ns - 1);
+    sx[q] = sample[k];
+    sy[q] = sample[kSample + k];
+    sz[q] = sample[2 * kSample + k];
+  }
+  __syncthreads();
+  float vol = 1.0f, emax = 0.0f;
+  if (t == 0) {
+    for (int a = 0; a < 3; ++a) {
+      float lo = sm[a][0], hi = sm[3 + a][0];
+      for (int w = 1; w < kParamThreads / 64; ++w) {
+        lo = fminf(lo, sm[a][w]);
+        hi = fmaxf(hi, sm[3 + a][w]);
+      }
+      G.lo[a] = lo;
+      s_ext[a] = fmaxf(hi - lo, 0.0f);
+      emax = fmaxf(emax, s_ext[a]);
+    }
+    if (!(emax > 0.0f)) emax = 1.0f;
+    for (int a = 0; a < 3; ++a) vol *= fmaxf(s_ext[a], emax * 1e-3f);
+    const float ext[3] = {s_ext[0], s_ext[1], s_ext[2]};
+    grid_dims(ext, fmaxf(cbrtf(vol / (float)ns), emax * 1e-6f), kSample, G);
+    occupied[0] = occupied[1] = 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    if (t + q * kParamThreads >= ns || !(sx[q] == sx[q])) continue;
+    const int cx = cell_coord(sx[q], G.lo[0], G.inv_h, G.g[0]);
+    const int cy = cell_coord(sy[q], G.lo[1], G.inv_h, G.g[1]);
+    const int cz = cell_coord(sz[q], G.lo[2], G.inv_h, G.g[2]);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int s = e + 1, gx = ((G.g[0] - 1) >> s) + 1, gy = ((G.g[1] - 1) >> s) + 1;
+      const int c = ((cz >> s) * gy + (cy >> s)) * gx + (cx >> s);
+      atomicOr(&bits[e][c >> 5], 1u << (c & 31));
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    int occ = 0;
+    for (int i = t; i < kWords; i += kParamThreads) occ += __popc(bits[e][i]);
+    if (occ) atomicAdd(&occupied[e], occ);
+  }
+  __syncthreads();
+  if (t == 0) {
+    const float ext[3] = {s_ext[0], s_ext[1], s_ext[2]};
+    const float n2 = (float)occupied[0], n4 = (float)occupied[1];
+    float h = cbrtf(vol / (float)n);                            // one cell per point
+    if (n2 < kSurfaceRatio * n4)
+      h = fminf(h, fmaxf(2.0f * G.h * sqrtf(per_cell * n2 / (float)n),
+                         cbrtf(vol / ((float)max_cells * 0.8f))));
+    grid_dims(ext, fmaxf(h, emax * 1e-6f), max_cells, G);
+    G.n_far = 0;
+    *P = G;
+  }
+}
+
+// Clears the counts of the grid's cells and the entry that closes the last
+// one, and the blocks' marks.
+__global__ __launch_bounds__(kKnnThreads) void k_cell_zero(const GridParams* __restrict__ P,
+                                                           uint4* __restrict__ count,
+                                                           uint4* __restrict__ block) {
+  const int64_t words = (P->n_cells + 1 + 3) / 4, bwords = (P->n_blocks + 15) / 16;
+  const int64_t i0 = (int64_t)blockIdx.x * kKnnThreads + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * kKnnThreads;
+  for (int64_t i = i0; i < words; i += step) count[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (int64_t i = i0; i < bwords; i += step) block[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 __global__ __launch_bounds__(kKnnThreads) void k_cell_count(const float* __restrict__ pts, int64_t n,
                                                             const GridParams* __restrict__ P,
                                                             uint32_t* __restrict__ cell,
-                                                            uint32_t* __restrict__ count) {
+                                                            uint32_t* __restrict__ rank,
+                                                            uint32_t* __restrict__ count,
+                                                            uint8_t* __restrict__ block) {
   const int64_t i = (int64_t)blockIdx.x * kKnnThreads + threadIdx.x;
   if (i >= n) return;
   const GridParams G = *P;
@@ -139,103 +291,248 @@ __global__ __launch_bounds__(kKnnThreads) void k_cell_count(const float* __restr
   const int cz = cell_coord(pts[2 * n + i], G.lo[2], G.inv_h, G.g[2]);
   const uint32_t c = (uint32_t)(((int64_t)cz * G.g[1] + cy) * G.g[0] + cx);
   cell[i] = c;
-  atomicAdd(&count[c], 1u);
+  const uint32_t r = atomicAdd(&count[c], 1u);
+  rank[i] = r;
+  // (the first point of a cell marks its block; equal stores may race)
+  if (r == 0u)
+    block[((int64_t)(cz >> kBlockShift) * G.bg[1] + (cy >> kBlockShift)) * G.bg[0] +
+          (cx >> kBlockShift)] = 1;
 }
 
 // exclusive scan of count[0 .. n_cells] (n_cells read from P) in place; the
-// extra entry (zero before the scan) becomes n and closes the last cell
+// extra entry (zero before the scan) becomes n and closes the last cell.
+// Blocks past the grid's cells return at once.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t u = __shfl_up(v, d, 64);
+    if ((int)(threadIdx.x & 63) >= d) v += u;
+  }
+  return v;
+}
+
+// Exclusive prefix over the block's threads; total in every thread.
+template <int THREADS>
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* sm, uint32_t& total) {
+  const int w = threadIdx.x >> 6;
+  const uint32_t inc = wave_scan(v);
+  if ((threadIdx.x & 63) == 63) sm[w] = inc;
+  __syncthreads();
+  uint32_t base = 0, tot = 0;
+#pragma unroll
+  for (int k = 0; k < THREADS / 64; ++k) {
+    if (k < w) base += sm[k];
+    tot += sm[k];
+  }
+  __syncthreads();
+  total = tot;
+  return base + inc - v;
+}
+
+// A thread's kKnnScanPer consecutive counts (0 past nc), as 16-byte words.
+__device__ __forceinline__ void load_counts(const uint32_t* __restrict__ count, int64_t i0,
+                                            int64_t nc, uint32_t (&v)[kKnnScanPer]) {
+#pragma unroll
+  for (int q = 0; q < kKnnScanPer / 4; ++q) {
+    uint4 w = make_uint4(0u, 0u, 0u, 0u);
+    if (i0 + 4 * q < nc) w = *reinterpret_cast<const uint4*>(count + i0 + 4 * q);
+    v[4 * q] = w.x;
+    v[4 * q + 1] = w.y;
+    v[4 * q + 2] = w.z;
+    v[4 * q + 3] = w.w;
+  }
+#pragma unroll
+  for (int k = 0; k < kKnnScanPer; ++k)
+    if (i0 + k >= nc) v[k] = 0u;
+}
+
 __global__ __launch_bounds__(kKnnThreads) void k_knn_scan_reduce(const uint32_t* __restrict__ count,
                                                                  const GridParams* __restrict__ P,
                                                                  uint32_t* __restrict__ bsum) {
+  __shared__ uint32_t sm[kKnnThreads / 64];
   const int64_t nc = P->n_cells + 1;
   const int64_t base = (int64_t)blockIdx.x * kKnnScanItems;
-  uint32_t s = 0;
-  for (int k = 0; k < kKnnScanPer; ++k) {
-    const int64_t i = base + k * kKnnThreads + threadIdx.x;
-    if (i < nc) s += count[i];
-  }
-  __shared__ uint32_t sm[kKnnThreads];
-  sm[threadIdx.x] = s;
-  __syncthreads();
-  for (int d = kKnnThreads / 2; d > 0; d >>= 1) {
-    if (threadIdx.x < d) sm[threadIdx.x] += sm[threadIdx.x + d];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) bsum[blockIdx.x] = sm[0];
+  if (base >= nc) return;
+  uint32_t v[kKnnScanPer], s = 0, total;
+  load_counts(count, base + threadIdx.x * kKnnScanPer, nc, v);
+#pragma unroll
+  for (int k = 0; k < kKnnScanPer; ++k) s += v[k];
+  block_scan<kKnnThreads>(s, sm, total);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kKnnThreads) void k_knn_scan_top(uint32_t* __restrict__ bsum, int64_t nb) {
-  if (threadIdx.x != 0) return;
-  uint32_t run = 0;
-  for (int64_t b = 0; b < nb; ++b) {
-    const uint32_t x = bsum[b];
-    bsum[b] = run;
-    run += x;
+constexpr int kTopThreads = 1024;
+
+__global__ __launch_bounds__(kTopThreads) void k_knn_scan_top(const GridParams* __restrict__ P,
+                                                              uint32_t* __restrict__ bsum) {
+  __shared__ uint32_t sm[kTopThreads / 64];
+  const int64_t nb = (P->n_cells + 1 + kKnnScanItems - 1) / kKnnScanItems;
+  uint32_t carry = 0;
+  for (int64_t b0 = 0; b0 < nb; b0 += kTopThreads) {
+    const int64_t b = b0 + threadIdx.x;
+    const uint32_t x = b < nb ? bsum[b] : 0u;
+    uint32_t total;
+    const uint32_t ex = block_scan<kTopThreads>(x, sm, total);
+    if (b < nb) bsum[b] = carry + ex;
+    carry += total;
   }
 }
 
 __global__ __launch_bounds__(kKnnThreads) void k_knn_scan_down(uint32_t* __restrict__ count,
                                                                const GridParams* __restrict__ P,
                                                                const uint32_t* __restrict__ bsum) {
-  __shared__ uint32_t sm[kKnnScanItems];
+  __shared__ uint32_t sm[kKnnThreads / 64];
   const int64_t nc = P->n_cells + 1;
   const int64_t base = (int64_t)blockIdx.x * kKnnScanItems;
+  if (base >= nc) return;
+  const int64_t i0 = base + threadIdx.x * kKnnScanPer;
+  uint32_t v[kKnnScanPer], s = 0, total;
+  load_counts(count, i0, nc, v);
+#pragma unroll
+  for (int k = 0; k < kKnnScanPer; ++k) s += v[k];
+  uint32_t run = bsum[blockIdx.x] + block_scan<kKnnThreads>(s, sm, total);
+#pragma unroll
   for (int k = 0; k < kKnnScanPer; ++k) {
-    const int li = k * kKnnThreads + threadIdx.x;
-    const int64_t i = base + li;
-    sm[li] = i < nc ? count[i] : 0u;
+    const uint32_t x = v[k];
+    v[k] = run;
+    run += x;
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t run = bsum[blockIdx.x];
-    for (int li = 0; li < kKnnScanItems; ++li) {
-      const uint32_t x = sm[li];
-      sm[li] = run;
-      run += x;
-    }
-  }
-  __syncthreads();
-  for (int k = 0; k < kKnnScanPer; ++k) {
-    const int li = k * kKnnThreads + threadIdx.x;
-    const int64_t i = base + li;
-    if (i < nc) count[i] = sm[li];
-  }
+  // (the words past nc lie inside the 256-byte padded array)
+#pragma unroll
+  for (int q = 0; q < kKnnScanPer / 4; ++q)
+    if (i0 + 4 * q < nc)
+      *reinterpret_cast<uint4*>(count + i0 + 4 * q) =
+          make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
 }
 
 __global__ __launch_bounds__(kKnnThreads) void k_cell_scatter(const float* __restrict__ pts, int64_t n,
                                                               const uint32_t* __restrict__ cell,
+                                                              const uint32_t* __restrict__ rank,
                                                               const uint32_t* __restrict__ start,
-                                                              uint32_t* __restrict__ cursor,
                                                               float4* __restrict__ sorted) {
   const int64_t i = (int64_t)blockIdx.x * kKnnThreads + threadIdx.x;
   if (i >= n) return;
-  const uint32_t c = cell[i];
-  const uint32_t pos = start[c] + atomicAdd(&cursor[c], 1u);
-  sorted[pos] = make_float4(pts[i], pts[n + i], pts[2 * n + i], __int_as_float((int)i));
+  sorted[start[cell[i]] + rank[i]] = make_float4(pts[i], pts[n + i], pts[2 * n + i], __int_as_float((int)i));
 }
 
+// The K best (distance^2, index) pairs, ascending, as 64-bit keys: distances
+// are not negative, so their bits order as they do.
+__device__ __forceinline__ uint64_t knn_key(float d2, int j) {
+  return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
+}
+constexpr uint64_t kNoNeighbour = ((uint64_t)0x7f800000u << 32) | 0x7fffffffu;
+
+// Puts a key that beats the K-th into place: entry s becomes the median of
+// its predecessor, itself and the key (a compare and four selects; swapping
+// pairs of distances and indices took twice that).
 template <int K>
-__device__ __forceinline__ void knn_insert(float (&bd)[K], int (&bi)[K], float d2, int j) {
-  // (d2, j) goes in if it beats the current K-th entry; bubble it into place
-  if (!(d2 < bd[K - 1] || (d2 == bd[K - 1] && j < bi[K - 1]))) return;
-  bd[K - 1] = d2;
-  bi[K - 1] = j;
+__device__ __forceinline__ void knn_insert(uint64_t (&best)[K], uint64_t key) {
+  if (!(key < best[K - 1])) return;
+  bool below = true;                                // key < best[s]
 #pragma unroll
   for (int s = K - 1; s > 0; --s) {
-    const bool sw = bd[s] < bd[s - 1] || (bd[s] == bd[s - 1] && bi[s] < bi[s - 1]);
-    const float td = sw ? bd[s - 1] : bd[s];
-    const int ti = sw ? bi[s - 1] : bi[s];
-    bd[s - 1] = sw ? bd[s] : bd[s - 1];
-    bi[s - 1] = sw ? bi[s] : bi[s - 1];
-    bd[s] = td;
-    bi[s] = ti;
+    const bool below_prev = key < best[s - 1];
+    best[s] = below_prev ? best[s - 1] : (below ? key : best[s]);
+    below = below_prev;
+  }
+  best[0] = below ? key : best[0];
+}
+
+// Distance^2 of the K-th neighbour found so far.
+template <int K>
+__device__ __forceinline__ float knn_bound(const uint64_t (&best)[K]) {
+  return __uint_as_float((uint32_t)(best[K - 1] >> 32));
+}
+
+// The points of sorted positions j .. end - 1 against query q of index qi.
+template <int K>
+__device__ __forceinline__ void knn_scan(uint64_t (&best)[K], const float4& q, int qi,
+                                         const float4* __restrict__ sorted, uint32_t j,
+                                         uint32_t end) {
+  for (; j < end; ++j) {
+    const float4 p = sorted[j];
+    const int pj = __float_as_int(p.w);
+    const float dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
+    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+    if (d2 <= knn_bound(best) && pj != qi) knn_insert<K>(best, knn_key(d2, pj));
   }
 }
 
+// Distance of x to the nearer of the faces of cells c0 .. c1 that have cells
+// beyond them.
+__device__ __forceinline__ float knn_wall(float x, float lo, float h, int g, int c0, int c1) {
+  float wall = INFINITY;
+  if (c0 > 0) wall = fminf(wall, x - (lo + c0 * h));
+  if (c1 < g - 1) wall = fminf(wall, lo + (c1 + 1) * h - x);
+  return wall;
+}
+
+// Whether the k-th distance is within `wall`, the distance to the faces of
+// the searched cells: every unsearched point is beyond them.
+template <int K>
+__device__ __forceinline__ bool knn_done(const uint64_t (&best)[K], int k, float wall) {
+  wall = fmaxf(wall, 0.0f);
+  // (the k-th as the largest of the first k: a choice by k would put the
+  // array in memory)
+  uint32_t kth = 0;
+#pragma unroll
+  for (int t = 0; t < K; ++t) kth = max(kth, t < k ? (uint32_t)(best[t] >> 32) : 0u);
+  return __uint_as_float(kth) <= wall * wall * 0.9999f || wall == INFINITY;
+}
+
+template <int K>
+__device__ __forceinline__ void knn_write(const uint64_t (&best)[K], int qi, int k,
+                                          int32_t* __restrict__ idx, float* __restrict__ dist,
+                                          float* __restrict__ mean_dist) {
+  float d[K], dsum = 0.0f;
+  int bi[K], found = 0;
+#pragma unroll
+  for (int t = 0; t < K; ++t) {
+    const bool has = best[t] != kNoNeighbour;
+    bi[t] = has ? (int)(uint32_t)best[t] : -1;
+    d[t] = sqrtf(__uint_as_float((uint32_t)(best[t] >> 32)));
+    if (t < k && has) {
+      dsum += d[t];
+      ++found;
+    }
+  }
+  // whole rows of 16-byte words where they fit, else one value at a time
+  const int64_t o = (int64_t)qi * k;
+  const bool wide = K % 4 == 0 && k == K && (((uintptr_t)idx | (uintptr_t)dist) & 15) == 0;
+  if (wide) {
+#pragma unroll
+    for (int t = 0; t < K; t += 4) {
+      if (idx)
+        *reinterpret_cast<int4*>(idx + o + t) = make_int4(bi[t], bi[t + 1], bi[t + 2], bi[t + 3]);
+      if (dist)
+        *reinterpret_cast<float4*>(dist + o + t) = make_float4(d[t], d[t + 1], d[t + 2], d[t + 3]);
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < K; ++t)
+      if (t < k) {
+        if (idx) idx[o + t] = bi[t];
+        if (dist) dist[o + t] = d[t];
+      }
+  }
+  // mean over the neighbours found, in ascending order of distance
+  if (mean_dist) mean_dist[qi] = found ? dsum / (float)found : 0.0f;
+}
+
+// The rows of cells around a point, nearest first: 4 bits a row, dy + 1 and
+// dz + 1.
+constexpr uint64_t kRowOrder = 0xa82091645ull;
+
+// Shells of cells searched here; a point of a surface or a volume is done by
+// the second.  A point far from its neighbours would visit (2 r + 1)^3 mostly
+// empty cells: it goes to the list far[0 .. P->n_far) for k_query_far.
+constexpr int kFineShells = 4;
+
 template <int K>
 __global__ __launch_bounds__(kKnnThreads) void k_query(const float4* __restrict__ sorted, int64_t n,
-                                                       int k, const GridParams* __restrict__ P,
+                                                       int k, GridParams* __restrict__ P,
                                                        const uint32_t* __restrict__ start,
+                                                       uint32_t* __restrict__ far,
                                                        int32_t* __restrict__ idx,
                                                        float* __restrict__ dist,
                                                        float* __restrict__ mean_dist) {
@@ -247,65 +544,111 @@ __global__ __launch_bounds__(kKnnThreads) void k_query(const float4* __restrict_
   const int cx = cell_coord(q.x, G.lo[0], G.inv_h, G.g[0]);
   const int cy = cell_coord(q.y, G.lo[1], G.inv_h, G.g[1]);
   const int cz = cell_coord(q.z, G.lo[2], G.inv_h, G.g[2]);
-  float bd[K];
-  int bi[K];
+  uint64_t best[K];
 #pragma unroll
-  for (int t = 0; t < K; ++t) {
-    bd[t] = INFINITY;
-    bi[t] = 0x7fffffff;
+  for (int t = 0; t < K; ++t) best[t] = kNoNeighbour;
+  // distance from the point to its cell's faces, less the rounding of both
+  // sides of a cell boundary; a row of cells beyond a face is at least that
+  // far away
+  auto face = [&](float x, float lo, int c, int d) {
+    if (d == 0) return 0.0f;
+    const float edge = lo + (float)(d < 0 ? c : c + 1) * G.h;
+    return fmaxf((d < 0 ? x - edge : edge - x) - (1e-3f * G.h + 1e-6f * fabsf(edge)), 0.0f);
+  };
+  // the 3x3 rows of cells around the point, its own first, so that the K-th
+  // distance is small when the others are reached; rows that are farther than
+  // it are left out
+#pragma unroll 1
+  for (int i = 0; i < 9; ++i) {
+    const int dy = (int)(kRowOrder >> (4 * i) & 3) - 1;
+    const int dz = (int)(kRowOrder >> (4 * i + 2) & 3) - 1;
+    const int y = cy + dy, z = cz + dz;
+    if (y < 0 || y >= G.g[1] || z < 0 || z >= G.g[2]) continue;
+    const float fy = face(q.y, G.lo[1], cy, dy), fz = face(q.z, G.lo[2], cz, dz);
+    if (fmaf(fy, fy, fz * fz) * 0.9999f > knn_bound(best)) continue;
+    const int64_t row = ((int64_t)z * G.g[1] + y) * G.g[0];
+    knn_scan(best, q, qi, sorted, start[row + max(cx - 1, 0)],
+             start[row + min(cx + 1, G.g[0] - 1) + 1]);
   }
-  const int rmax = max(G.g[0], max(G.g[1], G.g[2]));
-  for (int r = 0; r <= rmax; ++r) {
-    const int z0 = max(cz - r, 0), z1 = min(cz + r, G.g[2] - 1);
-    const int y0 = max(cy - r, 0), y1 = min(cy + r, G.g[1] - 1);
-    const int x0 = max(cx - r, 0), x1 = min(cx + r, G.g[0] - 1);
-    for (int z = z0; z <= z1; ++z)
-      for (int y = y0; y <= y1; ++y) {
-        const bool face = (abs(z - cz) == r) || (abs(y - cy) == r);
-        // interior rows of the shell only contribute their two end cells
-        const int step = face ? 1 : max(x1 - x0, 1);
-        for (int x = x0; x <= x1; x += step) {
-          if (!face && abs(x - cx) != r) continue;
-          const int64_t c = ((int64_t)z * G.g[1] + y) * G.g[0] + x;
-          const uint32_t a = start[c], b = start[c + 1];
-          for (uint32_t j = a; j < b; ++j) {
-            const float4 p = sorted[j];
-            const int pj = __float_as_int(p.w);
-            if (pj == qi) continue;
-            const float dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
-            knn_insert<K>(bd, bi, fmaf(dx, dx, fmaf(dy, dy, dz * dz)), pj);
+#pragma unroll 1
+  for (int r = 1;; ++r) {
+    if (r > 1) {
+      for (int z = max(cz - r, 0); z <= min(cz + r, G.g[2] - 1); ++z)
+        for (int y = max(cy - r, 0); y <= min(cy + r, G.g[1] - 1); ++y) {
+          const int64_t row = ((int64_t)z * G.g[1] + y) * G.g[0];
+          // interior rows of the shell only contribute their two end cells
+          const bool whole = abs(z - cz) == r || abs(y - cy) == r;
+          const int w = whole ? 2 * r : 0;
+          for (int x = cx - r; x <= cx + r; x += whole ? 2 * r + 1 : 2 * r)
+            if (x + w >= 0 && x < G.g[0])
+              knn_scan(best, q, qi, sorted, start[row + max(x, 0)],
+                       start[row + min(x + w, G.g[0] - 1) + 1]);
+        }
+    }
+    const float wall = fminf(knn_wall(q.x, G.lo[0], G.h, G.g[0], cx - r, cx + r),
+                             fminf(knn_wall(q.y, G.lo[1], G.h, G.g[1], cy - r, cy + r),
+                                   knn_wall(q.z, G.lo[2], G.h, G.g[2], cz - r, cz + r)));
+    if (knn_done(best, k, wall)) break;
+    if (r == kFineShells) {
+      far[atomicAdd(&P->n_far, 1u)] = (uint32_t)s;
+      return;
+    }
+  }
+  knn_write(best, qi, k, idx, dist, mean_dist);
+}
+
+// The points that k_query left: shells of blocks of cells, of which the empty
+// ones and those beyond the K-th distance are passed over.
+template <int K>
+__global__ __launch_bounds__(kKnnThreads) void k_query_far(
+    const float4* __restrict__ sorted, int k, const GridParams* __restrict__ P,
+    const uint32_t* __restrict__ start, const uint8_t* __restrict__ block,
+    const uint32_t* __restrict__ far, int32_t* __restrict__ idx, float* __restrict__ dist,
+    float* __restrict__ mean_dist) {
+  const GridParams G = *P;
+  auto slab = [&](float x, float lo, int b) {
+    const float e0 = lo + (float)(b * kBlock) * G.h, e1 = e0 + (float)kBlock * G.h;
+    const float d = fmaxf(e0 - x, x - e1);
+    return fmaxf(d - (1e-3f * G.h + 1e-6f * (fabsf(e0) + fabsf(e1))), 0.0f);
+  };
+  for (uint32_t i = blockIdx.x * kKnnThreads + threadIdx.x; i < G.n_far;
+       i += gridDim.x * kKnnThreads) {
+    const float4 q = sorted[far[i]];
+    const int qi = __float_as_int(q.w);
+    const int bx = cell_coord(q.x, G.lo[0], G.inv_h, G.g[0]) >> kBlockShift;
+    const int by = cell_coord(q.y, G.lo[1], G.inv_h, G.g[1]) >> kBlockShift;
+    const int bz = cell_coord(q.z, G.lo[2], G.inv_h, G.g[2]) >> kBlockShift;
+    uint64_t best[K];
+#pragma unroll
+    for (int t = 0; t < K; ++t) best[t] = kNoNeighbour;
+#pragma unroll 1
+    for (int r = 0;; ++r) {
+      for (int z = max(bz - r, 0); z <= min(bz + r, G.bg[2] - 1); ++z)
+        for (int y = max(by - r, 0); y <= min(by + r, G.bg[1] - 1); ++y) {
+          const bool whole = abs(z - bz) == r || abs(y - by) == r;
+          for (int x = bx - r; x <= bx + r; x += whole ? 1 : 2 * r) {
+            if (x < 0 || x >= G.bg[0]) continue;
+            if (!block[((int64_t)z * G.bg[1] + y) * G.bg[0] + x]) continue;
+            const float fx = slab(q.x, G.lo[0], x), fy = slab(q.y, G.lo[1], y),
+                        fz = slab(q.z, G.lo[2], z);
+            if (fmaf(fx, fx, fmaf(fy, fy, fz * fz)) * 0.9999f > knn_bound(best)) continue;
+            const int x0 = x * kBlock, x1 = min(x0 + kBlock, G.g[0]);
+            for (int cz = z * kBlock; cz < min((z + 1) * kBlock, G.g[2]); ++cz)
+              for (int cy = y * kBlock; cy < min((y + 1) * kBlock, G.g[1]); ++cy) {
+                const int64_t row = ((int64_t)cz * G.g[1] + cy) * G.g[0];
+                knn_scan(best, q, qi, sorted, start[row + x0], start[row + x1]);
+              }
           }
         }
-      }
-    // every unsearched point is at least `wall` away
-    float wall = INFINITY;
-    if (cx - r > 0) wall = fminf(wall, q.x - (G.lo[0] + (cx - r) * G.h));
-    if (cx + r < G.g[0] - 1) wall = fminf(wall, G.lo[0] + (cx + r + 1) * G.h - q.x);
-    if (cy - r > 0) wall = fminf(wall, q.y - (G.lo[1] + (cy - r) * G.h));
-    if (cy + r < G.g[1] - 1) wall = fminf(wall, G.lo[1] + (cy + r + 1) * G.h - q.y);
-    if (cz - r > 0) wall = fminf(wall, q.z - (G.lo[2] + (cz - r) * G.h));
-    if (cz + r < G.g[2] - 1) wall = fminf(wall, G.lo[2] + (cz + r + 1) * G.h - q.z);
-    wall = fmaxf(wall, 0.0f);
-    float kth = bd[0];
-#pragma unroll
-    for (int t = 1; t < K; ++t) kth = (t == k - 1) ? bd[t] : kth;
-    if (kth <= wall * wall * 0.9999f || wall == INFINITY) break;
-  }
-  float dsum = 0.0f;
-  int found = 0;
-#pragma unroll
-  for (int t = 0; t < K; ++t)
-    if (t < k) {
-      const float d = sqrtf(bd[t]);
-      if (idx) idx[(int64_t)qi * k + t] = bi[t] == 0x7fffffff ? -1 : bi[t];
-      if (dist) dist[(int64_t)qi * k + t] = d;
-      if (bi[t] != 0x7fffffff) {
-        dsum += d;
-        ++found;
-      }
+      const int r1 = r + 1;
+      const float wall = fminf(
+          knn_wall(q.x, G.lo[0], G.h, G.g[0], (bx - r) * kBlock, (bx + r1) * kBlock - 1),
+          fminf(knn_wall(q.y, G.lo[1], G.h, G.g[1], (by - r) * kBlock, (by + r1) * kBlock - 1),
+                knn_wall(q.z, G.lo[2], G.h, G.g[2], (bz - r) * kBlock, (bz + r1) * kBlock - 1)));
+      if (knn_done(best, k, wall)) break;    // (true once the whole grid is searched)
     }
-  // mean over the neighbours found, in ascending order of distance
-  if (mean_dist) mean_dist[qi] = found ? dsum / (float)found : 0.0f;
+    knn_write(best, qi, k, idx, dist, mean_dist);
+  }
 }
 
 // Plain initialisation of the Gaussians of surface points (one thread per
@@ -360,44 +703,63 @@ gs_status gs_knn(const float* pts, int64_t n, int32_t k, void* ws, size_t ws_byt
   GS_REQUIRE(((uintptr_t)ws & 255) == 0, "gs_knn: workspace must be 256-byte aligned");
   char* w = (char*)ws;
   float* part = (float*)(w + L.off_part);
+  float* sample = (float*)(w + L.off_sample);
   GridParams* P = (GridParams*)(w + L.off_params);
   uint32_t* cell = (uint32_t*)(w + L.off_cell);
   uint32_t* count = (uint32_t*)(w + L.off_count);
-  uint32_t* cursor = (uint32_t*)(w + L.off_cursor);
+  uint32_t* rank = (uint32_t*)(w + L.off_rank);
+  uint8_t* block = (uint8_t*)(w + L.off_block);
   float4* sorted = (float4*)(w + L.off_sorted);
   uint32_t* bsum = (uint32_t*)(w + L.off_bsum);
   hipStream_t s = as_stream(stream);
   const unsigned nb = (unsigned)L.nb_pts;
-  hipLaunchKernelGGL(k_bbox_partial, dim3(nb), dim3(kKnnThreads), 0, s, pts, n, part);
+  const KnnSample smp = knn_sample(L.nb_pts);
+  const int ns = (int)(ceil_div(L.nb_pts, smp.span) << (8 - smp.shift));
+  hipLaunchKernelGGL(k_bbox_partial, dim3((unsigned)L.nb_bbox), dim3(kKnnThreads), 0, s, pts, n,
+                     smp, part, sample);
   GS_LAUNCH_CHECK("gs_knn/bbox");
-  hipLaunchKernelGGL(k_grid_params, dim3(1), dim3(64), 0, s, part, L.nb_pts, n, L.max_cells, P);
+  // points wanted in an occupied cell: the 3x3 cells around a surface point
+  // then hold its k nearest (a disc of k points has a radius of
+  // sqrt(k / (pi per_cell)) cell edges)
+  const float per_cell = std::max(2.0f, (float)k / 3.0f);
+  hipLaunchKernelGGL(k_grid_params, dim3(1), dim3(kParamThreads), 0, s, part, L.nb_bbox, sample,
+                     ns, n, L.max_cells, per_cell, P);
   GS_LAUNCH_CHECK("gs_knn/grid");
-  gs_status st = gs_zero(count, sizeof(uint32_t) * (size_t)(L.max_cells + 1), stream);
-  if (st != GS_OK) return st;
-  st = gs_zero(cursor, sizeof(uint32_t) * (size_t)L.max_cells, stream);
-  if (st != GS_OK) return st;
-  hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kKnnThreads), 0, s, pts, n, P, cell, count);
+  hipLaunchKernelGGL(k_cell_zero,
+                     dim3((unsigned)std::min<int64_t>(ceil_div(L.max_cells + 4, 4 * kKnnThreads),
+                                                      8 * (int64_t)device_cu_count())),
+                     dim3(kKnnThreads), 0, s, P, (uint4*)count, (uint4*)block);
+  GS_LAUNCH_CHECK("gs_knn/zero");
+  hipLaunchKernelGGL(k_cell_count, dim3(nb), dim3(kKnnThreads), 0, s, pts, n, P, cell, rank, count,
+                     block);
   GS_LAUNCH_CHECK("gs_knn/count");
   // scan n_cells + 1 entries so that start[n_cells] = n closes the last cell
   hipLaunchKernelGGL(k_knn_scan_reduce, dim3((unsigned)L.nb_scan), dim3(kKnnThreads), 0, s, count,
                      P, bsum);
   GS_LAUNCH_CHECK("gs_knn/scan_reduce");
-  hipLaunchKernelGGL(k_knn_scan_top, dim3(1), dim3(64), 0, s, bsum, L.nb_scan);
+  hipLaunchKernelGGL(k_knn_scan_top, dim3(1), dim3(kTopThreads), 0, s, P, bsum);
   GS_LAUNCH_CHECK("gs_knn/scan_top");
   hipLaunchKernelGGL(k_knn_scan_down, dim3((unsigned)L.nb_scan), dim3(kKnnThreads), 0, s, count, P,
                      bsum);
   GS_LAUNCH_CHECK("gs_knn/scan_down");
-  hipLaunchKernelGGL(k_cell_scatter, dim3(nb), dim3(kKnnThreads), 0, s, pts, n, cell, count, cursor,
+  hipLaunchKernelGGL(k_cell_scatter, dim3(nb), dim3(kKnnThreads), 0, s, pts, n, cell, rank, count,
                      sorted);
   GS_LAUNCH_CHECK("gs_knn/scatter");
-#define GS_KNN_Q(KK)                                                                        \
-  hipLaunchKernelGGL(k_query<KK>, dim3(nb), dim3(kKnnThreads), 0, s, sorted, n, k, P, count, \
-                     idx, dist, mean_dist)
-  if (k <= 4) GS_KNN_Q(4);
-  else if (k <= 8) GS_KNN_Q(8);
-  else if (k <= 16) GS_KNN_Q(16);
-  else GS_KNN_Q(32);
-#undef GS_KNN_Q
+  // (the cells of the points are not needed any more: their array takes the
+  // list of far points)
+  uint32_t* far = cell;
+  const unsigned nb_far = (unsigned)std::min<int64_t>(L.nb_pts, 4 * (int64_t)device_cu_count());
+  auto query = [&](auto KK) {
+    constexpr int K = decltype(KK)::value;
+    hipLaunchKernelGGL(k_query<K>, dim3(nb), dim3(kKnnThreads), 0, s, sorted, n, k, P, count, far,
+                       idx, dist, mean_dist);
+    hipLaunchKernelGGL(k_query_far<K>, dim3(nb_far), dim3(kKnnThreads), 0, s, sorted, k, P, count,
+                       block, far, idx, dist, mean_dist);
+  };
+  if (k <= 4) query(std::integral_constant<int, 4>{});
+  else if (k <= 8) query(std::integral_constant<int, 8>{});
+  else if (k <= 16) query(std::integral_constant<int, 16>{});
+  else query(std::integral_constant<int, 32>{});
   GS_LAUNCH_CHECK("gs_knn/query");
   return GS_OK;
 }
