@@ -36,18 +36,22 @@ namespace gsmi {
 constexpr int kIn = 96, kHid = 64, kOut = 8;
 constexpr int kMlpWaves = 4;                       // waves per work-group
 constexpr int kMlpThreads = 64 * kMlpWaves;
+// LDS row strides (elements) of the 96- and 64-column matrices: rows padded by
+// 16 bytes, so that the 16 rows of a fragment start in different banks (at 96
+// and 64 columns they fell into 4 and 2 groups of banks)
+constexpr int kInS = kIn + 8, kHidS = kHid + 8, kOutS = 20;
 constexpr int kWSize = kIn * kHid + kHid * kHid + kHid * kOut;     // weight floats
 constexpr int kBSize = kHid + kHid + kOut;                          // bias floats
 constexpr int kPartial = kWSize + kBSize;                           // 10888
-constexpr int kBwdBlockCap = 512;                  // bwd work-groups (partials)
+constexpr int kBwdBlockCap = 256;                  // bwd work-groups (partials): one per CU, as
+                                                   // the gradients fill the registers
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// Rounded to nearest even (v_cvt_pk_bf16_f32).
 __device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);                 // round to nearest even
-  return (uint16_t)(u >> 16);
+  return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -76,13 +80,10 @@ __device__ __forceinline__ bf16x4 frag(const uint16_t* m, int stride, int row0, 
   return *reinterpret_cast<const bf16x4*>(m + (row0 + (l & 15)) * stride + k0 + 4 * (l >> 4));
 }
 
+typedef __bf16 bf16v4 __attribute__((ext_vector_type(4)));
+
 __device__ __forceinline__ bf16x4 pack4(float a, float b, float c, float d) {
-  bf16x4 r;
-  r[0] = (short)f2bf(a);
-  r[1] = (short)f2bf(b);
-  r[2] = (short)f2bf(c);
-  r[3] = (short)f2bf(d);
-  return r;
+  return __builtin_bit_cast(bf16x4, __builtin_convertvector((f32x4{a, b, c, d}), bf16v4));
 }
 
 // Orders this wave's LDS accesses (one wave reads what its other lanes wrote).
@@ -107,43 +108,59 @@ struct MlpW {
 //   w2n [64][64]  W2 as is       (B operand of dH1 = dZ2 W2^T)
 //   w3t [16][64]  W3 transposed, rows >= 8 zero (B operand of layer 3)
 //   w3n [64][16]  W3 as is, columns >= 8 zero (B operand of dH2 = dY W3^T)
+// (row strides kInS, kHidS and kOutS)
 struct MlpLds {
-  uint16_t w1t[kHid * kIn];
-  uint16_t w2t[kHid * kHid];
-  uint16_t w2n[kHid * kHid];
-  uint16_t w3t[16 * kHid];
-  uint16_t w3n[kHid * 16];
+  uint16_t w1t[kHid * kInS];
+  uint16_t w2t[kHid * kHidS];
+  uint16_t w2n[kHid * kHidS];
+  uint16_t w3t[16 * kHidS];
+  uint16_t w3n[kHid * kOutS];
   float b1[kHid], b2[kHid], b3[16];
 };
 
 // Per-wave scratch: the point tile's x, H1 (reused for dZ1), H2 and dZ2 as
 // row-major bf16.
 struct WaveLds {
-  uint16_t x[16 * kIn];
-  uint16_t h1[16 * kHid];
-  uint16_t h2[16 * kHid];
-  uint16_t dz2[16 * kHid];
+  uint16_t x[16 * kInS];
+  uint16_t h1[16 * kHidS];
+  uint16_t h2[16 * kHidS];
+  uint16_t dz2[16 * kHidS];
 };
 
 constexpr int kSmemBytes = (int)(sizeof(MlpLds) + kMlpWaves * sizeof(WaveLds));
 static_assert(kSmemBytes >= kPartial * 4, "block gradient reduction reuses the LDS");
 
+// Eight floats f(0..7) as 16 bytes of bf16.
+template <typename F>
+__device__ __forceinline__ uint4 pack8(F&& f) {
+  const bf16x4 a = pack4(f(0), f(1), f(2), f(3)), b = pack4(f(4), f(5), f(6), f(7));
+  const uint2 lo = __builtin_bit_cast(uint2, a), hi = __builtin_bit_cast(uint2, b);
+  return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+
+// (neighbouring lanes read neighbouring weights and write 16 bytes each)
 __device__ void stage_weights(const MlpW& w, MlpLds& L) {
-  for (int i = threadIdx.x; i < kIn * kHid; i += blockDim.x) {
-    const int k = i / kHid, n = i % kHid;
-    L.w1t[n * kIn + k] = f2bf(w.w1[i]);
+  for (int i = threadIdx.x; i < kHid * (kIn / 8); i += blockDim.x) {
+    const int n = i % kHid, k = 8 * (i / kHid);
+    *reinterpret_cast<uint4*>(L.w1t + n * kInS + k) =
+        pack8([&](int j) { return w.w1[(k + j) * kHid + n]; });
   }
-  for (int i = threadIdx.x; i < kHid * kHid; i += blockDim.x) {
-    const int k = i / kHid, n = i % kHid;
-    const uint16_t v = f2bf(w.w2[i]);
-    L.w2t[n * kHid + k] = v;
-    L.w2n[i] = v;
+  for (int i = threadIdx.x; i < kHid * (kHid / 8); i += blockDim.x) {
+    const int n = i % kHid, k = 8 * (i / kHid);
+    *reinterpret_cast<uint4*>(L.w2t + n * kHidS + k) =
+        pack8([&](int j) { return w.w2[(k + j) * kHid + n]; });
+    const int r = i / (kHid / 8), c = 8 * (i % (kHid / 8));
+    *reinterpret_cast<uint4*>(L.w2n + r * kHidS + c) =
+        pack8([&](int j) { return w.w2[r * kHid + c + j]; });
+  }
+  for (int i = threadIdx.x; i < 16 * (kHid / 8); i += blockDim.x) {
+    const int n = i % 16, k = 8 * (i / 16);      // w3t[n][k] = W3[k][n]
+    *reinterpret_cast<uint4*>(L.w3t + n * kHidS + k) =
+        pack8([&](int j) { return n < kOut ? w.w3[(k + j) * kOut + n] : 0.0f; });
   }
   for (int i = threadIdx.x; i < 16 * kHid; i += blockDim.x) {
-    const int n = i / kHid, k = i % kHid;      // w3t[n][k] = W3[k][n]
-    L.w3t[i] = n < kOut ? f2bf(w.w3[k * kOut + n]) : (uint16_t)0;
-    const int k2 = i / 16, n2 = i % 16;        // w3n[k2][n2] = W3[k2][n2]
-    L.w3n[i] = n2 < kOut ? f2bf(w.w3[k2 * kOut + n2]) : (uint16_t)0;
+    const int k = i / 16, n = i % 16;            // w3n[k][n] = W3[k][n]
+    L.w3n[k * kOutS + n] = n < kOut ? f2bf(w.w3[k * kOut + n]) : (uint16_t)0;
   }
   for (int i = threadIdx.x; i < kHid; i += blockDim.x) {
     L.b1[i] = w.b1[i];
@@ -175,7 +192,7 @@ __device__ __forceinline__ void store_x(const XRegs& r, uint16_t* xs) {
 #pragma unroll
   for (int s = 0; s < 3; ++s) {
     const int i = l + 64 * s;
-    *reinterpret_cast<uint4*>(xs + (i / 12) * kIn + 8 * (i % 12)) = r.v[s];
+    *reinterpret_cast<uint4*>(xs + (i / 12) * kInS + 8 * (i % 12)) = r.v[s];
   }
 }
 
@@ -188,9 +205,9 @@ __device__ __forceinline__ void tile_forward(const MlpLds& L, WaveLds& Wv, f32x4
   for (int nt = 0; nt < 4; ++nt) z1[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int kt = 0; kt < kIn / 32; ++kt) {
-    const bf16x8 a = frag8(Wv.x, kIn, 0, 32 * kt);
+    const bf16x8 a = frag8(Wv.x, kInS, 0, 32 * kt);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) z1[nt] = mfma32(a, frag8(L.w1t, kIn, 16 * nt, 32 * kt), z1[nt]);
+    for (int nt = 0; nt < 4; ++nt) z1[nt] = mfma32(a, frag8(L.w1t, kInS, 16 * nt, 32 * kt), z1[nt]);
   }
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt) {
@@ -198,7 +215,7 @@ __device__ __forceinline__ void tile_forward(const MlpLds& L, WaveLds& Wv, f32x4
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       z1[nt][j] += L.b1[col];
-      Wv.h1[(4 * (l >> 4) + j) * kHid + col] = f2bf(fmaxf(z1[nt][j], 0.0f));
+      Wv.h1[(4 * (l >> 4) + j) * kHidS + col] = f2bf(fmaxf(z1[nt][j], 0.0f));
     }
   }
   wave_lds_sync();
@@ -206,9 +223,9 @@ __device__ __forceinline__ void tile_forward(const MlpLds& L, WaveLds& Wv, f32x4
   for (int nt = 0; nt < 4; ++nt) z2[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int kt = 0; kt < kHid / 32; ++kt) {
-    const bf16x8 a = frag8(Wv.h1, kHid, 0, 32 * kt);
+    const bf16x8 a = frag8(Wv.h1, kHidS, 0, 32 * kt);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) z2[nt] = mfma32(a, frag8(L.w2t, kHid, 16 * nt, 32 * kt), z2[nt]);
+    for (int nt = 0; nt < 4; ++nt) z2[nt] = mfma32(a, frag8(L.w2t, kHidS, 16 * nt, 32 * kt), z2[nt]);
   }
 #pragma unroll
   for (int nt = 0; nt < 4; ++nt) {
@@ -216,43 +233,111 @@ __device__ __forceinline__ void tile_forward(const MlpLds& L, WaveLds& Wv, f32x4
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       z2[nt][j] += L.b2[col];
-      Wv.h2[(4 * (l >> 4) + j) * kHid + col] = f2bf(fmaxf(z2[nt][j], 0.0f));
+      Wv.h2[(4 * (l >> 4) + j) * kHidS + col] = f2bf(fmaxf(z2[nt][j], 0.0f));
     }
   }
   wave_lds_sync();
   y = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int kt = 0; kt < kHid / 32; ++kt)
-    y = mfma32(frag8(Wv.h2, kHid, 0, 32 * kt), frag8(L.w3t, kHid, 0, 32 * kt), y);
+    y = mfma32(frag8(Wv.h2, kHidS, 0, 32 * kt), frag8(L.w3t, kHidS, 0, 32 * kt), y);
 #pragma unroll
   for (int j = 0; j < 4; ++j) y[j] += L.b3[l & 15];
 }
 
-__global__ __launch_bounds__(kMlpThreads) void k_mlp_fwd(const uint16_t* __restrict__ x, int64_t n,
-                                                         MlpW w, float* __restrict__ y) {
-  __shared__ __align__(16) unsigned char smem[kSmemBytes];
-  MlpLds& L = *reinterpret_cast<MlpLds*>(smem);
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-  WaveLds& S = reinterpret_cast<WaveLds*>(smem + sizeof(MlpLds))[wave];
-  stage_weights(w, L);
+// Forward on transposed products, Z^T = W^T X^T: a lane then holds four
+// neighbouring hidden units of one point, so the hand-off to the next layer is
+// four 8-byte LDS writes and two 16-byte reads, and the x rows are the B
+// operand as they lie in memory.  The weights' A operands stay in registers
+// (88 of them); a wave takes one 16-point tile after the other, the next
+// tile's rows loading meanwhile.  Bound by the feature rows (224 bytes a point
+// with the output): 4M points 320 -> 174 us with the weights in LDS, whose
+// unpadded rows shared banks; 64K points 26 -> 9 us.
+struct FwdLds {
+  uint16_t h1[16 * kHidS];
+  uint16_t h2[16 * kHidS];
+};
+
+// relu(z + b) of four hidden units of the lane's point, as bf16.
+__device__ __forceinline__ bf16x4 relu4(const f32x4& z, const f32x4& b) {
+  return pack4(fmaxf(z[0] + b[0], 0.0f), fmaxf(z[1] + b[1], 0.0f), fmaxf(z[2] + b[2], 0.0f),
+               fmaxf(z[3] + b[3], 0.0f));
+}
+
+__global__ __launch_bounds__(kMlpThreads, 2) void k_mlp_fwd(const uint16_t* __restrict__ x,
+                                                            int64_t n, MlpW w,
+                                                            float* __restrict__ y) {
+  __shared__ __align__(16) FwdLds lds[kMlpWaves];
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, c = l & 15, g = l >> 4;
+  FwdLds& S = lds[wave];
   const int64_t tiles = (n + 15) / 16;
   const int64_t stride = (int64_t)gridDim.x * kMlpWaves;
   int64_t t = (int64_t)blockIdx.x * kMlpWaves + wave;
-  XRegs nx;
-  if (t < tiles) load_x(nx, x, t * 16, n);
-  for (; t < tiles; t += stride) {
-    store_x(nx, S.x);
-    if (t + stride < tiles) load_x(nx, x, (t + stride) * 16, n);
-    wave_lds_sync();
-    f32x4 z1[4], z2[4], yy;
-    tile_forward(L, S, z1, z2, yy);
-    const int col = l & 15;
-    if (col < kOut) {
+  bf16x8 nx[3];
+  auto load = [&](int64_t tile) {
+    const int64_t p = tile * 16 + c;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t p = t * 16 + 4 * (l >> 4) + j;
-        if (p < n) y[p * kOut + col] = yy[j];
-      }
+    for (int kt = 0; kt < 3; ++kt) {
+      uint4 v = make_uint4(0u, 0u, 0u, 0u);
+      if (p < n) v = *reinterpret_cast<const uint4*>(x + p * kIn + 32 * kt + 8 * g);
+      nx[kt] = __builtin_bit_cast(bf16x8, v);
+    }
+  };
+  if (t < tiles) load(t);
+  // A operands: row = hidden unit (output) 16 mt + c, 8 inputs from 32 kt + 8 g
+  bf16x8 w1[3][4], w2[2][4], w3[2];
+  f32x4 b1[4], b2[4], b3;
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+    for (int kt = 0; kt < 3; ++kt)
+      w1[kt][mt] = __builtin_bit_cast(bf16x8, pack8([&](int j) {
+        return w.w1[(32 * kt + 8 * g + j) * kHid + 16 * mt + c];
+      }));
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+      w2[kt][mt] = __builtin_bit_cast(bf16x8, pack8([&](int j) {
+        return w.w2[(32 * kt + 8 * g + j) * kHid + 16 * mt + c];
+      }));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      b1[mt][j] = w.b1[16 * mt + 4 * g + j];
+      b2[mt][j] = w.b2[16 * mt + 4 * g + j];
+    }
+  }
+#pragma unroll
+  for (int kt = 0; kt < 2; ++kt)
+    w3[kt] = __builtin_bit_cast(bf16x8, pack8([&](int j) {
+      return c < kOut ? w.w3[(32 * kt + 8 * g + j) * kOut + c] : 0.0f;
+    }));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) b3[j] = 4 * g + j < kOut ? w.b3[4 * g + j] : 0.0f;
+  for (; t < tiles; t += stride) {
+    const bf16x8 x0 = nx[0], x1 = nx[1], x2 = nx[2];
+    if (t + stride < tiles) load(t + stride);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      f32x4 z = mfma32(w1[0][mt], x0, f32x4{0.f, 0.f, 0.f, 0.f});
+      z = mfma32(w1[1][mt], x1, z);
+      z = mfma32(w1[2][mt], x2, z);
+      *reinterpret_cast<bf16x4*>(S.h1 + c * kHidS + 16 * mt + 4 * g) = relu4(z, b1[mt]);
+    }
+    wave_lds_sync();
+    const bf16x8 h0 = frag8(S.h1, kHidS, 0, 0), h1 = frag8(S.h1, kHidS, 0, 32);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      f32x4 z = mfma32(w2[0][mt], h0, f32x4{0.f, 0.f, 0.f, 0.f});
+      z = mfma32(w2[1][mt], h1, z);
+      *reinterpret_cast<bf16x4*>(S.h2 + c * kHidS + 16 * mt + 4 * g) = relu4(z, b2[mt]);
+    }
+    wave_lds_sync();
+    f32x4 o = mfma32(w3[0], frag8(S.h2, kHidS, 0, 0), f32x4{0.f, 0.f, 0.f, 0.f});
+    o = mfma32(w3[1], frag8(S.h2, kHidS, 0, 32), o);
+    const int64_t p = t * 16 + c;
+    if (g < 2 && p < n) {
+      float* yp = y + p * kOut + 4 * g;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) yp[j] = o[j] + b3[j];
     }
     wave_lds_sync();
   }
@@ -328,14 +413,14 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(const uint16_t* __restr
     bf16x4 dz2c[4];
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-      const f32x4 d = mfma(dyA, frag(L.w3n, 16, 16 * nt, 0), f32x4{0.f, 0.f, 0.f, 0.f});
+      const f32x4 d = mfma(dyA, frag(L.w3n, kOutS, 16 * nt, 0), f32x4{0.f, 0.f, 0.f, 0.f});
       float v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = z2[nt][j] > 0.f ? d[j] : 0.f;
       dz2c[nt] = pack4(v[0], v[1], v[2], v[3]);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        S.dz2[(4 * (l >> 4) + j) * kHid + 16 * nt + (l & 15)] = (uint16_t)dz2c[nt][j];
+        S.dz2[(4 * (l >> 4) + j) * kHidS + 16 * nt + (l & 15)] = (uint16_t)dz2c[nt][j];
         gb2[nt] += bf2f((uint16_t)dz2c[nt][j]);
       }
     }
@@ -352,7 +437,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(const uint16_t* __restr
       f32x4 d = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int kt = 0; kt < kHid / 32; ++kt)
-        d = mfma32(frag8(S.dz2, kHid, 0, 32 * kt), frag8(L.w2n, kHid, 16 * nt, 32 * kt), d);
+        d = mfma32(frag8(S.dz2, kHidS, 0, 32 * kt), frag8(L.w2n, kHidS, 16 * nt, 32 * kt), d);
       float v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = z1[nt][j] > 0.f ? d[j] : 0.f;
@@ -360,7 +445,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(const uint16_t* __restr
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         gb1[nt] += bf2f((uint16_t)dz1c[nt][j]);
-        if (WITH_DX) S.h1[(4 * (l >> 4) + j) * kHid + 16 * nt + (l & 15)] = (uint16_t)dz1c[nt][j];
+        if (WITH_DX) S.h1[(4 * (l >> 4) + j) * kHidS + 16 * nt + (l & 15)] = (uint16_t)dz1c[nt][j];
       }
     }
     // dW1 += X^T dZ1; X^T fragments: rows = inputs, k = the tile's points
@@ -369,7 +454,7 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(const uint16_t* __restr
       const int col = 16 * mt + (l & 15);
       bf16x4 xa;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) xa[j] = (short)S.x[(4 * (l >> 4) + j) * kIn + col];
+      for (int j = 0; j < 4; ++j) xa[j] = (short)S.x[(4 * (l >> 4) + j) * kInS + col];
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) gw1[mt][nt] = mfma(xa, dz1c[nt], gw1[mt][nt]);
     }
@@ -385,8 +470,8 @@ __global__ __launch_bounds__(kMlpThreads) void k_mlp_bwd(const uint16_t* __restr
 #pragma unroll
           for (int j = 0; j < 8; ++j)
             b[j] = __builtin_bit_cast(
-                __bf16, L.w1t[(32 * kt + 8 * (l >> 4) + j) * kIn + 16 * nt + (l & 15)]);
-          d = mfma32(frag8(S.h1, kHid, 0, 32 * kt), b, d);
+                __bf16, L.w1t[(32 * kt + 8 * (l >> 4) + j) * kInS + 16 * nt + (l & 15)]);
+          d = mfma32(frag8(S.h1, kHidS, 0, 32 * kt), b, d);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -469,12 +554,28 @@ struct MlpG {
   float* db3;
 };
 
-__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ part, int nparts,
-                                                    MlpG g) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= kPartial) return;
+// A work-group sums kRedCols columns: kRedSegs threads of a column take every
+// kRedSegs-th partial, eight loads in flight, and their sums are added in
+// segment order (one thread per column waited for each of up to 512 loads:
+// 121 us for a 64K-point batch, 5 us with the segments and
+// half as many partials).
+constexpr int kRedCols = 32, kRedSegs = 8;
+
+__global__ __launch_bounds__(kRedCols* kRedSegs) void k_mlp_reduce(const float* __restrict__ part,
+                                                                   int nparts, MlpG g) {
+  __shared__ float sm[kRedSegs][kRedCols];
+  const int c = threadIdx.x % kRedCols, seg = threadIdx.x / kRedCols;
+  const int i = blockIdx.x * kRedCols + c;
   float s = 0.f;
-  for (int w = 0; w < nparts; ++w) s += part[(int64_t)w * kPartial + i];
+  if (i < kPartial) {
+#pragma unroll 8
+    for (int w = seg; w < nparts; w += kRedSegs) s += part[(int64_t)w * kPartial + i];
+  }
+  sm[seg][c] = s;
+  __syncthreads();
+  if (seg != 0 || i >= kPartial) return;
+#pragma unroll
+  for (int k = 1; k < kRedSegs; ++k) s += sm[k][c];
   int o = i;
   if (o < kIn * kHid) { g.dw1[o] += s; return; }
   o -= kIn * kHid;
@@ -543,58 +644,56 @@ __device__ __forceinline__ void rotm_to_quat(const float R[9], float q[4]) {
 
 // ---------------------------------------------------------------- features
 
-// One thread per point.  Neighbour k (sorted by distance, index) fills
-// x[6k .. 6k+2] = F (p_j - p) / dbar and x[6k+3 .. 6k+5] = F n_j; missing
-// neighbours (index -1) are zero.  dbar = mean distance over the present
-// neighbours (1 when there are none).
+// 16 lanes per point, one neighbour each.  Neighbour k (sorted by distance,
+// index) fills x[6k .. 6k+2] = F (p_j - p) / dbar and x[6k+3 .. 6k+5] = F n_j;
+// missing neighbours (index -1) are zero.  dbar = mean distance over the
+// present neighbours (1 when there are none), added nearest first.  The lists
+// are read and the features written (12 bytes a lane) as whole rows side by
+// side; with one thread per point every access of a wave touched 64 rows (4M
+// points: 1483 -> 545 us).
+constexpr int kNb = 16;
+
 __global__ __launch_bounds__(256) void k_mlp_features(const float* __restrict__ pts,
                                                       const float* __restrict__ nrm, int64_t n,
                                                       const int32_t* __restrict__ idx,
                                                       const float* __restrict__ dist,
                                                       uint16_t* __restrict__ x,
                                                       float* __restrict__ dbar) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t i = e / kNb;
+  const int k = threadIdx.x % kNb;
   if (i >= n) return;
-  float F[9];
-  local_frame(nrm[i], nrm[n + i], nrm[2 * n + i], F);
+  const int j = idx[e];
+  const float d = j >= 0 ? dist[e] : 0.0f;
+  // the sum in list order: every lane adds the 16 values one after the other
+  // (0 for a missing neighbour leaves it unchanged)
   float dm = 0.f;
-  int cnt = 0;
-  for (int k = 0; k < 16; ++k)
-    if (idx[i * 16 + k] >= 0) {
-      dm += dist[i * 16 + k];
-      ++cnt;
-    }
+#pragma unroll
+  for (int q = 0; q < kNb; ++q) dm += __shfl(d, q, kNb);
+  const uint64_t have = __ballot(j >= 0) >> (threadIdx.x & 48) & 0xffffull;
+  const int cnt = (int)__popcll(have);
   dm = cnt > 0 ? dm / (float)cnt : 1.0f;
   dm = fmaxf(dm, 1e-30f);
-  dbar[i] = dm;
+  if (k == 0) dbar[i] = dm;
   const float inv = 1.0f / dm;
-  const float px = pts[i], py = pts[n + i], pz = pts[2 * n + i];
-  uint4* xr = reinterpret_cast<uint4*>(x + i * kIn);
-  // four neighbours = 24 bf16 = 48 B = 3 x 16 B
-  for (int k4 = 0; k4 < 4; ++k4) {
-    uint32_t wds[12];
+  float F[9];
+  local_frame(nrm[i], nrm[n + i], nrm[2 * n + i], F);
+  float f[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (j >= 0) {
+    const float px = pts[i], py = pts[n + i], pz = pts[2 * n + i];
+    const float dx = (pts[j] - px) * inv, dy = (pts[n + j] - py) * inv,
+                dz = (pts[2 * n + j] - pz) * inv;
+    const float mx = nrm[j], my = nrm[n + j], mz = nrm[2 * n + j];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int j = idx[i * 16 + 4 * k4 + kk];
-      float f[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if (j >= 0) {
-        const float dx = (pts[j] - px) * inv, dy = (pts[n + j] - py) * inv,
-                    dz = (pts[2 * n + j] - pz) * inv;
-        const float mx = nrm[j], my = nrm[n + j], mz = nrm[2 * n + j];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          f[a] = F[3 * a] * dx + F[3 * a + 1] * dy + F[3 * a + 2] * dz;
-          f[3 + a] = F[3 * a] * mx + F[3 * a + 1] * my + F[3 * a + 2] * mz;
-        }
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-        wds[3 * kk + a] = (uint32_t)f2bf(f[2 * a]) | ((uint32_t)f2bf(f[2 * a + 1]) << 16);
+    for (int a = 0; a < 3; ++a) {
+      f[a] = F[3 * a] * dx + F[3 * a + 1] * dy + F[3 * a + 2] * dz;
+      f[3 + a] = F[3 * a] * mx + F[3 * a + 1] * my + F[3 * a + 2] * mz;
     }
-    xr[3 * k4 + 0] = make_uint4(wds[0], wds[1], wds[2], wds[3]);
-    xr[3 * k4 + 1] = make_uint4(wds[4], wds[5], wds[6], wds[7]);
-    xr[3 * k4 + 2] = make_uint4(wds[8], wds[9], wds[10], wds[11]);
   }
+  uint32_t* xr = reinterpret_cast<uint32_t*>(x + i * kIn) + 3 * k;
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+    xr[a] = (uint32_t)f2bf(f[2 * a]) | ((uint32_t)f2bf(f[2 * a + 1]) << 16);
 }
 
 // ---------------------------------------------------------------- targets
@@ -742,7 +841,7 @@ gs_status gs_mlp_features(const float* pts, const float* normals, int64_t n, con
   GS_REQUIRE(pts && normals && knn_idx && knn_dist && x_bf16 && dbar,
              "gs_mlp_features: NULL argument");
   GS_REQUIRE(((uintptr_t)x_bf16 & 15) == 0, "gs_mlp_features: x must be 16-byte aligned");
-  hipLaunchKernelGGL(k_mlp_features, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0,
+  hipLaunchKernelGGL(k_mlp_features, dim3((unsigned)ceil_div(n * kNb, 256)), dim3(256), 0,
                      as_stream(stream), pts, normals, n, knn_idx, knn_dist, x_bf16, dbar);
   GS_LAUNCH_CHECK("gs_mlp_features");
   return GS_OK;
@@ -757,7 +856,7 @@ gs_status gs_mlp_fwd(const uint16_t* x_bf16, int64_t n, const gs_mlp* w, float* 
   GS_REQUIRE(x_bf16 && y, "gs_mlp_fwd: NULL x/y");
   GS_REQUIRE(((uintptr_t)x_bf16 & 15) == 0, "gs_mlp_fwd: x must be 16-byte aligned");
   MlpW W{w->w1, w->w2, w->w3, w->b1, w->b2, w->b3};
-  hipLaunchKernelGGL(k_mlp_fwd, dim3(mlp_blocks(n, (int64_t)device_cu_count() * 8)),
+  hipLaunchKernelGGL(k_mlp_fwd, dim3(mlp_blocks(n, (int64_t)device_cu_count() * 2)),
                      dim3(kMlpThreads), 0, as_stream(stream), x_bf16, n, W, y);
   GS_LAUNCH_CHECK("gs_mlp_fwd");
   return GS_OK;
@@ -791,7 +890,8 @@ gs_status gs_mlp_bwd(const uint16_t* x_bf16, int64_t n, const gs_mlp* w, const f
                        (float*)ws, (float*)nullptr);
   GS_LAUNCH_CHECK("gs_mlp_bwd");
   MlpG G{g->dw1, g->dw2, g->dw3, g->db1, g->db2, g->db3};
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((unsigned)ceil_div(kPartial, 256)), dim3(256), 0, s,
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((unsigned)ceil_div(kPartial, kRedCols)),
+                     dim3(kRedCols * kRedSegs), 0, s,
                      (const float*)ws, (int)blocks, G);
   GS_LAUNCH_CHECK("gs_mlp_bwd/reduce");
   return GS_OK;
