@@ -4,10 +4,10 @@
 //
 // One work-group per (image, channel, 32x32 output tile), one kernel for
 // the loss terms and the gradient: the masked image and target are staged
-// with a 10-pixel halo (zero outside the image); the five moment maps are
+// with a 10-pixel halo (zero outside the image); the four moment maps are
 // blurred with the separable 11-tap window over the 42x42 positions whose
 // SSIM terms reach the tile's pixels; the three per-position partials
-// dS/dmu_x, dS/dE[x^2], dS/dE[xy] (zero outside the image) are blurred again
+// dS/dmu_x, dS/dvar_x, dS/dcov (zero outside the image) are blurred again
 // with the same symmetric window, which is the adjoint of the forward blur,
 // and combined with the L1 subgradient into d loss / d image.  The block
 // sums of S and |x - y| over the tile go to a partials array;
@@ -16,7 +16,9 @@
 // once per thread rather than once per tap.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "gs_device.h"
@@ -73,22 +75,30 @@ static LossLayout loss_layout(int S, int H, int W) {
   return L;
 }
 
-// LDS: region A holds the staged image and target, later the partials;
-// region B the horizontal moment sums, later the horizontal pass of the
-// partials.
-constexpr int kLRegionA = (2 * kLS * kLSs > 3 * kLM * kLMs) ? 2 * kLS * kLSs : 3 * kLM * kLMs;
-constexpr int kLMom = 6;              // blurred moments: x, y, xx, yy, xy, foreground
-constexpr int kLRegionB = (kLMom * kLS * kLMs > 3 * kLM * kLTs) ? kLMom * kLS * kLMs
-                                                                 : 3 * kLM * kLTs;
+// LDS, one region that holds in turn the staged image and target, the
+// horizontal moment sums, and the partials with their horizontal pass.
+// 38 KB: four work-groups a CU.
+constexpr int kLMom = 4;              // blurred moments: x, y, xx + yy, xy (SSIM uses the two
+                                      // variances only as a sum)
+constexpr int kLLds = std::max({2 * kLS * kLSs, kLMom * kLS * kLM,
+                                3 * kLM * kLMs + 3 * kLM * kLTs});
 
+// Bound by the vector ALU (about 7 blur FMAs of every 10 instructions; the halo of
+// both blurs makes 2.1x and 1.7x the tile's positions), and before
+// that by latency: with six moment planes beside the staged images (76 KB, two
+// work-groups a CU) a wave waited alone on its SIMD at every barrier.  The
+// horizontal sums now wait in registers and replace the images, the variances
+// are blurred as one sum, and where every staged pixel is foreground (wt = 1,
+// the inside of the object or of an unmasked image) no mask is blurred; at
+// other tiles its plane goes through the LDS first, alone.  4 images of
+// 1277x717: 215 -> 139 us; 1920x1080, 65% foreground: 146 -> 98 us.
 template <bool MASK>
-__global__ __launch_bounds__(kLThreads) void k_ssim(
+__global__ __launch_bounds__(kLThreads, 4) void k_ssim(
     const float* __restrict__ image, const float* __restrict__ target,
     const uint8_t* __restrict__ mask, int H, int W, int64_t tiles_x, int64_t blocks_per_img,
     Window win, float l1_coef, float ssim_coef, float* __restrict__ d_image,
     float* __restrict__ part) {
-  __shared__ float sA[kLRegionA];
-  __shared__ float sB[kLRegionB];
+  __shared__ float lds[kLLds];
   __shared__ float s_red[3][kLThreads / 64];
   const int64_t ic = blockIdx.x / blocks_per_img;          // image * 3 + channel
   const int64_t img = ic / 3;
@@ -100,11 +110,11 @@ __global__ __launch_bounds__(kLThreads) void k_ssim(
   const float* I = image + ic * HW;
   const float* G = target + ic * HW;
   const uint8_t* Mk = MASK ? mask + img * HW : nullptr;
-  float* s_x = sA;                  // [kLS][kLSs], staged row r = image row oy - 10 + r
-  float* s_y = sA + kLS * kLSs;
-  float* s_h = sB;                  // [5][kLS][kLMs]
-  float* s_p = sA;                  // [3][kLM][kLMs], position row r = image row oy - 5 + r
-  float* s_g = sB;                  // [3][kLM][kLTs]
+  float* s_x = lds;                 // [kLS][kLSs], staged row r = image row oy - 10 + r
+  float* s_y = lds + kLS * kLSs;
+  float* s_h = lds;                 // [kLMom][kLS][kLM]
+  float* s_p = lds;                 // [3][kLM][kLMs], position row r = image row oy - 5 + r
+  float* s_g = lds + 3 * kLM * kLMs;   // [3][kLM][kLTs]
 
   // stage the masked image and target with their foreground pixels shifted
   // by the foreground means (x'' = M (x - sx)): variances and the covariance
@@ -119,6 +129,7 @@ __global__ __launch_bounds__(kLThreads) void k_ssim(
   constexpr int kStageQ = (kStage + kLThreads - 1) / kLThreads;
   bool fg = false;      // a foreground pixel among the inputs of the tile's SSIM terms
   float shx, shy;       // the shifts of image and target
+  bool all_fg;          // every staged pixel is foreground
   {
     float iv[kStageQ], gv[kStageQ];
     uint8_t mv[kStageQ];
@@ -160,6 +171,7 @@ __global__ __launch_bounds__(kLThreads) void k_ssim(
       ty_ += s_red[1][w];
       tn += s_red[2][w];
     }
+    all_fg = tn == (float)kStage;
     shx = tn > 0.f ? tx_ / tn : 0.f;
     shy = tn > 0.f ? ty_ / tn : 0.f;
 #pragma unroll
@@ -200,44 +212,146 @@ __global__ __launch_bounds__(kLThreads) void k_ssim(
     return;
   }
 
-  // moments, horizontal: staged row r, positions c0 .. c0 + kH1 - 1
+  // The blurred foreground wt[u] at this thread's positions of the vertical
+  // pass (column vc, rows vr .. vr + kV1 - 1): 1 where every staged pixel is
+  // foreground, else one more plane, blurred before the others.
+  const int vc = t % kLM, vr = (t / kLM) * kV1;
+  const bool vert = t < (kLM / kV1) * kLM;
+  float P[kV1][3];
+  float ssum = 0.f;
+  // SSIM of position (vr + u, vc) from its blurred moments; the partials to
+  // P[u].  ALL: every staged pixel is foreground (wt = 1).
+  auto position = [&](int u, auto ALL, float ux, float uy, float e2, float exy, float wt) {
+    constexpr bool all = decltype(ALL)::value;
+    const int y = oy - kLR + vr + u, x = ox - kLR + vc;
+    const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
+    // moments of the shifted values (mu', E') and the blurred mask wt,
+    // om = 1 - wt (x = x'' + s M with M^2 = M and x'' M = x''):
+    //   mu = mu' + s wt,  var = E'xx - mu'^2 + om (2 s mu' + s^2 wt),
+    //   cov = E'xy - mu'x mu'y + om (sy mu'x + sx mu'y + sx sy wt)
+    // and only the sum of the two variances is used
+    const float om = all ? 0.f : 1.f - wt;
+    const float mx = all ? ux + shx : fmaf(shx, wt, ux);
+    const float my = all ? uy + shy : fmaf(shy, wt, uy);
+    float v2 = (e2 - ux * ux) - uy * uy;
+    float cv = exy - ux * uy;
+    if (!all) {
+      v2 += om * ((2.f * shx * ux + shx * shx * wt) + (2.f * shy * uy + shy * shy * wt));
+      cv += om * (shy * ux + shx * uy + shx * shy * wt);
+    }
+    const float A1 = 2.f * mx * my + C1;
+    const float A2 = 2.f * cv + C2;
+    const float B1 = mx * mx + my * my + C1;
+    const float B2 = v2 + C2;
+    // B1, B2 >= C1, C2 > 0: hardware reciprocals (1 ulp) suffice
+    const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
+    const float iB = iB1 * iB2;
+    const float S = A1 * A2 * iB;
+    const bool in = x >= 0 && x < W && y >= 0 && y < H;
+    if (in && vc >= kLR && vc < kLR + kLT && vr + u >= kLR && vr + u < kLR + kLT) ssum += S;
+    // partials of S in (mu, var, cov), folded so that, at a foreground
+    // pixel p, dS/dx_p = sum_q w_qp (Q0_q + 2 x''_p Q1_q + y''_p Q2_q)
+    // since there x_p - mu_q = x''_p - mu'_q + sx om_q
+    // dS/dmu_x = 2 A2 / (B1^2 B2) (my - mx) (my (mx + my) + C1), the
+    // factored form of 2 my A2 / (B1 B2) - 2 mx A1 A2 / (B1^2 B2), whose
+    // two terms cancel where the means agree; my - mx from the shifted means
+    const float dm = all ? (uy - ux) + (shy - shx) : (uy - ux) + (shy - shx) * wt;
+    const float Pm = 2.f * A2 * iB2 * iB1 * iB1 * dm * fmaf(my, mx + my, C1);
+    const float Pv = -S * iB2;                                  // dS/dvar_x
+    const float Pc = 2.f * A1 * iB;                             // dS/dcov
+    const float Q0 = all ? Pm - 2.f * ux * Pv - uy * Pc
+                         : Pm + 2.f * (shx * om - ux) * Pv + (shy * om - uy) * Pc;
+    P[u][0] = in ? Q0 : 0.f;
+    P[u][1] = in ? Pv : 0.f;
+    P[u][2] = in ? Pc : 0.f;
+  };
+
+  // moments, horizontal: item it = staged row r, positions c0 .. c0 + kH1 - 1.
+  // Held in registers until every thread has read the images, whose LDS they
+  // then take.
   constexpr int kItems1 = kLS * (kLM / kH1);
-  for (int it = t; it < kItems1; it += kLThreads) {
+  constexpr int kRounds1 = (kItems1 + kLThreads - 1) / kLThreads;
+  float acc[kRounds1][kH1][kLMom];
+#pragma unroll
+  for (int i = 0; i < kRounds1; ++i) {
+    const int it = min(t + i * kLThreads, kItems1 - 1);
     const int r = it / (kLM / kH1), c0 = (it - r * (kLM / kH1)) * kH1;
-    float acc[kH1][kLMom];
 #pragma unroll
     for (int u = 0; u < kH1; ++u)
 #pragma unroll
-      for (int q = 0; q < kLMom; ++q) acc[u][q] = 0.f;
+      for (int q = 0; q < kLMom; ++q) acc[i][u][q] = 0.f;
 #pragma unroll
     for (int j = 0; j < kH1 + 2 * kLR; ++j) {
       const float xv = s_x[r * kLSs + c0 + j], yv = s_y[r * kLSs + c0 + j];
-      const float xx = xv * xv, yy = yv * yv, xy = xv * yv;
-      const float mk = __float_as_uint(xv) == 0x80000000u ? 0.f : 1.f;
+      const float e2 = fmaf(xv, xv, yv * yv), xy = xv * yv;
 #pragma unroll
       for (int u = 0; u < kH1; ++u) {
         const int k = j - u;
         if (k < 0 || k > 2 * kLR) continue;
         const float w = win.w[k];
-        acc[u][0] = fmaf(w, xv, acc[u][0]);
-        acc[u][1] = fmaf(w, yv, acc[u][1]);
-        acc[u][2] = fmaf(w, xx, acc[u][2]);
-        acc[u][3] = fmaf(w, yy, acc[u][3]);
-        acc[u][4] = fmaf(w, xy, acc[u][4]);
-        acc[u][5] = fmaf(w, mk, acc[u][5]);
+        acc[i][u][0] = fmaf(w, xv, acc[i][u][0]);
+        acc[i][u][1] = fmaf(w, yv, acc[i][u][1]);
+        acc[i][u][2] = fmaf(w, e2, acc[i][u][2]);
+        acc[i][u][3] = fmaf(w, xy, acc[i][u][3]);
       }
     }
+  }
+  float wt[kV1];
+  if (!all_fg) {
+    float am[kRounds1][kH1];
 #pragma unroll
-    for (int u = 0; u < kH1; ++u)
+    for (int i = 0; i < kRounds1; ++i) {
+      const int it = min(t + i * kLThreads, kItems1 - 1);
+      const int r = it / (kLM / kH1), c0 = (it - r * (kLM / kH1)) * kH1;
 #pragma unroll
-      for (int q = 0; q < kLMom; ++q) s_h[(q * kLS + r) * kLMs + c0 + u] = acc[u][q];
+      for (int u = 0; u < kH1; ++u) am[i][u] = 0.f;
+#pragma unroll
+      for (int j = 0; j < kH1 + 2 * kLR; ++j) {
+        const float mk = __float_as_uint(s_x[r * kLSs + c0 + j]) == 0x80000000u ? 0.f : 1.f;
+#pragma unroll
+        for (int u = 0; u < kH1; ++u) {
+          const int k = j - u;
+          if (k < 0 || k > 2 * kLR) continue;
+          am[i][u] = fmaf(win.w[k], mk, am[i][u]);
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kRounds1; ++i)
+      if (t + i * kLThreads < kItems1)
+#pragma unroll
+        for (int u = 0; u < kH1; ++u) s_h[(t + i * kLThreads) * kH1 + u] = am[i][u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kV1; ++u) wt[u] = 0.f;
+    if (vert) {
+#pragma unroll
+      for (int j = 0; j < kV1 + 2 * kLR; ++j) {
+        const float h = s_h[(vr + j) * kLM + vc];
+#pragma unroll
+        for (int u = 0; u < kV1; ++u) {
+          const int k = j - u;
+          if (k < 0 || k > 2 * kLR) continue;
+          wt[u] = fmaf(win.w[k], h, wt[u]);
+        }
+      }
+    }
   }
   __syncthreads();
+  // rows of kLM = 14 kH1 values: item it's kH1 values start at it * kH1
+#pragma unroll
+  for (int i = 0; i < kRounds1; ++i)
+    if (t + i * kLThreads < kItems1)
+#pragma unroll
+      for (int q = 0; q < kLMom; ++q)
+#pragma unroll
+        for (int u = 0; u < kH1; ++u)
+          s_h[q * kLS * kLM + (t + i * kLThreads) * kH1 + u] = acc[i][u][q];
+  __syncthreads();
 
-  // moments, vertical, then SSIM and its partials at positions (r0 + u, c)
-  float ssum = 0.f;
-  if (t < (kLM / kV1) * kLM) {
-    const int c = t % kLM, r0 = (t / kLM) * kV1;
+  // moments, vertical, then SSIM and its partials at positions (vr + u, vc)
+  if (vert) {
     float m[kV1][kLMom];
 #pragma unroll
     for (int u = 0; u < kV1; ++u)
@@ -247,7 +361,7 @@ __global__ __launch_bounds__(kLThreads) void k_ssim(
     for (int j = 0; j < kV1 + 2 * kLR; ++j) {
       float h[kLMom];
 #pragma unroll
-      for (int q = 0; q < kLMom; ++q) h[q] = s_h[(q * kLS + r0 + j) * kLMs + c];
+      for (int q = 0; q < kLMom; ++q) h[q] = s_h[(q * kLS + vr + j) * kLM + vc];
 #pragma unroll
       for (int u = 0; u < kV1; ++u) {
         const int k = j - u;
@@ -256,54 +370,22 @@ __global__ __launch_bounds__(kLThreads) void k_ssim(
         for (int q = 0; q < kLMom; ++q) m[u][q] = fmaf(win.w[k], h[q], m[u][q]);
       }
     }
-    const int x = ox - kLR + c;
-    const bool colin = x >= 0 && x < W;
-    const bool colc = c >= kLR && c < kLR + kLT;
-    float P[kV1][3];
+    if (all_fg) {
 #pragma unroll
-    for (int u = 0; u < kV1; ++u) {
-      const int y = oy - kLR + r0 + u;
-      const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
-      // moments of the shifted values (mu', E') and the blurred mask wt,
-      // om = 1 - wt (x = x'' + s M with M^2 = M and x'' M = x''):
-      //   mu = mu' + s wt,  var = E'xx - mu'^2 + om (2 s mu' + s^2 wt),
-      //   cov = E'xy - mu'x mu'y + om (sy mu'x + sx mu'y + sx sy wt)
-      const float wt = m[u][5], om = 1.f - wt;
-      const float ux = m[u][0], uy = m[u][1];
-      const float mx = fmaf(shx, wt, ux), my = fmaf(shy, wt, uy);
-      const float vx = (m[u][2] - ux * ux) + om * (2.f * shx * ux + shx * shx * wt);
-      const float vy = (m[u][3] - uy * uy) + om * (2.f * shy * uy + shy * shy * wt);
-      const float cv = (m[u][4] - ux * uy) + om * (shy * ux + shx * uy + shx * shy * wt);
-      const float A1 = 2.f * mx * my + C1;
-      const float A2 = 2.f * cv + C2;
-      const float B1 = mx * mx + my * my + C1;
-      const float B2 = vx + vy + C2;
-      // B1, B2 >= C1, C2 > 0: hardware reciprocals (1 ulp) suffice
-      const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
-      const float iB = iB1 * iB2;
-      const float S = A1 * A2 * iB;
-      const bool in = colin && y >= 0 && y < H;
-      if (in && colc && r0 + u >= kLR && r0 + u < kLR + kLT) ssum += S;
-      // partials of S in (mu, var, cov), folded so that, at a foreground
-      // pixel p, dS/dx_p = sum_q w_qp (Q0_q + 2 x''_p Q1_q + y''_p Q2_q)
-      // since there x_p - mu_q = x''_p - mu'_q + sx om_q
-      // dS/dmu_x = 2 A2 / (B1^2 B2) (my - mx) (my (mx + my) + C1), the
-      // factored form of 2 my A2 / (B1 B2) - 2 mx A1 A2 / (B1^2 B2), whose
-      // two terms cancel where the means agree; my - mx from the shifted means
-      const float dm = (uy - ux) + (shy - shx) * wt;
-      const float Pm = 2.f * A2 * iB2 * iB1 * iB1 * dm * fmaf(my, mx + my, C1);
-      const float Pv = -S * iB2;                                  // dS/dvar_x
-      const float Pc = 2.f * A1 * iB;                             // dS/dcov
-      P[u][0] = in ? Pm + 2.f * (shx * om - ux) * Pv + (shy * om - uy) * Pc : 0.f;
-      P[u][1] = in ? Pv : 0.f;
-      P[u][2] = in ? Pc : 0.f;
+      for (int u = 0; u < kV1; ++u)
+        position(u, std::true_type{}, m[u][0], m[u][1], m[u][2], m[u][3], 1.f);
+    } else {
+#pragma unroll
+      for (int u = 0; u < kV1; ++u)
+        position(u, std::false_type{}, m[u][0], m[u][1], m[u][2], m[u][3], wt[u]);
     }
-    // region A (the staged images) is free once every thread is past the
-    // horizontal pass, which the barrier above guarantees
+  }
+  __syncthreads();
+  if (vert) {
 #pragma unroll
     for (int u = 0; u < kV1; ++u)
 #pragma unroll
-      for (int q = 0; q < 3; ++q) s_p[(q * kLM + r0 + u) * kLMs + c] = P[u][q];
+      for (int q = 0; q < 3; ++q) s_p[(q * kLM + vr + u) * kLMs + vc] = P[u][q];
   }
   __syncthreads();
 
@@ -404,29 +486,48 @@ __global__ __launch_bounds__(kLThreads) void k_ssim(
   }
 }
 
-__global__ __launch_bounds__(256) void k_loss_final(const float* __restrict__ part,
-                                                    int64_t blocks_per_img, double inv_n,
-                                                    float lambda, float* __restrict__ loss_out,
-                                                    int64_t* __restrict__ status) {
-  __shared__ double sm[2][256];
-  const int64_t img = blockIdx.x;
+// One work-group per image; four pairs a thread in flight (256 threads with one
+// pair each: FINALUS).
+constexpr int kFinalThreads = 1024;
+
+__global__ __launch_bounds__(kFinalThreads) void k_loss_final(
+    const float* __restrict__ part, int64_t blocks_per_img, double inv_n, float lambda,
+    float* __restrict__ loss_out, int64_t* __restrict__ status) {
+  __shared__ double sm[2][kFinalThreads / 64];
+  const int64_t img = blockIdx.x, n = 3 * blocks_per_img;
+  const float* p = part + 2 * img * n;
   double s = 0.0, l = 0.0;
-  for (int64_t b = threadIdx.x; b < 3 * blocks_per_img; b += 256) {
-    s += (double)part[2 * (img * 3 * blocks_per_img + b)];
-    l += (double)part[2 * (img * 3 * blocks_per_img + b) + 1];
-  }
-  sm[0][threadIdx.x] = s;
-  sm[1][threadIdx.x] = l;
-  __syncthreads();
-  for (int d = 128; d > 0; d >>= 1) {
-    if (threadIdx.x < d) {
-      sm[0][threadIdx.x] += sm[0][threadIdx.x + d];
-      sm[1][threadIdx.x] += sm[1][threadIdx.x + d];
+  for (int64_t b = threadIdx.x; b < n; b += 4 * kFinalThreads) {
+    float vs[4], vl[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int64_t i = b + k * kFinalThreads;
+      vs[k] = i < n ? p[2 * i] : 0.f;
+      vl[k] = i < n ? p[2 * i + 1] : 0.f;
     }
-    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      s += (double)vs[k];
+      l += (double)vl[k];
+    }
   }
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    s += __shfl_down(s, d);
+    l += __shfl_down(l, d);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sm[0][threadIdx.x >> 6] = s;
+    sm[1][threadIdx.x >> 6] = l;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    const double ssim = sm[0][0] * inv_n, l1 = sm[1][0] * inv_n;
+    s = l = 0.0;
+    for (int w = 0; w < kFinalThreads / 64; ++w) {
+      s += sm[0][w];
+      l += sm[1][w];
+    }
+    const double ssim = s * inv_n, l1 = l * inv_n;
     const float L = (float)((1.0 - lambda) * l1 + lambda * (1.0 - ssim));
     loss_out[img] = L;
     if (status && !isfinite(L)) atomicOr((unsigned long long*)&status[0], (unsigned long long)GS_FLAG_NONFINITE);
@@ -632,8 +733,8 @@ static gs_status launch_loss(const float* image, const float* target, const uint
                        mask, H, W, L.tiles_x, L.blocks_per_img, win, l1_coef, ssim_coef, d_image,
                        part);
   GS_LAUNCH_CHECK("gs_loss/ssim");
-  hipLaunchKernelGGL(k_loss_final, dim3((unsigned)S), dim3(256), 0, s, part, L.blocks_per_img,
-                     1.0 / N, lambda_dssim, loss_out, status);
+  hipLaunchKernelGGL(k_loss_final, dim3((unsigned)S), dim3(kFinalThreads), 0, s, part,
+                     L.blocks_per_img, 1.0 / N, lambda_dssim, loss_out, status);
   GS_LAUNCH_CHECK("gs_loss/final");
   return GS_OK;
 }
