@@ -145,6 +145,10 @@ __device__ __forceinline__ uint64_t splat_pass_lanes(const Splat& s, float p2) {
   constexpr int kOle = 5, kOge = 3;                       // ordered <=, >=
   return __builtin_amdgcn_fcmpf(p2, 0.0f, kOle) & __builtin_amdgcn_fcmpf(p2, s.thr, kOge);
 }
+__device__ __forceinline__ uint64_t lanes_lt(float a, float b) {
+  constexpr int kOlt = 4;                                 // ordered <
+  return __builtin_amdgcn_fcmpf(a, b, kOlt);
+}
 __device__ __forceinline__ uint64_t lanes_le(int a, int b) {
   constexpr int kSle = 41;                                // signed <=
   return __builtin_amdgcn_sicmp(a, b, kSle);

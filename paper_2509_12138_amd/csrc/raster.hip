@@ -23,6 +23,8 @@
 namespace gsmi {
 
 constexpr int kRasterWave = 64;
+// A forward wave's LDS batch: 64 entries and the two that its loop reads ahead.
+constexpr int kFwdSlots = kRasterWave + 2;
 
 // XCD-aware tile order: work-group i runs on XCD (i mod 8); give each XCD a
 // contiguous range of tiles.
@@ -81,10 +83,93 @@ struct PixBox {
   float x0, x1, y0, y1;
 };
 
+// The forward's walk over one staged batch.  Only entries that may reach the
+// wave's box are kept, packed in list order, so that a visit costs an address
+// increment and no bit scan; pad1 carries the list position.  Entry i + 1 is
+// read while i is composited (two register sets alternate), its colour with
+// the words of the skip test: read behind the test's branch, it made a lone
+// wave wait for the LDS at every blend.  What a visit costs in instructions,
+// scalar ones included, is what counts: the longest lists' waves run on alone
+// after the others (1080p: 150 us of 360 for lists of 6400 entries), and there
+// a wave issues one instruction in about 5 cycles.  70 -> 45 instructions a
+// blending visit: 1920x1080 forward 361 -> 308 us, 8 partitions x 4 views 595
+// -> 519, 3-band colour at 1024x830 216 -> 176; split forward at 4K, part 745
+// -> 624.
+struct FwdEntry {
+  float4 g;                 // mx, my, A, B
+  float2 h;                 // C, thr
+  float4 col;               // o, r, g, b
+};
+
+__device__ __forceinline__ FwdEntry fwd_entry(const Splat* s) {
+  return FwdEntry{*reinterpret_cast<const float4*>(s), *reinterpret_cast<const float2*>(&s->C),
+                  *reinterpret_cast<const float4*>(&s->o)};
+}
+
+// Packs the lanes' hits into s_splat (kFwdSlots entries); returns their number.
+__device__ __forceinline__ int fwd_pack(Splat& s, bool hit, int pos, Splat* s_splat) {
+  const uint64_t hits = __ballot(hit);
+  const int cnt = __builtin_popcountll(hits);
+  wave_sync();
+  if (hit) {
+    s.pad1 = __builtin_bit_cast(float, pos);
+    s_splat[__builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32),
+                                      __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u))] = s;
+  }
+  s_splat[cnt].thr = INFINITY;        // an odd count's partner passes no test
+  wave_sync();
+  return cnt;
+}
+
+// body(entry, packed index) for the cnt packed entries, in order.
+template <typename F>
+__device__ __forceinline__ void fwd_for_each(const Splat* s_splat, int cnt, F&& body) {
+  if (cnt) {
+    FwdEntry ea = fwd_entry(s_splat);
+    for (int i = 0;; i += 2) {
+      const FwdEntry eb = fwd_entry(s_splat + i + 1);
+      body(ea, i);
+      ea = fwd_entry(s_splat + i + 2);
+      body(eb, i + 1);
+      if (i + 2 >= cnt) break;
+    }
+  }
+}
+
+// Falloff exponents of the lane's pixels and, per pixel, the lanes of mask
+// live whose skip tests entry e passes; returns the union of the masks.
+template <int PX>
+__device__ __forceinline__ uint64_t fwd_test(const FwdEntry& e, float fx, const float* fy,
+                                             const uint64_t (&live)[PX], float (&p2)[PX],
+                                             uint64_t (&pass)[PX]) {
+  // keeps the read of the colour with the others, ahead of the branch
+  asm volatile("" ::"v"(e.col.x), "v"(e.col.y), "v"(e.col.z), "v"(e.col.w));
+  Splat sp;
+  sp.mx = e.g.x;
+  sp.my = e.g.y;
+  sp.A = e.g.z;
+  sp.B = e.g.w;
+  sp.C = e.h.x;
+  sp.thr = e.h.y;
+  splat_p2_column<PX>(sp, __fsub_rn(fx, sp.mx), fy, p2);
+  uint64_t any = 0;
+#pragma unroll
+  for (int k = 0; k < PX; ++k) {
+    pass[k] = splat_pass_lanes(sp, p2[k]) & live[k];
+    any |= pass[k];
+  }
+  return any;
+}
+
+// List position after the packed entry i.
+__device__ __forceinline__ int fwd_pos(const Splat* s_splat, int i) {
+  return __builtin_bit_cast(int, s_splat[i].pad1);
+}
+
 // Forward pass of one tile for one lane's PX pixels (pixel slots q0 + 64 k
 // of the tile, slot = row * TW + column), which lie in the wave's box.
 // WITH_COLOR=false is the replay used by the backward in RECOMPUTE mode.
-// s_splat: this wave's 64-entry LDS batch.
+// s_splat: this wave's LDS batch of kFwdSlots entries.
 // CHUNKED (with colour) also prepares the chunked backward: boundary c is
 // the list position (c+1)*chunk; for each pixel the forward stores at slot c
 // of `ck` (ck[c * TW*TH + pixel]) the transmittance T_c there and the colour
@@ -102,16 +187,14 @@ __device__ __forceinline__ void tile_forward(const float* __restrict__ rec,
                                              float4* ck = nullptr, int chunk = 0, float bg0 = 0.f,
                                              float bg1 = 0.f, float bg2 = 0.f, int q0 = 0) {
   const int lane = threadIdx.x & (kRasterWave - 1);
-  // a pixel that is done (outside the image, or stopped) gets a NaN row
-  // coordinate: its falloff exponent is NaN and fails both skip tests, so
-  // no separate flag is tested per entry
-  float fyk[PX];
+  // lanes whose pixel k still composites: inside the image and not stopped
+  uint64_t live[PX];
   float Tl[PX], Lc[PX][3];
 #pragma unroll
   for (int k = 0; k < PX; ++k) {
     T[k] = 1.0f;
     last[k] = 0;
-    fyk[k] = inside[k] ? fy[k] : __builtin_nanf("");
+    live[k] = __ballot(inside[k]);
     if (WITH_COLOR) C[k][0] = C[k][1] = C[k][2] = 0.0f;
     if (CHUNKED) {
       Tl[k] = 1.0f;
@@ -127,97 +210,58 @@ __device__ __forceinline__ void tile_forward(const float* __restrict__ rec,
   if (start + lane < end) nraw = fetch_splat(rec, ids[start + lane]);
   if (start + kRasterWave + lane < end) nid2 = ids[start + kRasterWave + lane];
   for (uint32_t b0 = start; b0 < end; b0 += kRasterWave) {
-    bool lane_done = true;
+    uint64_t any_live = 0;
 #pragma unroll
-    for (int k = 0; k < PX; ++k) lane_done = lane_done && (fyk[k] != fyk[k]);
-    if (__all(lane_done)) break;
+    for (int k = 0; k < PX; ++k) any_live |= live[k];
+    if (!any_live) break;
     const int n = (int)min((uint32_t)kRasterWave, end - b0);
     const RawSplat raw = nraw;
     const uint32_t nid = nid2;
     if (b0 + kRasterWave + lane < end) nraw = fetch_splat(rec, nid);
     if (b0 + 2 * kRasterWave + lane < end) nid2 = ids[b0 + 2 * kRasterWave + lane];
-    wave_sync();
-    bool hit = false;
-    if (lane < n) {
-      const Splat s = make_splat(raw);
-      hit = splat_may_hit(s, box.x0, box.x1, box.y0, box.y1);
-      s_splat[lane] = s;
-    }
-    // entries that cannot reach the wave's box are never visited
-    uint64_t todo = __ballot(hit);
-    const bool hit_any = todo != 0;
-    wave_sync();
-    // composite entry j of the batch (skip-test words g = mx, my, A, B and
-    // h = C, thr already read)
-    auto composite = [&](const float4& g, const float2& h, int j) {
-      Splat sp;
-      sp.mx = g.x;
-      sp.my = g.y;
-      sp.A = g.z;
-      sp.B = g.w;
-      sp.C = h.x;
-      sp.thr = h.y;
-      const float dx = __fsub_rn(fx, sp.mx);
+    Splat s = make_splat(raw);
+    const bool hit = lane < n && splat_may_hit(s, box.x0, box.x1, box.y0, box.y1);
+    const int cnt = fwd_pack(s, hit, (int)(b0 - start) + lane + 1, s_splat);
+    int lastc[PX];            // packed index of the lane's last blend in the batch
+#pragma unroll
+    for (int k = 0; k < PX; ++k) lastc[k] = -1;
+    fwd_for_each(s_splat, cnt, [&](const FwdEntry& e, int i) {
       float p2[PX];
-      splat_p2_column<PX>(sp, dx, fyk, p2);
-      bool pass[PX], any = false;
+      uint64_t pass[PX];
+      if (!fwd_test<PX>(e, fx, fy, live, p2, pass)) return;
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
-        pass[k] = splat_pass(sp, p2[k]);
-        any = any || pass[k];
-      }
-      if (!__any(any)) return;
-      const float4 col = *reinterpret_cast<const float4*>(&s_splat[j].o);   // o, r, g, b
-      const int pos = (int)(b0 - start) + j + 1;
-#pragma unroll
-      for (int k = 0; k < PX; ++k) {
-        if (!pass[k]) continue;
-        const float alpha = fminf(kAlphaMax, col.x * splat_gauss(p2[k]));
+        if (PX > 1 && !pass[k]) continue;
+        const float alpha = fminf(kAlphaMax, e.col.x * splat_gauss(p2[k]));
         const float Tn = T[k] * (1.0f - alpha);
-        const bool stop = Tn < kTMin;
-        fyk[k] = stop ? __builtin_nanf("") : fyk[k];
-        if (stop) continue;
-        if (WITH_COLOR) {
-          const float w = alpha * T[k];
-          C[k][0] = fmaf(col.y, w, C[k][0]);
-          C[k][1] = fmaf(col.z, w, C[k][1]);
-          C[k][2] = fmaf(col.w, w, C[k][2]);
+        const uint64_t stop = pass[k] & lanes_lt(Tn, kTMin);
+        if (__builtin_expect(stop != 0, 0)) {   // rare: a branch, not mask operations a visit
+          asm volatile("");
+          live[k] &= ~stop;
+          pass[k] &= ~stop;
         }
-        if (CHUNKED) {
-          const float wl = alpha * Tl[k];
-          Lc[k][0] = fmaf(col.y, wl, Lc[k][0]);
-          Lc[k][1] = fmaf(col.z, wl, Lc[k][1]);
-          Lc[k][2] = fmaf(col.w, wl, Lc[k][2]);
-          Tl[k] = Tl[k] * (1.0f - alpha);
+        if (lane_in(pass[k])) {
+          if (WITH_COLOR) {
+            const float w = alpha * T[k];
+            C[k][0] = fmaf(e.col.y, w, C[k][0]);
+            C[k][1] = fmaf(e.col.z, w, C[k][1]);
+            C[k][2] = fmaf(e.col.w, w, C[k][2]);
+          }
+          if (CHUNKED) {
+            const float wl = alpha * Tl[k];
+            Lc[k][0] = fmaf(e.col.y, wl, Lc[k][0]);
+            Lc[k][1] = fmaf(e.col.z, wl, Lc[k][1]);
+            Lc[k][2] = fmaf(e.col.w, wl, Lc[k][2]);
+            Tl[k] = Tl[k] * (1.0f - alpha);
+          }
+          T[k] = Tn;
+          lastc[k] = i;
         }
-        T[k] = Tn;
-        last[k] = pos;
       }
-    };
-    // the skip-test words of the next entry are read from LDS while the
-    // current one is composited; two register sets alternate
-    if (hit_any) {
-      int ja = (int)__builtin_ctzll(todo);
-      todo &= todo - 1;
-      float4 ga = *reinterpret_cast<const float4*>(&s_splat[ja]);     // mx, my, A, B
-      float2 ha = *reinterpret_cast<const float2*>(&s_splat[ja].C);   // C, thr
-      for (;;) {
-        const bool more_a = todo != 0;
-        const int jb = more_a ? (int)__builtin_ctzll(todo) : ja;
-        const float4 gb = *reinterpret_cast<const float4*>(&s_splat[jb]);
-        const float2 hb = *reinterpret_cast<const float2*>(&s_splat[jb].C);
-        todo &= todo - 1;
-        composite(ga, ha, ja);
-        if (!more_a) break;
-        const bool more_b = todo != 0;
-        ja = more_b ? (int)__builtin_ctzll(todo) : jb;
-        ga = *reinterpret_cast<const float4*>(&s_splat[ja]);
-        ha = *reinterpret_cast<const float2*>(&s_splat[ja].C);
-        todo &= todo - 1;
-        composite(gb, hb, jb);
-        if (!more_b) break;
-      }
-    }
+    });
+#pragma unroll
+    for (int k = 0; k < PX; ++k)
+      if (lastc[k] >= 0) last[k] = fwd_pos(s_splat, lastc[k]);
     if (CHUNKED) {
       reached = b0 + (uint32_t)n - start;
       if (reached % (uint32_t)chunk == 0) {
@@ -421,9 +465,9 @@ void k_raster_fwd(RasterDev a, TileSched sch,
                                                                  float* __restrict__ image,
                                                                  float* __restrict__ T_final,
                                                                  int32_t* __restrict__ n_contrib) {
-  __shared__ Splat s_splat[kRasterWave * NW];
+  __shared__ Splat s_splat[kFwdSlots * NW];
   // wave-uniform base (scalar), so per-entry LDS addresses stay scalar too
-  Splat* mine = s_splat + __builtin_amdgcn_readfirstlane(threadIdx.x / kRasterWave) * kRasterWave;
+  Splat* mine = s_splat + __builtin_amdgcn_readfirstlane(threadIdx.x / kRasterWave) * kFwdSlots;
   for_each_tile(sch, a.n_tiles, [&](int64_t tile, int) {
     fwd_tile<TW, TH, NW>(a, ch, tile, mine, image, T_final, n_contrib);
   });
@@ -739,7 +783,7 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_bwd(RasterDev a, TileSch
                                                             const float* __restrict__ d_image,
                                                             float* __restrict__ d_rec) {
   constexpr int NB = TW * TH / 64 / NK;
-  __shared__ Splat s_splat[kRasterWave];
+  __shared__ Splat s_splat[RECOMPUTE ? kFwdSlots : kRasterWave];
   for_each_tile<NB>(sch, a.n_tiles, [&](int64_t tile, int b) {
     bwd_blocks<TW, TH, NK, RECOMPUTE>(a, tile, b, s_splat, T_final, n_contrib, d_image, d_rec);
   });
@@ -1041,7 +1085,7 @@ template <int TW, int TH>
 __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_part(RasterDev a, ChunkDev ch,
                                                                 uint16_t* __restrict__ clast) {
   constexpr int PX = TileGeom<TW, TH>::PX;
-  __shared__ Splat s_splat[kRasterWave];
+  __shared__ Splat s_splat[kFwdSlots];
   const uint32_t item = blockIdx.x;
   if (item >= ch.offset[a.n_tiles]) return;
   const int64_t tile = ch.items[item];
@@ -1054,52 +1098,48 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_part(RasterDev a, Ch
   const PixBox box{(float)(L.tx * TW) + 0.5f, (float)(L.tx * TW + TW - 1) + 0.5f,
                    (float)(L.ty * TH) + 0.5f, (float)(L.ty * TH + TH - 1) + 0.5f};
   const int lane = threadIdx.x;
-  float fyk[PX], Tl[PX], Lc[PX][3];
+  uint64_t live[PX];
+  float Tl[PX], Lc[PX][3];
   int lastl[PX];
 #pragma unroll
   for (int k = 0; k < PX; ++k) {
-    fyk[k] = L.inside[k] ? L.fy[k] : __builtin_nanf("");
+    live[k] = __ballot(L.inside[k]);
     Tl[k] = 1.0f;
     Lc[k][0] = Lc[k][1] = Lc[k][2] = 0.0f;
     lastl[k] = 0;
   }
   for (int b0 = lo; b0 < hi_pos; b0 += kRasterWave) {
     const int n = min(kRasterWave, hi_pos - b0);
-    wave_sync();
+    Splat s{};
     bool hit = false;
     if (lane < n) {
-      const Splat s = load_splat(a.rec, a.ids[start + b0 + lane]);
+      s = load_splat(a.rec, a.ids[start + b0 + lane]);
       hit = splat_may_hit(s, box.x0, box.x1, box.y0, box.y1);
-      s_splat[lane] = s;
     }
-    uint64_t todo = __ballot(hit);
-    wave_sync();
-    while (todo) {
-      const int j = (int)__builtin_ctzll(todo);
-      todo &= todo - 1;
-      const Splat sp = s_splat[j];
-      const float dx = __fsub_rn(L.fx, sp.mx);
+    const int cnt = fwd_pack(s, hit, b0 - lo + lane + 1, s_splat);
+    int lastc[PX];
+#pragma unroll
+    for (int k = 0; k < PX; ++k) lastc[k] = -1;
+    fwd_for_each(s_splat, cnt, [&](const FwdEntry& e, int i) {
       float p2[PX];
-      splat_p2_column<PX>(sp, dx, fyk, p2);
-      bool pass[PX], any = false;
+      uint64_t pass[PX];
+      if (!fwd_test<PX>(e, L.fx, L.fy, live, p2, pass)) return;
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
-        pass[k] = splat_pass(sp, p2[k]);
-        any = any || pass[k];
+        if (lane_in(pass[k])) {
+          const float alpha = fminf(kAlphaMax, e.col.x * splat_gauss(p2[k]));
+          const float wl = alpha * Tl[k];
+          Lc[k][0] = fmaf(e.col.y, wl, Lc[k][0]);
+          Lc[k][1] = fmaf(e.col.z, wl, Lc[k][1]);
+          Lc[k][2] = fmaf(e.col.w, wl, Lc[k][2]);
+          Tl[k] = Tl[k] * (1.0f - alpha);
+          lastc[k] = i;
+        }
       }
-      if (!__any(any)) continue;
+    });
 #pragma unroll
-      for (int k = 0; k < PX; ++k) {
-        if (!pass[k]) continue;
-        const float alpha = fminf(kAlphaMax, sp.o * splat_gauss(p2[k]));
-        const float wl = alpha * Tl[k];
-        Lc[k][0] = fmaf(sp.r, wl, Lc[k][0]);
-        Lc[k][1] = fmaf(sp.g, wl, Lc[k][1]);
-        Lc[k][2] = fmaf(sp.b, wl, Lc[k][2]);
-        Tl[k] = Tl[k] * (1.0f - alpha);
-        lastl[k] = b0 - lo + j + 1;
-      }
-    }
+    for (int k = 0; k < PX; ++k)
+      if (lastc[k] >= 0) lastl[k] = fwd_pos(s_splat, lastc[k]);
   }
   float4* ck = ch.ck + ((int64_t)c0 + (c >= 1 ? c - 1 : nc - 1)) * (TW * TH);
   uint16_t* cl = clast + ((int64_t)c0 + c) * (TW * TH);
@@ -1121,14 +1161,15 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_part(RasterDev a, Ch
 // over the chunks' (P, L) (identity after a pixel's stop, the partial
 // composite up to it in the stopping chunk).  Both walks over the chunks
 // keep D chunks' loads in flight: a long list's join is a chain of
-// dependent loads otherwise.
+// dependent loads otherwise (lists of 450 chunks at 4K: D 4 -> 8, 945 -> 776
+// us).
 template <int TW, int TH>
 __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
     RasterDev a, TileSched sch, ChunkDev ch, const uint16_t* __restrict__ clast,
     float* __restrict__ image, float* __restrict__ T_final, int32_t* __restrict__ n_contrib) {
   constexpr int PX = TileGeom<TW, TH>::PX, NP = TW * TH;
-  constexpr int D = PX >= 4 ? 1 : 4 / PX;
-  __shared__ Splat s_splat[kRasterWave];
+  constexpr int D = PX >= 8 ? 1 : 8 / PX;
+  __shared__ Splat s_splat[kFwdSlots];
   for_each_tile(sch, a.n_tiles, [&](int64_t tile, int) {
     const LanePixels<TW, TH> L(a, tile);
     const int lane = threadIdx.x;
@@ -1181,62 +1222,57 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
       if (!__any(any_fix)) return;
       // composite chunk c again, entry by entry with the stop rule, for the
       // pixels whose transmittance reaches the cut-off inside it
-      float fyk[PX], Tl[PX], Lc[PX][3];
+      uint64_t live[PX];
+      float Tl[PX], Lc[PX][3];
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
-        fyk[k] = fix[k] ? L.fy[k] : __builtin_nanf("");
+        live[k] = __ballot(fix[k]);
         Tl[k] = 1.0f;
         Lc[k][0] = Lc[k][1] = Lc[k][2] = 0.0f;
       }
       const int lo = c * ch.chunk, hi_pos = min(lo + ch.chunk, len);
       for (int b0 = lo; b0 < hi_pos; b0 += kRasterWave) {
         const int n = min(kRasterWave, hi_pos - b0);
-        wave_sync();
+        Splat s{};
         bool hit = false;
         if (lane < n) {
-          const Splat s = load_splat(a.rec, a.ids[start + b0 + lane]);
+          s = load_splat(a.rec, a.ids[start + b0 + lane]);
           hit = splat_may_hit(s, box.x0, box.x1, box.y0, box.y1);
-          s_splat[lane] = s;
         }
-        uint64_t todo = __ballot(hit);
-        wave_sync();
-        while (todo) {
-          const int j = (int)__builtin_ctzll(todo);
-          todo &= todo - 1;
-          const Splat sp = s_splat[j];
-          const float dx = __fsub_rn(L.fx, sp.mx);
+        const int cnt = fwd_pack(s, hit, b0 + lane + 1, s_splat);
+        int lastc[PX];
+#pragma unroll
+        for (int k = 0; k < PX; ++k) lastc[k] = -1;
+        fwd_for_each(s_splat, cnt, [&](const FwdEntry& e, int i) {
           float p2[PX];
-          splat_p2_column<PX>(sp, dx, fyk, p2);
-          bool pass[PX], any = false;
+          uint64_t pass[PX];
+          if (!fwd_test<PX>(e, L.fx, L.fy, live, p2, pass)) return;
 #pragma unroll
           for (int k = 0; k < PX; ++k) {
-            pass[k] = splat_pass(sp, p2[k]);
-            any = any || pass[k];
-          }
-          if (!__any(any)) continue;
-#pragma unroll
-          for (int k = 0; k < PX; ++k) {
-            if (!pass[k]) continue;
-            const float alpha = fminf(kAlphaMax, sp.o * splat_gauss(p2[k]));
+            const float alpha = fminf(kAlphaMax, e.col.x * splat_gauss(p2[k]));
             const float Tn = T[k] * (1.0f - alpha);
-            if (Tn < kTMin) {              // the pixel stops; this entry is not blended
-              fyk[k] = __builtin_nanf("");
-              cs[k] = c;
-              continue;
+            // the pixel stops; this entry is not blended
+            const uint64_t stop = pass[k] & lanes_lt(Tn, kTMin);
+            live[k] &= ~stop;
+            if (lane_in(stop)) cs[k] = c;
+            if (lane_in(pass[k] & ~stop)) {
+              const float w = alpha * T[k];
+              C[k][0] = fmaf(e.col.y, w, C[k][0]);
+              C[k][1] = fmaf(e.col.z, w, C[k][1]);
+              C[k][2] = fmaf(e.col.w, w, C[k][2]);
+              const float wl = alpha * Tl[k];
+              Lc[k][0] = fmaf(e.col.y, wl, Lc[k][0]);
+              Lc[k][1] = fmaf(e.col.z, wl, Lc[k][1]);
+              Lc[k][2] = fmaf(e.col.w, wl, Lc[k][2]);
+              Tl[k] = Tl[k] * (1.0f - alpha);
+              T[k] = Tn;
+              lastc[k] = i;
             }
-            const float w = alpha * T[k];
-            C[k][0] = fmaf(sp.r, w, C[k][0]);
-            C[k][1] = fmaf(sp.g, w, C[k][1]);
-            C[k][2] = fmaf(sp.b, w, C[k][2]);
-            const float wl = alpha * Tl[k];
-            Lc[k][0] = fmaf(sp.r, wl, Lc[k][0]);
-            Lc[k][1] = fmaf(sp.g, wl, Lc[k][1]);
-            Lc[k][2] = fmaf(sp.b, wl, Lc[k][2]);
-            Tl[k] = Tl[k] * (1.0f - alpha);
-            T[k] = Tn;
-            last[k] = b0 + j + 1;
           }
-        }
+        });
+#pragma unroll
+        for (int k = 0; k < PX; ++k)
+          if (lastc[k] >= 0) last[k] = fwd_pos(s_splat, lastc[k]);
       }
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
