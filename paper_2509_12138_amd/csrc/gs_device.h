@@ -88,9 +88,12 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
   return v;
 }
 
-__device__ __forceinline__ float lane63(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+// The value of lane l (wave-uniform).
+__device__ __forceinline__ float lane_f(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
 }
+
+__device__ __forceinline__ float lane63(float v) { return lane_f(v, 63); }
 
 __device__ __forceinline__ float wave_sum(float v) { return lane63(wave_sum_to_lane63(v)); }
 

@@ -1155,7 +1155,10 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_part(RasterDev a, Ch
 // T_min: the partial products only fall, so no entry of the chunk stops
 // it) takes C += T L_c, T = T P_c; where T P_c < T_min the chunk is
 // composited again entry by entry from T with the stop rule (all lanes stage
-// it, the pixels concerned composite), and the pixel ends there.  Then the
+// it and test one such pixel after another, a lane per entry; the pixels
+// concerned composite what passed: with the whole wave visiting every entry,
+// as the first part does, these few pixels were most of the join, 776 -> 488
+// us at 4K), and the pixel ends there.  Then the
 // image, T_final and n_contrib are written, and the checkpoints become the
 // (T_c, U_c) the backward reads, by the recursion of the sequential forward
 // over the chunks' (P, L) (identity after a pixel's stop, the partial
@@ -1169,7 +1172,7 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
     float* __restrict__ image, float* __restrict__ T_final, int32_t* __restrict__ n_contrib) {
   constexpr int PX = TileGeom<TW, TH>::PX, NP = TW * TH;
   constexpr int D = PX >= 8 ? 1 : 8 / PX;
-  __shared__ Splat s_splat[kFwdSlots];
+  __shared__ Splat s_splat[kRasterWave];
   for_each_tile(sch, a.n_tiles, [&](int64_t tile, int) {
     const LanePixels<TW, TH> L(a, tile);
     const int lane = threadIdx.x;
@@ -1179,8 +1182,6 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
     const int nc = (int)(ch.offset[tile + 1] - c0);
     float4* ck = ch.ck + (int64_t)c0 * NP;
     const uint16_t* cl = clast + (int64_t)c0 * NP;
-    const PixBox box{(float)(L.tx * TW) + 0.5f, (float)(L.tx * TW + TW - 1) + 0.5f,
-                     (float)(L.ty * TH) + 0.5f, (float)(L.ty * TH + TH - 1) + 0.5f};
     float T[PX], C[PX][3], Ps[PX], Ls[PX][3];
     int last[PX], cs[PX];
 #pragma unroll
@@ -1221,58 +1222,61 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
       }
       if (!__any(any_fix)) return;
       // composite chunk c again, entry by entry with the stop rule, for the
-      // pixels whose transmittance reaches the cut-off inside it
-      uint64_t live[PX];
+      // pixels whose transmittance reaches the cut-off inside it.  Those are
+      // few: each is tested by all lanes at once, a lane per entry, and its
+      // own lane then composites the entries that passed.
       float Tl[PX], Lc[PX][3];
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
-        live[k] = __ballot(fix[k]);
         Tl[k] = 1.0f;
         Lc[k][0] = Lc[k][1] = Lc[k][2] = 0.0f;
       }
       const int lo = c * ch.chunk, hi_pos = min(lo + ch.chunk, len);
       for (int b0 = lo; b0 < hi_pos; b0 += kRasterWave) {
-        const int n = min(kRasterWave, hi_pos - b0);
         Splat s{};
-        bool hit = false;
-        if (lane < n) {
+        s.thr = INFINITY;                  // past the chunk's end: no pass
+        wave_sync();
+        if (b0 + lane < hi_pos) {
           s = load_splat(a.rec, a.ids[start + b0 + lane]);
-          hit = splat_may_hit(s, box.x0, box.x1, box.y0, box.y1);
+          s_splat[lane] = s;
         }
-        const int cnt = fwd_pack(s, hit, b0 + lane + 1, s_splat);
-        int lastc[PX];
+        wave_sync();
 #pragma unroll
-        for (int k = 0; k < PX; ++k) lastc[k] = -1;
-        fwd_for_each(s_splat, cnt, [&](const FwdEntry& e, int i) {
-          float p2[PX];
-          uint64_t pass[PX];
-          if (!fwd_test<PX>(e, L.fx, L.fy, live, p2, pass)) return;
-#pragma unroll
-          for (int k = 0; k < PX; ++k) {
-            const float alpha = fminf(kAlphaMax, e.col.x * splat_gauss(p2[k]));
-            const float Tn = T[k] * (1.0f - alpha);
-            // the pixel stops; this entry is not blended
-            const uint64_t stop = pass[k] & lanes_lt(Tn, kTMin);
-            live[k] &= ~stop;
-            if (lane_in(stop)) cs[k] = c;
-            if (lane_in(pass[k] & ~stop)) {
-              const float w = alpha * T[k];
-              C[k][0] = fmaf(e.col.y, w, C[k][0]);
-              C[k][1] = fmaf(e.col.z, w, C[k][1]);
-              C[k][2] = fmaf(e.col.w, w, C[k][2]);
-              const float wl = alpha * Tl[k];
-              Lc[k][0] = fmaf(e.col.y, wl, Lc[k][0]);
-              Lc[k][1] = fmaf(e.col.z, wl, Lc[k][1]);
-              Lc[k][2] = fmaf(e.col.w, wl, Lc[k][2]);
-              Tl[k] = Tl[k] * (1.0f - alpha);
-              T[k] = Tn;
-              lastc[k] = i;
-            }
+        for (int k = 0; k < PX; ++k) {
+          uint64_t todo = __ballot(fix[k] && cs[k] == nc);
+          uint64_t list = 0;               // the entries that the lane's pixel passes
+          while (todo) {
+            const int p = (int)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            const float qx = lane_f(L.fx, p), qy = lane_f(L.fy[k], p);
+            const float p2 = splat_p2(s, __fsub_rn(qx, s.mx), __fsub_rn(qy, s.my));
+            const uint64_t pass = splat_pass_lanes(s, p2);
+            if (lane == p) list = pass;
           }
-        });
-#pragma unroll
-        for (int k = 0; k < PX; ++k)
-          if (lastc[k] >= 0) last[k] = fwd_pos(s_splat, lastc[k]);
+          while (list) {
+            const int j = (int)__builtin_ctzll(list);
+            list &= list - 1;
+            const Splat& e = s_splat[j];
+            const float p2 = splat_p2(e, __fsub_rn(L.fx, e.mx), __fsub_rn(L.fy[k], e.my));
+            const float alpha = fminf(kAlphaMax, e.o * splat_gauss(p2));
+            const float Tn = T[k] * (1.0f - alpha);
+            if (Tn < kTMin) {              // the pixel stops; this entry is not blended
+              cs[k] = c;
+              break;
+            }
+            const float w = alpha * T[k];
+            C[k][0] = fmaf(e.r, w, C[k][0]);
+            C[k][1] = fmaf(e.g, w, C[k][1]);
+            C[k][2] = fmaf(e.b, w, C[k][2]);
+            const float wl = alpha * Tl[k];
+            Lc[k][0] = fmaf(e.r, wl, Lc[k][0]);
+            Lc[k][1] = fmaf(e.g, wl, Lc[k][1]);
+            Lc[k][2] = fmaf(e.b, wl, Lc[k][2]);
+            Tl[k] = Tl[k] * (1.0f - alpha);
+            T[k] = Tn;
+            last[k] = b0 + j + 1;
+          }
+        }
       }
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
