@@ -186,6 +186,8 @@ __device__ __forceinline__ void tile_forward(const float* __restrict__ rec,
                                              float (*C)[3], int* last, const PixBox& box,
                                              float4* ck = nullptr, int chunk = 0, float bg0 = 0.f,
                                              float bg1 = 0.f, float bg2 = 0.f, int q0 = 0) {
+  // one pixel a lane: the wave's pixels are an 8x8 block, row by row
+  constexpr bool kBlock8 = PX == 1 && TW % 8 == 0 && TH % 8 == 0;
   const int lane = threadIdx.x & (kRasterWave - 1);
   // lanes whose pixel k still composites: inside the image and not stopped
   uint64_t live[PX];
@@ -219,8 +221,22 @@ __device__ __forceinline__ void tile_forward(const float* __restrict__ rec,
     const uint32_t nid = nid2;
     if (b0 + kRasterWave + lane < end) nraw = fetch_splat(rec, nid);
     if (b0 + 2 * kRasterWave + lane < end) nid2 = ids[b0 + 2 * kRasterWave + lane];
+    // the cull's box: the wave's pixels, or of an 8x8 block the box of those
+    // that still composite.  A long list's tail is for a few pixels only (at
+    // 1080p the last wave to end visited 2628 entries, 823 of which blended
+    // somewhere): forward 308 -> 233 us there, 176 -> 158 with 3-band colour.
+    PixBox bx = box;
+    if (kBlock8) {
+      const uint64_t m = live[0];
+      uint32_t c = (uint32_t)(m | (m >> 32));
+      c |= c >> 16;
+      c = (c | (c >> 8)) & 0xff;
+      bx = PixBox{box.x0 + (float)__builtin_ctz(c), box.x0 + (float)(31 - __builtin_clz(c)),
+                  box.y0 + (float)(__builtin_ctzll(m) >> 3),
+                  box.y0 + (float)((63 - __builtin_clzll(m)) >> 3)};
+    }
     Splat s = make_splat(raw);
-    const bool hit = lane < n && splat_may_hit(s, box.x0, box.x1, box.y0, box.y1);
+    const bool hit = lane < n && splat_may_hit(s, bx.x0, bx.x1, bx.y0, bx.y1);
     const int cnt = fwd_pack(s, hit, (int)(b0 - start) + lane + 1, s_splat);
     int lastc[PX];            // packed index of the lane's last blend in the batch
 #pragma unroll
