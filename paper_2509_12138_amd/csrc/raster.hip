@@ -26,12 +26,19 @@ constexpr int kRasterWave = 64;
 // A forward wave's LDS batch: 64 entries and the two that its loop reads ahead.
 constexpr int kFwdSlots = kRasterWave + 2;
 
-// XCD-aware tile order: work-group i runs on XCD (i mod 8); give each XCD a
-// contiguous range of tiles.
-__device__ __forceinline__ int64_t tile_of_block(int64_t i, int64_t n_tiles) {
-  const int64_t chunk = (n_tiles + 7) / 8;
-  return (i & 7) * chunk + (i >> 3);
+// XCD-aware tile order: work-group i runs on XCD (i mod 8), and the XCDs take
+// groups of kXcdTiles consecutive tiles in turn: neighbours that share
+// Gaussians share an L2, and an image's middle rows, whose lists are the
+// longest, do not all fall to two XCDs.
+// An eighth of the image to each XCD instead: 1M Gaussians at 1920x1080, whole
+// forward 389 us, groups of 4, 8 or 32 tiles 223-227 us.
+constexpr int64_t kXcdTiles = 8;
+
+__device__ __forceinline__ int64_t tile_of_block(int64_t i) {
+  const int64_t j = i >> 3;
+  return (j / kXcdTiles * 8 + (i & 7)) * kXcdTiles + j % kXcdTiles;
 }
+static int64_t xcd_blocks(int64_t n_tiles) { return ceil_div(n_tiles, 8 * kXcdTiles) * 8 * kXcdTiles; }
 
 // A projected record as three 16-byte words (mean, conic, opacity, rgb).
 struct RawSplat {
@@ -394,7 +401,7 @@ __device__ __forceinline__ void for_each_tile(const TileSched& sch, int64_t n_ti
     if ((int64_t)i < n_tiles) body((int64_t)sch.order[i], (int)(blockIdx.x % NB));
   } else {
     // consecutive work-groups of one XCD (ids 8 apart) share a tile
-    const int64_t tile = tile_of_block((blockIdx.x >> 3) / NB * 8 + (blockIdx.x & 7), n_tiles);
+    const int64_t tile = tile_of_block((blockIdx.x >> 3) / NB * 8 + (blockIdx.x & 7));
     if (tile < n_tiles) body(tile, (int)((blockIdx.x >> 3) % NB));
   }
 }
@@ -1499,7 +1506,7 @@ static Launch make_launch(const RasterDev& a, const gs_raster_plan* plan) {
   } else if (L.sch.order) {
     L.blocks = (unsigned)std::max<int64_t>(a.n_tiles, 1);
   } else {
-    L.blocks = (unsigned)(8 * ((a.n_tiles + 7) / 8));
+    L.blocks = (unsigned)xcd_blocks(a.n_tiles);
   }
   return L;
 }
