@@ -384,25 +384,28 @@ struct ChunkDev {
   float4* ck;
 };
 
-// Calls body(tile, b) for the work-group's tiles; NB work-groups, b = 0 ..
-// NB-1, share a tile (adjacent launches, or adjacent queue items).
-template <int NB = 1, typename F>
-__device__ __forceinline__ void for_each_tile(const TileSched& sch, int64_t n_tiles, F&& body) {
+// Calls body(tile, b) for the work-group's tiles; 1 << lg work-groups, b = 0 ..
+// (1 << lg) - 1, share a tile (adjacent launches, or adjacent queue items).
+template <typename F>
+__device__ __forceinline__ void for_each_tile(const TileSched& sch, int64_t n_tiles, int lg,
+                                              F&& body) {
+  const uint32_t part = (1u << lg) - 1;
   if (sch.queue) {
     for (;;) {
       uint32_t item = 0;
       if (threadIdx.x == 0) item = atomicAdd(sch.queue, 1u);
       item = __builtin_amdgcn_readfirstlane(item);
-      if ((int64_t)item >= n_tiles * NB) break;
-      body((int64_t)(sch.order ? sch.order[item / NB] : item / NB), (int)(item % NB));
+      if ((int64_t)item >= n_tiles << lg) break;
+      body((int64_t)(sch.order ? sch.order[item >> lg] : item >> lg), (int)(item & part));
     }
   } else if (sch.order) {
-    const uint32_t i = blockIdx.x / NB;
-    if ((int64_t)i < n_tiles) body((int64_t)sch.order[i], (int)(blockIdx.x % NB));
+    const uint32_t i = blockIdx.x >> lg;
+    if ((int64_t)i < n_tiles) body((int64_t)sch.order[i], (int)(blockIdx.x & part));
   } else {
     // consecutive work-groups of one XCD (ids 8 apart) share a tile
-    const int64_t tile = tile_of_block((blockIdx.x >> 3) / NB * 8 + (blockIdx.x & 7));
-    if (tile < n_tiles) body(tile, (int)((blockIdx.x >> 3) % NB));
+    const uint32_t j = blockIdx.x >> 3;
+    const int64_t tile = tile_of_block((int64_t)(j >> lg) * 8 + (blockIdx.x & 7));
+    if (tile < n_tiles) body(tile, (int)(j & part));
   }
 }
 
@@ -491,7 +494,7 @@ void k_raster_fwd(RasterDev a, TileSched sch,
   __shared__ Splat s_splat[kFwdSlots * NW];
   // wave-uniform base (scalar), so per-entry LDS addresses stay scalar too
   Splat* mine = s_splat + __builtin_amdgcn_readfirstlane(threadIdx.x / kRasterWave) * kFwdSlots;
-  for_each_tile(sch, a.n_tiles, [&](int64_t tile, int) {
+  for_each_tile(sch, a.n_tiles, 0, [&](int64_t tile, int) {
     fwd_tile<TW, TH, NW>(a, ch, tile, mine, image, T_final, n_contrib);
   });
 }
@@ -633,7 +636,8 @@ struct BwdPixels {
 // start+hi-1, last first) for the wave's blocks, the first of which starts at
 // pixel (x0, y0).  With a.dup_grads (the wave owns the whole tile) an entry's
 // components go to its emission slot, else they are added atomically to
-// d_rec.
+// d_rec.  mine: the entries (by slot of their batch) whose sums this wave
+// takes; the others only move its pixels' transmittance on.
 // The walk is bound by vector instruction issue.  A footprint reaches 1.3 of
 // a 16x16 tile's four blocks on average (28 of 256 pixels blend at 1080p), so
 // staging tests every block's box and a visit evaluates only the blocks that
@@ -642,7 +646,8 @@ struct BwdPixels {
 template <int BX, int NK>
 __device__ __forceinline__ void reverse_pass(const RasterDev& a, uint32_t start, int lo, int hi,
                                              int x0, int y0, BwdPixels<BX, NK>& p, Splat* s_splat,
-                                             float* __restrict__ d_rec) {
+                                             float* __restrict__ d_rec, uint2* s_meta = nullptr,
+                                             uint64_t mine = ~0ull) {
   const int lane = threadIdx.x & (kRasterWave - 1);
   const bool det = a.dup_grads != nullptr;
   float* const gbase = det ? a.dup_grads : d_rec;
@@ -654,6 +659,7 @@ __device__ __forceinline__ void reverse_pass(const RasterDev& a, uint32_t start,
     wave_sync();
     uint32_t reach = 0;               // blocks the lane's entry may reach
     uint32_t eid = 0;                 // its pair, or gradient slot
+    Splat staged{};
     if (lane < n) {
       const uint32_t id = a.ids[start + bot + lane];
       eid = det ? a.emit[start + bot + lane] : id;
@@ -665,23 +671,48 @@ __device__ __forceinline__ void reverse_pass(const RasterDev& a, uint32_t start,
       }
       s.pad1 = __builtin_amdgcn_rcpf(s.o);
       s.pad2 = 0.5f * s.B;
-      s_splat[lane] = s;
+      if (NK == 1) staged = s;
+      else s_splat[lane] = s;
       // an entry that cannot reach the tile gets zero gradients
-      if (det && !reach && (int64_t)eid < a.dup_cap) {
+      if (det && !reach && (mine >> lane & 1) && (int64_t)eid < a.dup_cap) {
         float* g = gbase + (int64_t)eid * GS_DREC_STRIDE;
 #pragma unroll
         for (int c = 0; c < GS_DREC_STRIDE; ++c) g[c] = 0.0f;
       }
     }
-    uint64_t todo = __ballot(reach != 0);
-    wave_sync();
-    while (todo) {
-      const int j = 63 - (int)__builtin_clzll(todo);
-      todo &= ~(1ull << j);
-      const uint32_t blocks = __builtin_amdgcn_readlane(reach, j);
-      const uint32_t entry = __builtin_amdgcn_readlane(eid, j);
-      const Splat sp = s_splat[j];
-      const int pos = bot + j + 1;
+    // moves pixel k's state in front of an entry that it blends
+    struct Step {
+      float aa, alpha, w, dLda;
+    };
+    auto step = [&](const Splat& sp, int k, float p2) {
+      Step b;
+      b.aa = sp.o * splat_gauss(p2);
+      b.alpha = fminf(kAlphaMax, b.aa);
+      const float inv = __builtin_amdgcn_rcpf(1.0f - b.alpha);
+      const float Tb = p.T[k] * inv;                 // transmittance in front of it
+      b.w = b.alpha * Tb;
+      const float dIc = fmaf(p.dI[k][2], sp.b, fmaf(p.dI[k][1], sp.g, p.dI[k][0] * sp.r));
+      b.dLda = fmaf(Tb, dIc, -inv * p.dIacc[k]);
+      p.dIacc[k] = fmaf(b.w, dIc, p.dIacc[k]);
+      p.T[k] = Tb;
+      return b;
+    };
+    // an entry whose sums another wave takes
+    auto pass_by = [&](const Splat& sp, uint32_t blocks, int pos) {
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        if (NK > 1 && !(blocks & (1u << k))) continue;
+        const float p2 = splat_p2(sp, __fsub_rn(p.fx + (float)(8 * (k % BX)), sp.mx),
+                                  __fsub_rn(p.fy + (float)(8 * (k / BX)), sp.my));
+        if (lane_in(splat_pass_lanes(sp, p2) & lanes_le(pos, p.last[k]))) step(sp, k, p2);
+      }
+    };
+    // one entry, its blocks, pair (or gradient slot) and list position
+    auto visit = [&](const Splat& sp, uint32_t blocks, uint32_t entry, int pos, bool take) {
+      if (!take) {
+        pass_by(sp, blocks, pos);
+        return;
+      }
       // sums over the lane's pixels of G = dL/d(exponent) times 1, dx, dy,
       // dx^2, dx dy, dy^2 and of the blend weight times dI
       float sG = 0.f, sGx = 0.f, sGy = 0.f, sGxx = 0.f, sGxy = 0.f, sGyy = 0.f;
@@ -696,21 +727,12 @@ __device__ __forceinline__ void reverse_pass(const RasterDev& a, uint32_t start,
         const uint64_t pass = splat_pass_lanes(sp, p2) & lanes_le(pos, p.last[k]);
         hit |= pass;
         if (lane_in(pass)) {
-          const float gss = splat_gauss(p2);
-          const float aa = sp.o * gss;
-          const float alpha = fminf(kAlphaMax, aa);
-          const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
-          const float Tb = p.T[k] * inv;                 // transmittance in front of it
-          const float w = alpha * Tb;
-          const float dIc = fmaf(p.dI[k][2], sp.b, fmaf(p.dI[k][1], sp.g, p.dI[k][0] * sp.r));
-          const float dLda = fmaf(Tb, dIc, -inv * p.dIacc[k]);
-          p.dIacc[k] = fmaf(w, dIc, p.dIacc[k]);
-          p.T[k] = Tb;
-          sr = fmaf(p.dI[k][0], w, sr);
-          sg = fmaf(p.dI[k][1], w, sg);
-          sb = fmaf(p.dI[k][2], w, sb);
+          const Step b = step(sp, k, p2);
+          sr = fmaf(p.dI[k][0], b.w, sr);
+          sg = fmaf(p.dI[k][1], b.w, sg);
+          sb = fmaf(p.dI[k][2], b.w, sb);
           // (the derivative through a clamped alpha is zero)
-          const float G = aa < kAlphaMax ? dLda * alpha : 0.0f;
+          const float G = b.aa < kAlphaMax ? b.dLda * b.alpha : 0.0f;
           const float Gx = G * dx, Gy = G * dy;
           sG += G;
           sGx += Gx;
@@ -723,7 +745,7 @@ __device__ __forceinline__ void reverse_pass(const RasterDev& a, uint32_t start,
       if (!hit) {
         if (det && lane < GS_DREC_STRIDE && (int64_t)entry < a.dup_cap)
           gbase[(int64_t)entry * GS_DREC_STRIDE + lane] = 0.0f;
-        continue;
+        return;
       }
       // (constant factors applied per component after the reduction)
       const float comp[9] = {fmaf(sp.A, sGx, sp.pad2 * sGy),    // d mx / -2 ln2
@@ -738,6 +760,43 @@ __device__ __forceinline__ void reverse_pass(const RasterDev& a, uint32_t start,
         float* dst = gbase + (int64_t)entry * GS_DREC_STRIDE + red.slot;
         if (!det) atomicAdd(dst, red.scale * tot);
         else if ((int64_t)entry < a.dup_cap) *dst = red.scale * tot;
+      }
+    };
+    const uint64_t hits = __ballot(reach != 0);
+    if constexpr (NK == 1) {
+      // packed last entry first, the next one read while one is visited
+      const int cnt = __builtin_popcountll(hits);
+      if (reach) {
+        const int i = cnt - 1 - (int)__builtin_amdgcn_mbcnt_hi(
+                                    (uint32_t)(hits >> 32),
+                                    __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+        s_splat[i] = staged;
+        s_meta[i] = make_uint2(eid, (uint32_t)(bot + lane + 1));
+      }
+      wave_sync();
+      if (cnt) {
+        Splat ea = s_splat[0], eb;
+        uint2 ma = s_meta[0], mb;
+        for (int i = 0;; i += 2) {
+          eb = s_splat[i + 1];
+          mb = s_meta[i + 1];
+          visit(ea, 1u, __builtin_amdgcn_readfirstlane(ma.x), (int)ma.y, mine >> i & 1);
+          if (i + 1 >= cnt) break;
+          ea = s_splat[i + 2];
+          ma = s_meta[i + 2];
+          visit(eb, 1u, __builtin_amdgcn_readfirstlane(mb.x), (int)mb.y, mine >> (i + 1) & 1);
+          if (i + 2 >= cnt) break;
+        }
+      }
+    } else {
+      uint64_t todo = hits;
+      wave_sync();
+      while (todo) {
+        const int j = 63 - (int)__builtin_clzll(todo);
+        todo &= ~(1ull << j);
+        const Splat sp = s_splat[j];
+        visit(sp, __builtin_amdgcn_readlane(reach, j), __builtin_amdgcn_readlane(eid, j),
+              bot + j + 1, mine >> j & 1);
       }
     }
   }
@@ -754,9 +813,11 @@ struct TilePos {
   }
 };
 
-// Whole-list backward of NK blocks of a tile from its block b.
+// Whole-list backward of NK blocks of a tile from its block b; the wave takes
+// the sums of the entries in `mine`.
 template <int TW, int TH, int NK, bool RECOMPUTE>
-__device__ __forceinline__ void bwd_blocks(const RasterDev& a, int64_t tile, int b, Splat* s_splat,
+__device__ __forceinline__ void bwd_blocks(const RasterDev& a, int64_t tile, int b, uint64_t mine,
+                                           Splat* s_splat, uint2* s_meta,
                                            const float* __restrict__ T_final,
                                            const int32_t* __restrict__ n_contrib,
                                            const float* __restrict__ d_image,
@@ -790,25 +851,45 @@ __device__ __forceinline__ void bwd_blocks(const RasterDev& a, int64_t tile, int
   const int lmax = min(p.load_gradient(d_image + (int64_t)tp.slot * 3 * p.HW), (int)(end - start));
 #pragma unroll
   for (int k = 0; k < NK; ++k) p.final_state(k, T_fin[k], a);
-  reverse_pass<BX, NK>(a, start, 0, lmax, x0, y0, p, s_splat, d_rec);
+  reverse_pass<BX, NK>(a, start, 0, lmax, x0, y0, p, s_splat, d_rec, s_meta, mine);
   if (a.dup_grads) zero_dup_slots(a, start, lmax, (int)(end - start));
 }
+
+// Waves are added up to 32 a CU, eight a SIMD, as many as can be resident: with
+// a limit of 16, 512x512 images (1 against 2 waves a block) took 136 against
+// 125 us for 20K Gaussians, 353 / 307 for 100K and 828 / 781 for 400K, 400x300
+// (2 / 4) 337 / 283 for 100K.
+constexpr int kBwdShareLgMax = 3;
+constexpr int64_t kBwdShareWavesPerCu = 32;
 
 // Whole-list backward.  Without chunks a tile's list is one serial walk, and
 // the call takes as long as its longest lists; in the atomic form every block
 // of a tile therefore has its own wave (NK = 1; the NB waves of a tile are
 // adjacent launches).  The deterministic form stores an entry's sums over the
 // whole tile, so one wave takes the tile (NK = NB).
+// Where that leaves the chip mostly idle, 1 << lg_share waves walk the same
+// pixels, every wave all entries but each the sums of every (1 << lg_share)-th
+// only: those, their reduction and the atomics are two thirds of a visit.
+// 128x128 with 64 tiles (8 waves a block): 131 -> 76 us; 333x251 with 336
+// tiles (4): 174 -> 130.
 template <int TW, int TH, int NK, bool RECOMPUTE>
 __global__ __launch_bounds__(kRasterWave) void k_raster_bwd(RasterDev a, TileSched sch,
+                                                            int lg_share,
                                                             const float* __restrict__ T_final,
                                                             const int32_t* __restrict__ n_contrib,
                                                             const float* __restrict__ d_image,
                                                             float* __restrict__ d_rec) {
   constexpr int NB = TW * TH / 64 / NK;
-  __shared__ Splat s_splat[RECOMPUTE ? kFwdSlots : kRasterWave];
-  for_each_tile<NB>(sch, a.n_tiles, [&](int64_t tile, int b) {
-    bwd_blocks<TW, TH, NK, RECOMPUTE>(a, tile, b, s_splat, T_final, n_contrib, d_image, d_rec);
+  __shared__ Splat s_splat[kFwdSlots];
+  __shared__ uint2 s_meta[kFwdSlots];
+  constexpr int kLgNB = NB == 1 ? 0 : (NB == 2 ? 1 : (NB == 4 ? 2 : 3));
+  static_assert(1 << kLgNB == NB, "blocks of a tile");
+  for_each_tile(sch, a.n_tiles, kLgNB + lg_share, [&](int64_t tile, int b) {
+    // bits q, q + Q, q + 2 Q, ... of Q = 1 << lg_share waves
+    const int Q = 1 << lg_share;
+    const uint64_t every = Q == 1 ? ~0ull : ~0ull / ((1ull << Q) - 1);
+    bwd_blocks<TW, TH, NK, RECOMPUTE>(a, tile, b >> lg_share, every << (b & (Q - 1)), s_splat,
+                                      s_meta, T_final, n_contrib, d_image, d_rec);
   });
 }
 
@@ -825,7 +906,8 @@ void k_raster_bwd_chunked(
     const int32_t* __restrict__ n_contrib, const float* __restrict__ d_image,
     float* __restrict__ d_rec) {
   constexpr int BX = TW / 8, NK = TW * TH / 64;
-  __shared__ Splat s_splat[kRasterWave];
+  __shared__ Splat s_splat[NK == 1 ? kFwdSlots : kRasterWave];
+  __shared__ uint2 s_meta[NK == 1 ? kFwdSlots : 1];
   const uint32_t item = blockIdx.x;
   if (item >= ch.offset[a.n_tiles]) return;
   const int64_t tile = ch.items[item];
@@ -858,7 +940,7 @@ void k_raster_bwd_chunked(
       p.dIacc[k] = s.x * (p.dI[k][0] * s.y + p.dI[k][1] * s.z + p.dI[k][2] * s.w);
     }
   }
-  reverse_pass<BX, NK>(a, start, lo, hi, x0, y0, p, s_splat, d_rec);
+  reverse_pass<BX, NK>(a, start, lo, hi, x0, y0, p, s_splat, d_rec, s_meta);
   if (a.dup_grads) zero_dup_slots(a, start, hi, hi_pos);
 }
 
@@ -1196,7 +1278,7 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
   constexpr int PX = TileGeom<TW, TH>::PX, NP = TW * TH;
   constexpr int D = PX >= 8 ? 1 : 8 / PX;
   __shared__ Splat s_splat[kRasterWave];
-  for_each_tile(sch, a.n_tiles, [&](int64_t tile, int) {
+  for_each_tile(sch, a.n_tiles, 0, [&](int64_t tile, int) {
     const LanePixels<TW, TH> L(a, tile);
     const int lane = threadIdx.x;
     const uint32_t start = a.ranges[2 * tile], end = a.ranges[2 * tile + 1];
@@ -1570,10 +1652,18 @@ static void launch_bwd(const RasterDev& a, const Launch& L, const float* T_final
     // whole lists: a wave per 8x8 block, or per tile where gradients are stored
     constexpr int NB = TW * TH / 64;
     const bool rec = mode == GS_BWD_RECOMPUTE;
-    const dim3 blocks(a.dup_grads || L.sch.queue ? L.blocks : L.blocks * NB);
+    // (a queue's grid is persistent and takes the waves of a tile as items)
+    int64_t waves = a.dup_grads || L.sch.queue ? L.blocks : (int64_t)L.blocks * NB;
+    int lg_share = 0;
+    if (!L.sch.queue)
+      while (lg_share < kBwdShareLgMax && 2 * waves <= kBwdShareWavesPerCu * device_cu_count()) {
+        ++lg_share;
+        waves *= 2;
+      }
+    const dim3 blocks((unsigned)waves);
 #define GS_BWD_LAUNCH(NK, REC)                                                                \
   hipLaunchKernelGGL((k_raster_bwd<TW, TH, NK, REC>), blocks, dim3(kRasterWave), 0, s, a,     \
-                     L.sch, T_final, n_contrib, d_image, d_rec)
+                     L.sch, lg_share, T_final, n_contrib, d_image, d_rec)
     if (a.dup_grads && rec) GS_BWD_LAUNCH(NB, true);
     else if (a.dup_grads) GS_BWD_LAUNCH(NB, false);
     else if (rec) GS_BWD_LAUNCH(1, true);
