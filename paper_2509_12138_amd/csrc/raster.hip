@@ -990,6 +990,120 @@ __device__ __forceinline__ int row_slot9(int l) {
   return b0 ? L3[1] : L3[0];
 }
 
+// ---- pairs of an entry and a pixel (8x8 tiles)
+//
+// A lane owns pixel p = lane: quadrant p / 16 (2 x 2 of them), in it column
+// p % 4 and row p % 16 / 4.
+__device__ __forceinline__ int quad_x(int p) { return ((p >> 2) & 4) | (p & 3); }
+__device__ __forceinline__ int quad_y(int p) { return ((p >> 3) & 4) | ((p >> 2) & 3); }
+
+// The pixels (bit p) of the 8x8 block with pixel-centre origin (x0, y0) that
+// may pass the alpha test: of every row the interval in which A dx^2 + B dx dy
+// + C dy^2 >= thr, widened by splat_may_hit's margin in the exponent, which
+// covers the rounding of both sides, and by 1e-3 pixels.
+__device__ __forceinline__ void splat_pixels(const Splat& s, float x0, float y0, uint32_t& lo,
+                                             uint32_t& hi) {
+  lo = hi = 0u;
+  if (!(s.A < 0.0f)) {
+    lo = hi = ~0u;
+    return;
+  }
+  const float dx0 = x0 - s.mx, dy0 = y0 - s.my;
+  const float X = fmaxf(fabsf(dx0), fabsf(dx0 + 7.0f)), Y = fmaxf(fabsf(dy0), fabsf(dy0 + 7.0f));
+  const float M = -s.A * X * X + fabsf(s.B) * X * Y - s.C * Y * Y;
+  const float thr = s.thr - (0.02f + 4e-6f * M);
+  const float K1 = s.B * s.B - 4.0f * s.A * s.C, K2 = 4.0f * s.A * thr;
+  const float iA = -0.5f * __builtin_amdgcn_rcpf(s.A);          // 1 / (-2A) > 0
+  const float cB = s.B * iA;                                    // interval centre per dy
+#pragma unroll
+  for (int y = 0; y < 8; ++y) {
+    const float dy = dy0 + (float)y;
+    const float t = fmaf(K1 * dy, dy, K2);                      // discriminant
+    const float h = __builtin_amdgcn_sqrtf(t) * iA + 1e-3f;     // NaN below zero
+    const float c = cB * dy - dx0;
+    const int i0 = (int)ceilf(__builtin_amdgcn_fmed3f(c - h, 0.0f, 8.0f));
+    const int i1 = (int)floorf(__builtin_amdgcn_fmed3f(c + h, -1.0f, 7.0f));
+    const uint32_t m = t >= 0.0f && i1 >= i0 ? (2u << i1) - (1u << i0) : 0u;
+    const uint32_t w = ((m | (m << 12)) & 0x000f000fu) << (4 * (y & 3));
+    if (y < 4) lo |= w;
+    else hi |= w;
+  }
+}
+
+// Transposes the 64x64 bit matrix whose row l is lane l's (hi, lo).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+}
+__device__ __forceinline__ uint32_t transpose32_step(uint32_t x, uint32_t other, uint32_t keep,
+                                                     int rot) {
+  // keep: the bits that stay; the partner's come from `rot` bits to the right
+  const uint32_t t = __builtin_amdgcn_alignbit(other, other, (uint32_t)rot);
+  return (x & keep) | (t & ~keep);
+}
+__device__ __forceinline__ void transpose64(uint32_t& lo, uint32_t& hi) {
+  const int l = threadIdx.x & 63;
+  const auto s32 = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+  uint32_t w[2] = {s32[0], s32[1]};
+  const bool b4 = l & 16, b3 = l & 8, b2 = l & 4, b1 = l & 2, b0 = l & 1;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    uint32_t x = w[i];
+    const auto s16 = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = transpose32_step(x, b4 ? s16[0] : s16[1], b4 ? 0xffff0000u : 0x0000ffffu, 16);
+    x = transpose32_step(x, dpp_u<kDppRowRor8>(x), b3 ? 0xff00ff00u : 0x00ff00ffu, b3 ? 8 : 24);
+    x = transpose32_step(x, dpp_u<kDppQuadReverse>(dpp_u<kDppRowHalfMirror>(x)),
+                         b2 ? 0xf0f0f0f0u : 0x0f0f0f0fu, b2 ? 4 : 28);
+    x = transpose32_step(x, dpp_u<kDppQuadSwap2>(x), b1 ? 0xccccccccu : 0x33333333u, b1 ? 2 : 30);
+    x = transpose32_step(x, dpp_u<kDppQuadSwap1>(x), b0 ? 0xaaaaaaaau : 0x55555555u, b0 ? 1 : 31);
+    w[i] = x;
+  }
+  lo = w[0];
+  hi = w[1];
+}
+
+// Inclusive scan over runs of lanes that start at lane `first`, by op.
+struct RunScan {
+  bool c1, c2, c4, c8, c15, c31;
+  __device__ __forceinline__ explicit RunScan(int first) {
+    const int l = threadIdx.x & 63;
+    const int a = min(l - first, l & 15);
+    c1 = a >= 1;
+    c2 = a >= 2;
+    c4 = a >= 4;
+    c8 = a >= 8;
+    c15 = (l & 16) && first < (l & 48);
+    c31 = l >= 32 && first < 32;
+  }
+  template <typename Op>
+  __device__ __forceinline__ float operator()(float x, Op op) const {
+    float y = dpp_f<kDppRowShr1>(x);
+    x = c1 ? op(x, y) : x;
+    y = dpp_f<kDppRowShr1 + 1>(x);
+    x = c2 ? op(x, y) : x;
+    y = dpp_f<kDppRowShr1 + 3>(x);
+    x = c4 ? op(x, y) : x;
+    y = dpp_f<kDppRowShr1 + 7>(x);
+    x = c8 ? op(x, y) : x;
+    y = dpp_f<kDppRowBcast15, 0xa>(x);
+    x = c15 ? op(x, y) : x;
+    y = dpp_f<kDppRowBcast31, 0xc>(x);
+    return c31 ? op(x, y) : x;
+  }
+};
+
+constexpr int kPairCap = 512;        // pairs of a batch that are taken pair by pair
+
+struct PairLds {
+  uint4 pix[kRasterWave];            // entries of the pixel (64 bits), its first pair, count | last
+  float2 state[kRasterWave];         // transmittance and dI . colour behind the walk's position
+  float4 dI[kRasterWave];
+  float2 xy[kRasterWave];            // pixel centre
+  uint16_t pair[kPairCap];           // entry | pixel << 6
+  float2 gw[kPairCap];               // G = dL/d(exponent) and blend weight of each pair;
+                                     // then the entries' sums
+};
+
 // Chunked backward on quadrant lane groups: row q of the wave (lanes 16q ..
 // 16q+15) owns the (TW/2) x (TH/2) quadrant (q mod 2, q / 2) of the tile,
 // PXQ pixels of one column per lane (column r mod QW, rows r / QW + k RS),
@@ -1001,7 +1115,8 @@ __device__ __forceinline__ int row_slot9(int l) {
 // 64.  Per pixel the arithmetic and the skip and stop decisions are those of
 // reverse_pass.  Atomic gradient sums only.
 template <int TW, int TH>
-__global__ __launch_bounds__(kRasterWave) void k_raster_bwd_chunked_q(
+__global__ __launch_bounds__(kRasterWave)
+__attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
     RasterDev a, ChunkDev ch, const float* __restrict__ T_final,
     const int32_t* __restrict__ n_contrib, const float* __restrict__ d_image,
     float* __restrict__ d_rec) {
@@ -1009,6 +1124,8 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_bwd_chunked_q(
   static_assert(QW * QH % 16 == 0 && 16 % QW == 0, "quadrant shape");
   __shared__ Splat s_splat[kRasterWave];
   __shared__ uint32_t s_id[kRasterWave];
+  static_assert(TW == 8 && TH == 8, "pairs");
+  __shared__ PairLds s_p;
   const uint32_t item = blockIdx.x;
   if (item >= ch.offset[a.n_tiles]) return;
   const int64_t tile = ch.items[item];
@@ -1065,33 +1182,143 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_bwd_chunked_q(
   const float sc[9] = {-kLn2, -kLn2, -0.5f, -1.0f, -0.5f, 1.0f, 1.0f, 1.0f, 1.0f};
   const float rscale = rslot >= 0 ? sc[rslot] : 0.0f;
   const float qx0 = (float)(tx * TW) + 0.5f, qy0 = (float)(ty * TH) + 0.5f;
+  s_p.dI[lane] = make_float4(dI[0][0], dI[0][1], dI[0][2], 0.0f);
+  s_p.xy[lane] = make_float2(fx, fy[0]);
   for (int top = hi; top > lo; top -= kRasterWave) {
     const int bot = max(lo, top - kRasterWave);
     const int n = top - bot;
     wave_sync();
-    uint32_t qm = 0;
+    // the entry's pixels, among those that blend in this batch
+    const uint64_t active = __ballot(last[0] > bot);
+    uint32_t id = 0, plo = 0, phi = 0;
+    Splat sp{};
     if (lane < n) {
-      const uint32_t id = a.ids[start + bot + lane];
+      id = a.ids[start + bot + lane];
       s_id[lane] = id;
-      const Splat sp = load_splat(a.rec, id);
+      sp = load_splat(a.rec, id);
       s_splat[lane] = sp;
-      // which quadrants' pixel-centre boxes the entry may reach
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float x0 = qx0 + (float)((g & 1) * QW), y0 = qy0 + (float)((g >> 1) * QH);
-        if (splat_may_hit(sp, x0, x0 + (float)(QW - 1), y0, y0 + (float)(QH - 1)))
-          qm |= 1u << g;
-      }
+      splat_pixels(sp, qx0, qy0, plo, phi);
+      plo &= (uint32_t)active;
+      phi &= (uint32_t)(active >> 32);
     }
+    uint32_t elo = plo, ehi = phi;           // the pixel's entries
+    transpose64(elo, ehi);
+    const int cnt = __builtin_popcount(elo) + __builtin_popcount(ehi);
+    int upto = cnt;                          // inclusive sum over the pixels
+#pragma unroll
+    for (int d = 1; d < kRasterWave; d <<= 1) {
+      const int o = __shfl_up(upto, d, kRasterWave);
+      if (lane >= d) upto += o;
+    }
+    const int total = __builtin_amdgcn_readlane(upto, kRasterWave - 1);
+    if (total == 0) continue;
+    if (total <= kPairCap) {
+      const int lrel = min(max(last[0] - bot, 0), kRasterWave);
+      s_p.pix[lane] = make_uint4(elo, ehi, (uint32_t)(upto - cnt), (uint32_t)(cnt << 16 | lrel));
+      s_p.state[lane] = make_float2(T[0], dIacc[0]);
+      wave_sync();
+      // the pairs by pixel, last entry first
+      const uint64_t above = lane == 63 ? 0ull : ~0ull << (lane + 1);
+      const uint32_t alo = (uint32_t)above, ahi = (uint32_t)(above >> 32);
+      auto place = [&](const uint4& px_) {
+        return (int)px_.z + __builtin_popcount(px_.x & alo) + __builtin_popcount(px_.y & ahi);
+      };
+      for (uint64_t m = (uint64_t)phi << 32 | plo; m; m &= m - 1) {
+        const int p = (int)__builtin_ctzll(m);
+        s_p.pair[place(s_p.pix[p])] = (uint16_t)(lane | p << 6);
+      }
+      wave_sync();
+      for (int i0 = 0; i0 < total; i0 += kRasterWave) {
+        const int i = min(i0 + lane, total - 1);
+        const bool valid = i0 + lane < total;
+        const uint32_t code = s_p.pair[i];
+        const int e = (int)(code & 63), p = (int)(code >> 6);
+        const Splat& se = s_splat[e];
+        const uint4 pix = s_p.pix[p];
+        const float2 st = s_p.state[p], xy = s_p.xy[p];
+        const float4 di = s_p.dI[p];
+        const float p2 = splat_p2(se, __fsub_rn(xy.x, se.mx), __fsub_rn(xy.y, se.my));
+        const bool pass = valid && e < (int)(pix.w & 0xffff) && splat_pass(se, p2);
+        const float aa = pass ? se.o * splat_gauss(p2) : 0.0f;
+        const float alpha = fminf(kAlphaMax, aa);
+        const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
+        const RunScan scan(max((int)pix.z - i0, 0));
+        const float Tb = st.x * scan(inv, [](float u, float v) { return u * v; });
+        const float w = alpha * Tb;
+        const float dIc = fmaf(di.z, se.b, fmaf(di.y, se.g, di.x * se.r));
+        const float wd = w * dIc;
+        const float sum = scan(wd, [](float u, float v) { return u + v; });
+        const float dLda = fmaf(Tb, dIc, -inv * (st.y + (sum - wd)));
+        if (valid) {
+          s_p.gw[i] = make_float2(aa < kAlphaMax ? dLda * alpha : 0.0f, w);
+          // the last pair of the pixel, or of this round
+          if (lane == kRasterWave - 1 || i + 1 == (int)pix.z + (int)(pix.w >> 16))
+            s_p.state[p] = make_float2(Tb, st.y + sum);
+        }
+        wave_sync();
+      }
+      // sums over an entry's pixels
+      float sG = 0.f, sGx = 0.f, sGy = 0.f, sGxx = 0.f, sGxy = 0.f, sGyy = 0.f;
+      float sr = 0.f, sg = 0.f, sb = 0.f, sw = 0.f;
+      for (uint64_t m = (uint64_t)phi << 32 | plo; m; m &= m - 1) {
+        const int p = (int)__builtin_ctzll(m);
+        const float2 gw = s_p.gw[place(s_p.pix[p])], xy = s_p.xy[p];
+        const float4 di = s_p.dI[p];
+        const float dx = __fsub_rn(xy.x, sp.mx), dy = __fsub_rn(xy.y, sp.my);
+        const float Gx = gw.x * dx, Gy = gw.x * dy;
+        sG += gw.x;
+        sGx += Gx;
+        sGy += Gy;
+        sGxx = fmaf(Gx, dx, sGxx);
+        sGxy = fmaf(Gx, dy, sGxy);
+        sGyy = fmaf(Gy, dy, sGyy);
+        sr = fmaf(di.x, gw.y, sr);
+        sg = fmaf(di.y, gw.y, sg);
+        sb = fmaf(di.z, gw.y, sb);
+        sw += gw.y;
+      }
+      wave_sync();
+      // through LDS, so that the 9 atomics of an entry are side by side; an
+      // entry that blended nowhere adds nothing
+      float* out = reinterpret_cast<float*>(s_p.gw);
+      const float hB = 0.5f * sp.B;
+      const float comp[9] = {-2.0f * kLn2 * fmaf(sp.A, sGx, hB * sGy),
+                             -2.0f * kLn2 * fmaf(sp.C, sGy, hB * sGx),
+                             -0.5f * sGxx,
+                             -sGxy,
+                             -0.5f * sGyy,
+                             sG * __builtin_amdgcn_rcpf(sp.o),
+                             sr,
+                             sg,
+                             sb};
+#pragma unroll
+      for (int k = 0; k < 9; ++k) out[lane * 9 + k] = comp[k];
+      const uint64_t adds = __ballot(sw != 0.0f);
+      wave_sync();
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        const int f = k * kRasterWave + lane, e = f / 9;
+        if (adds >> e & 1) atomicAdd(d_rec + (int64_t)s_id[e] * GS_DREC_STRIDE + (f - 9 * e), out[f]);
+      }
+      const float2 st = s_p.state[lane];
+      T[0] = st.x;
+      dIacc[0] = st.y;
+      continue;
+    }
+    // many pairs: quadrant by quadrant
+    uint32_t qm = 0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if ((g < 2 ? plo : phi) >> (16 * (g & 1)) & 0xffffu) qm |= 1u << g;
     const uint64_t m0 = __ballot(qm & 1u), m1 = __ballot(qm & 2u), m2 = __ballot(qm & 4u),
                    m3 = __ballot(qm & 8u);
-    wave_sync();
     uint64_t todo = q == 0 ? m0 : (q == 1 ? m1 : (q == 2 ? m2 : m3));
     while (__any(todo != 0)) {
       const bool act = todo != 0;
       const int j = act ? 63 - (int)__builtin_clzll(todo) : 0;     // last first
       if (act) todo &= ~(1ull << j);
-      const Splat sp = s_splat[j];
+      const Splat& se = s_splat[j];
+      const Splat sp = se;
       const int pos = bot + j + 1;
       const float dx = __fsub_rn(fx, sp.mx);
       float p2[PXQ];
