@@ -3,7 +3,8 @@
 // Sec. II "Isosurface Extraction") to the initial log-scale, rotation and
 // opacity of its Gaussian.  BF16 weights and activations on the MFMA matrix
 // cores, FP32 accumulation and biases; the FP32 master weights are rounded to
-// bf16 when a work-group stages them in LDS.
+// bf16 when they are staged: by the backward in LDS, by the forward in
+// registers, as the A operands of the transposed products.
 //
 // Products whose K runs over features or hidden units (the layers, and the
 // backward's dZ W^T) use v_mfma_f32_16x16x32_bf16, lane l, j = 0..7:
