@@ -4,7 +4,8 @@
 //
 // Pipeline (all sizes that depend on data stay on the device, so the whole
 // call can be captured in a HIP graph):
-//   k_depth_keys + 4 radix passes   the m pairs sorted stably by depth bits
+//   k_depth_keys + 4 radix passes (or, for few pairs, one work-group's sort)
+//                  the m pairs sorted stably by depth bits
 //                  (ties by pair index): the depth order is sorted once per
 //                  pair instead of once per duplicate; k_depth_keys also
 //                  decides which tiles of each pair's bbox meet its support
@@ -448,6 +449,47 @@ __global__ __launch_bounds__(256) void k_depth_keys(const float* __restrict__ re
   nt8[i] = (uint8_t)min(nt, kNtEscape);
   if (pair_count) pair_count[2 * i + 1] = nt;
   keys[i] = __float_as_uint(r[9]);
+}
+
+// The depth presort of up to kSmallSort pairs in one work-group: a bitonic
+// sort of (key, pair index) words in LDS, whose order is that of the stable
+// radix passes.  Those are 12 launches of 2 to 8 us that a few blocks of keys
+// do not fill: 4096 pairs 54 us, here 35, bound by the LDS (78 steps that read
+// and write up to 32 KB); at twice the pairs the steps would cost more than
+// the passes.
+constexpr int kSmallSort = 4096;
+constexpr int kSmallSortThreads = 1024;
+
+__global__ __launch_bounds__(kSmallSortThreads) void k_depth_sort_small(
+    uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, int m, int n2) {
+  __shared__ uint64_t s[kSmallSort];
+  for (int i = threadIdx.x; i < n2; i += kSmallSortThreads)
+    s[i] = i < m ? (uint64_t)keys[i] << 32 | (uint32_t)i : ~0ull;
+  __syncthreads();
+  for (int k = 2; k <= n2; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int p = threadIdx.x; p < n2 / 2; p += kSmallSortThreads) {
+        const int i = 2 * p - (p & (j - 1));             // bit j clear
+        const uint64_t a = s[i], b = s[i + j];
+        if ((a > b) == ((i & k) == 0)) {
+          s[i] = b;
+          s[i + j] = a;
+        }
+      }
+      // up to a distance of 64 a wave's pairs lie in its own 128 words
+      if (j > 64 || (j == 1 && k > 64)) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+    }
+  __syncthreads();
+  for (int i = threadIdx.x; i < m; i += kSmallSortThreads) {
+    keys[i] = (uint32_t)(s[i] >> 32);
+    vals[i] = (uint32_t)s[i];
+  }
 }
 
 // ------------------------------------------------------------ radix sort
@@ -949,7 +991,14 @@ gs_status gs_bin_sort(const gs_projected* proj, const gs_views* views, const gs_
                      tiling->tile_h, tiles_x, (int)tiles_per_slot, m, pk[0], nt8, erec,
                      pair_first, count_pairs, tile_ranges, 2 * n_tiles_all);
   GS_LAUNCH_CHECK("gs_bin_sort/depth_keys");
-  for (int p = 0; p < 4; ++p) {
+  if (m <= kSmallSort) {
+    int n2 = 2;
+    while (n2 < m) n2 <<= 1;
+    hipLaunchKernelGGL(k_depth_sort_small, dim3(1), dim3(kSmallSortThreads), 0, s, pk[0], pv[0],
+                       (int)m, n2);
+    GS_LAUNCH_CHECK("gs_bin_sort/depth_small");
+  }
+  for (int p = 0; p < 4 && m > kSmallSort; ++p) {
     const int shift = p * kRadixBits;
     const int a = p & 1, b = a ^ 1;
     launch_hist<kRadixBits>(pk[a], count_pairs, shift, L.nb_pairs, hist, s);
