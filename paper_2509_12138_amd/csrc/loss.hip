@@ -45,6 +45,7 @@ static_assert((kLM / kV1) * kLM <= kLThreads && (kLT / kV2) * kLT == kLThreads, 
 
 struct Window {
   float w[kLTaps];
+  float all;            // the blur, by both passes' sums, of a mask that is 1 everywhere
 };
 
 static Window ssim_window() {
@@ -56,6 +57,10 @@ static Window ssim_window() {
   }
   Window W;
   for (int k = 0; k < kLTaps; ++k) W.w[k] = (float)(w[k] / s);
+  float row = 0.f;
+  W.all = 0.f;
+  for (int k = 0; k < kLTaps; ++k) row = fmaf(W.w[k], 1.f, row);
+  for (int k = 0; k < kLTaps; ++k) W.all = fmaf(W.w[k], row, W.all);
   return W;
 }
 
@@ -76,22 +81,24 @@ static LossLayout loss_layout(int S, int H, int W) {
 }
 
 // LDS, one region that holds in turn the staged image and target, the
-// horizontal moment sums, and the partials with their horizontal pass.
-// 38 KB: four work-groups a CU.
-constexpr int kLMom = 4;              // blurred moments: x, y, xx + yy, xy (SSIM uses the two
-                                      // variances only as a sum)
-constexpr int kLLds = std::max({2 * kLS * kLSs, kLMom * kLS * kLM,
+// horizontal moment sums (three planes at a time), and the partials with
+// their horizontal pass.  38 KB: four work-groups a CU.
+constexpr int kLMom = 5;              // blurred moments: x, y, xy, xx, yy
+constexpr int kLMomA = 3;             // of which the first pass through the LDS takes x, y, xy
+constexpr int kLLds = std::max({2 * kLS * kLSs, kLMomA * kLS * kLM,
                                 3 * kLM * kLMs + 3 * kLM * kLTs});
 
 // Bound by the vector ALU (about 7 blur FMAs of every 10 instructions; the halo of
 // both blurs makes 2.1x and 1.7x the tile's positions), and before
 // that by latency: with six moment planes beside the staged images (76 KB, two
 // work-groups a CU) a wave waited alone on its SIMD at every barrier.  The
-// horizontal sums now wait in registers and replace the images, the variances
-// are blurred as one sum, and where every staged pixel is foreground (wt = 1,
-// the inside of the object or of an unmasked image) no mask is blurred; at
-// other tiles its plane goes through the LDS first, alone.  4 images of
-// 1277x717: 215 -> 139 us; 1920x1080, 65% foreground: 146 -> 98 us.
+// horizontal sums now wait in registers, replace the images and pass through
+// the LDS in two groups, and where every staged pixel is foreground (the
+// inside of the object or of an unmasked image) no mask is blurred: its blur
+// is Window::all there; at other tiles its plane goes through the LDS first,
+// alone.  4 images of 1277x717, whole call: 222 -> 158 us.  (144 with the two
+// variances blurred as one sum and a uniform tile's blur taken as 1: that moved
+// the gradient by 6e-7 and its error against 64 bits from 7.1e-7 to 7.8e-7.)
 template <bool MASK>
 __global__ __launch_bounds__(kLThreads, 4) void k_ssim(
     const float* __restrict__ image, const float* __restrict__ target,
@@ -213,58 +220,12 @@ __global__ __launch_bounds__(kLThreads, 4) void k_ssim(
   }
 
   // The blurred foreground wt[u] at this thread's positions of the vertical
-  // pass (column vc, rows vr .. vr + kV1 - 1): 1 where every staged pixel is
-  // foreground, else one more plane, blurred before the others.
+  // pass (column vc, rows vr .. vr + kV1 - 1): win.all where every staged
+  // pixel is foreground, else one more plane, blurred before the others.
   const int vc = t % kLM, vr = (t / kLM) * kV1;
   const bool vert = t < (kLM / kV1) * kLM;
-  float P[kV1][3];
+  float wt[kV1];
   float ssum = 0.f;
-  // SSIM of position (vr + u, vc) from its blurred moments; the partials to
-  // P[u].  ALL: every staged pixel is foreground (wt = 1).
-  auto position = [&](int u, auto ALL, float ux, float uy, float e2, float exy, float wt) {
-    constexpr bool all = decltype(ALL)::value;
-    const int y = oy - kLR + vr + u, x = ox - kLR + vc;
-    const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
-    // moments of the shifted values (mu', E') and the blurred mask wt,
-    // om = 1 - wt (x = x'' + s M with M^2 = M and x'' M = x''):
-    //   mu = mu' + s wt,  var = E'xx - mu'^2 + om (2 s mu' + s^2 wt),
-    //   cov = E'xy - mu'x mu'y + om (sy mu'x + sx mu'y + sx sy wt)
-    // and only the sum of the two variances is used
-    const float om = all ? 0.f : 1.f - wt;
-    const float mx = all ? ux + shx : fmaf(shx, wt, ux);
-    const float my = all ? uy + shy : fmaf(shy, wt, uy);
-    float v2 = (e2 - ux * ux) - uy * uy;
-    float cv = exy - ux * uy;
-    if (!all) {
-      v2 += om * ((2.f * shx * ux + shx * shx * wt) + (2.f * shy * uy + shy * shy * wt));
-      cv += om * (shy * ux + shx * uy + shx * shy * wt);
-    }
-    const float A1 = 2.f * mx * my + C1;
-    const float A2 = 2.f * cv + C2;
-    const float B1 = mx * mx + my * my + C1;
-    const float B2 = v2 + C2;
-    // B1, B2 >= C1, C2 > 0: hardware reciprocals (1 ulp) suffice
-    const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
-    const float iB = iB1 * iB2;
-    const float S = A1 * A2 * iB;
-    const bool in = x >= 0 && x < W && y >= 0 && y < H;
-    if (in && vc >= kLR && vc < kLR + kLT && vr + u >= kLR && vr + u < kLR + kLT) ssum += S;
-    // partials of S in (mu, var, cov), folded so that, at a foreground
-    // pixel p, dS/dx_p = sum_q w_qp (Q0_q + 2 x''_p Q1_q + y''_p Q2_q)
-    // since there x_p - mu_q = x''_p - mu'_q + sx om_q
-    // dS/dmu_x = 2 A2 / (B1^2 B2) (my - mx) (my (mx + my) + C1), the
-    // factored form of 2 my A2 / (B1 B2) - 2 mx A1 A2 / (B1^2 B2), whose
-    // two terms cancel where the means agree; my - mx from the shifted means
-    const float dm = all ? (uy - ux) + (shy - shx) : (uy - ux) + (shy - shx) * wt;
-    const float Pm = 2.f * A2 * iB2 * iB1 * iB1 * dm * fmaf(my, mx + my, C1);
-    const float Pv = -S * iB2;                                  // dS/dvar_x
-    const float Pc = 2.f * A1 * iB;                             // dS/dcov
-    const float Q0 = all ? Pm - 2.f * ux * Pv - uy * Pc
-                         : Pm + 2.f * (shx * om - ux) * Pv + (shy * om - uy) * Pc;
-    P[u][0] = in ? Q0 : 0.f;
-    P[u][1] = in ? Pv : 0.f;
-    P[u][2] = in ? Pc : 0.f;
-  };
 
   // moments, horizontal: item it = staged row r, positions c0 .. c0 + kH1 - 1.
   // Held in registers until every thread has read the images, whose LDS they
@@ -283,7 +244,7 @@ __global__ __launch_bounds__(kLThreads, 4) void k_ssim(
 #pragma unroll
     for (int j = 0; j < kH1 + 2 * kLR; ++j) {
       const float xv = s_x[r * kLSs + c0 + j], yv = s_y[r * kLSs + c0 + j];
-      const float e2 = fmaf(xv, xv, yv * yv), xy = xv * yv;
+      const float xx = xv * xv, yy = yv * yv, xy = xv * yv;
 #pragma unroll
       for (int u = 0; u < kH1; ++u) {
         const int k = j - u;
@@ -291,12 +252,14 @@ __global__ __launch_bounds__(kLThreads, 4) void k_ssim(
         const float w = win.w[k];
         acc[i][u][0] = fmaf(w, xv, acc[i][u][0]);
         acc[i][u][1] = fmaf(w, yv, acc[i][u][1]);
-        acc[i][u][2] = fmaf(w, e2, acc[i][u][2]);
-        acc[i][u][3] = fmaf(w, xy, acc[i][u][3]);
+        acc[i][u][2] = fmaf(w, xy, acc[i][u][2]);
+        acc[i][u][3] = fmaf(w, xx, acc[i][u][3]);
+        acc[i][u][4] = fmaf(w, yy, acc[i][u][4]);
       }
     }
   }
-  float wt[kV1];
+#pragma unroll
+  for (int u = 0; u < kV1; ++u) wt[u] = all_fg ? win.all : 0.f;
   if (!all_fg) {
     float am[kRounds1][kH1];
 #pragma unroll
@@ -323,8 +286,6 @@ __global__ __launch_bounds__(kLThreads, 4) void k_ssim(
 #pragma unroll
         for (int u = 0; u < kH1; ++u) s_h[(t + i * kLThreads) * kH1 + u] = am[i][u];
     __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kV1; ++u) wt[u] = 0.f;
     if (vert) {
 #pragma unroll
       for (int j = 0; j < kV1 + 2 * kLR; ++j) {
@@ -338,46 +299,88 @@ __global__ __launch_bounds__(kLThreads, 4) void k_ssim(
       }
     }
   }
-  __syncthreads();
-  // rows of kLM = 14 kH1 values: item it's kH1 values start at it * kH1
-#pragma unroll
-  for (int i = 0; i < kRounds1; ++i)
-    if (t + i * kLThreads < kItems1)
-#pragma unroll
-      for (int q = 0; q < kLMom; ++q)
-#pragma unroll
-        for (int u = 0; u < kH1; ++u)
-          s_h[q * kLS * kLM + (t + i * kLThreads) * kH1 + u] = acc[i][u][q];
-  __syncthreads();
 
-  // moments, vertical, then SSIM and its partials at positions (vr + u, vc)
-  if (vert) {
-    float m[kV1][kLMom];
+  // moments, vertical, planes q0 .. q1 - 1
+  float m[kV1][kLMom];
 #pragma unroll
-    for (int u = 0; u < kV1; ++u)
+  for (int u = 0; u < kV1; ++u)
 #pragma unroll
-      for (int q = 0; q < kLMom; ++q) m[u][q] = 0.f;
+    for (int q = 0; q < kLMom; ++q) m[u][q] = 0.f;
+  auto vertical = [&](auto Q0, auto Q1) {
+    constexpr int q0 = decltype(Q0)::value, q1 = decltype(Q1)::value;
+    __syncthreads();
+    // rows of kLM = 14 kH1 values: item it's kH1 values start at it * kH1
+#pragma unroll
+    for (int i = 0; i < kRounds1; ++i)
+      if (t + i * kLThreads < kItems1)
+#pragma unroll
+        for (int q = q0; q < q1; ++q)
+#pragma unroll
+          for (int u = 0; u < kH1; ++u)
+            s_h[(q - q0) * kLS * kLM + (t + i * kLThreads) * kH1 + u] = acc[i][u][q];
+    __syncthreads();
+    if (!vert) return;
 #pragma unroll
     for (int j = 0; j < kV1 + 2 * kLR; ++j) {
-      float h[kLMom];
+      float h[q1 - q0];
 #pragma unroll
-      for (int q = 0; q < kLMom; ++q) h[q] = s_h[(q * kLS + vr + j) * kLM + vc];
+      for (int q = q0; q < q1; ++q) h[q - q0] = s_h[((q - q0) * kLS + vr + j) * kLM + vc];
 #pragma unroll
       for (int u = 0; u < kV1; ++u) {
         const int k = j - u;
         if (k < 0 || k > 2 * kLR) continue;
 #pragma unroll
-        for (int q = 0; q < kLMom; ++q) m[u][q] = fmaf(win.w[k], h[q], m[u][q]);
+        for (int q = q0; q < q1; ++q) m[u][q] = fmaf(win.w[k], h[q - q0], m[u][q]);
       }
     }
-    if (all_fg) {
+  };
+  using std::integral_constant;
+  vertical(integral_constant<int, 0>{}, integral_constant<int, kLMomA>{});
+  vertical(integral_constant<int, kLMomA>{}, integral_constant<int, kLMom>{});
+
+  // SSIM and its partials at positions (vr + u, vc)
+  float P[kV1][3];
+  if (vert) {
+    const int x = ox - kLR + vc;
+    const bool colin = x >= 0 && x < W;
+    const bool colc = vc >= kLR && vc < kLR + kLT;
 #pragma unroll
-      for (int u = 0; u < kV1; ++u)
-        position(u, std::true_type{}, m[u][0], m[u][1], m[u][2], m[u][3], 1.f);
-    } else {
-#pragma unroll
-      for (int u = 0; u < kV1; ++u)
-        position(u, std::false_type{}, m[u][0], m[u][1], m[u][2], m[u][3], wt[u]);
+    for (int u = 0; u < kV1; ++u) {
+      const int y = oy - kLR + vr + u;
+      const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
+      // moments of the shifted values (mu', E') and the blurred mask wt,
+      // om = 1 - wt (x = x'' + s M with M^2 = M and x'' M = x''):
+      //   mu = mu' + s wt,  var = E'xx - mu'^2 + om (2 s mu' + s^2 wt),
+      //   cov = E'xy - mu'x mu'y + om (sy mu'x + sx mu'y + sx sy wt)
+      const float om = 1.f - wt[u];
+      const float ux = m[u][0], uy = m[u][1];
+      const float mx = fmaf(shx, wt[u], ux), my = fmaf(shy, wt[u], uy);
+      const float vx = (m[u][3] - ux * ux) + om * (2.f * shx * ux + shx * shx * wt[u]);
+      const float vy = (m[u][4] - uy * uy) + om * (2.f * shy * uy + shy * shy * wt[u]);
+      const float cv = (m[u][2] - ux * uy) + om * (shy * ux + shx * uy + shx * shy * wt[u]);
+      const float A1 = 2.f * mx * my + C1;
+      const float A2 = 2.f * cv + C2;
+      const float B1 = mx * mx + my * my + C1;
+      const float B2 = vx + vy + C2;
+      // B1, B2 >= C1, C2 > 0: hardware reciprocals (1 ulp) suffice
+      const float iB1 = __builtin_amdgcn_rcpf(B1), iB2 = __builtin_amdgcn_rcpf(B2);
+      const float iB = iB1 * iB2;
+      const float S = A1 * A2 * iB;
+      const bool in = colin && y >= 0 && y < H;
+      if (in && colc && vr + u >= kLR && vr + u < kLR + kLT) ssum += S;
+      // partials of S in (mu, var, cov), folded so that, at a foreground
+      // pixel p, dS/dx_p = sum_q w_qp (Q0_q + 2 x''_p Q1_q + y''_p Q2_q)
+      // since there x_p - mu_q = x''_p - mu'_q + sx om_q
+      // dS/dmu_x = 2 A2 / (B1^2 B2) (my - mx) (my (mx + my) + C1), the
+      // factored form of 2 my A2 / (B1 B2) - 2 mx A1 A2 / (B1^2 B2), whose
+      // two terms cancel where the means agree; my - mx from the shifted means
+      const float dm = (uy - ux) + (shy - shx) * wt[u];
+      const float Pm = 2.f * A2 * iB2 * iB1 * iB1 * dm * fmaf(my, mx + my, C1);
+      const float Pv = -S * iB2;                                  // dS/dvar_x
+      const float Pc = 2.f * A1 * iB;                             // dS/dcov
+      P[u][0] = in ? Pm + 2.f * (shx * om - ux) * Pv + (shy * om - uy) * Pc : 0.f;
+      P[u][1] = in ? Pv : 0.f;
+      P[u][2] = in ? Pc : 0.f;
     }
   }
   __syncthreads();
