@@ -72,7 +72,6 @@ __device__ __forceinline__ float dpp_f(float v) {
 constexpr int kDppQuadSwap1 = 0xB1;   // quad_perm [1,0,3,2]
 constexpr int kDppQuadSwap2 = 0x4E;   // quad_perm [2,3,0,1]
 constexpr int kDppQuadReverse = 0x1B; // quad_perm [3,2,1,0]
-constexpr int kDppRowShr1 = 0x111;    // row_shr:1 (row_shr:k is 0x110 + k)
 constexpr int kDppRowRor4 = 0x124;    // row_ror:4
 constexpr int kDppRowRor8 = 0x128;    // row_ror:8
 constexpr int kDppRowHalfMirror = 0x141;  // row_half_mirror (l <-> 7 - l in 8 lanes)

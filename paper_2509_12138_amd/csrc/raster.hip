@@ -1062,46 +1062,14 @@ __device__ __forceinline__ void transpose64(uint32_t& lo, uint32_t& hi) {
   hi = w[1];
 }
 
-// Inclusive scan over runs of lanes that start at lane `first`, by op.
-struct RunScan {
-  bool c1, c2, c4, c8, c15, c31;
-  __device__ __forceinline__ explicit RunScan(int first) {
-    const int l = threadIdx.x & 63;
-    const int a = min(l - first, l & 15);
-    c1 = a >= 1;
-    c2 = a >= 2;
-    c4 = a >= 4;
-    c8 = a >= 8;
-    c15 = (l & 16) && first < (l & 48);
-    c31 = l >= 32 && first < 32;
-  }
-  template <typename Op>
-  __device__ __forceinline__ float operator()(float x, Op op) const {
-    float y = dpp_f<kDppRowShr1>(x);
-    x = c1 ? op(x, y) : x;
-    y = dpp_f<kDppRowShr1 + 1>(x);
-    x = c2 ? op(x, y) : x;
-    y = dpp_f<kDppRowShr1 + 3>(x);
-    x = c4 ? op(x, y) : x;
-    y = dpp_f<kDppRowShr1 + 7>(x);
-    x = c8 ? op(x, y) : x;
-    y = dpp_f<kDppRowBcast15, 0xa>(x);
-    x = c15 ? op(x, y) : x;
-    y = dpp_f<kDppRowBcast31, 0xc>(x);
-    return c31 ? op(x, y) : x;
-  }
-};
-
 constexpr int kPairCap = 512;        // pairs of a batch that are taken pair by pair
 
 struct PairLds {
-  uint4 pix[kRasterWave];            // entries of the pixel (64 bits), its first pair, count | last
-  float2 state[kRasterWave];         // transmittance and dI . colour behind the walk's position
-  float4 dI[kRasterWave];
-  float2 xy[kRasterWave];            // pixel centre
+  uint4 pix[kRasterWave];            // entries of the pixel (64 bits), its first pair, last position
+  float4 dI[kRasterWave];            // image gradient; place in the tile, x | y << 8
   uint16_t pair[kPairCap];           // entry | pixel << 6
-  float2 gw[kPairCap];               // G = dL/d(exponent) and blend weight of each pair;
-                                     // then the entries' sums
+  float2 gw[kPairCap];               // alpha and dI . colour of each pair, then G = dL/d(exponent)
+                                     // and blend weight; then the entries' sums
 };
 
 // Chunked backward on quadrant lane groups: row q of the wave (lanes 16q ..
@@ -1119,14 +1087,19 @@ struct PairLds {
 // its 64 pixels, and the quadrants ran 3 to 10% of their lanes; batches of few
 // pairs are taken pair by pair: the pixels' bits of all entries at once (a
 // lane per entry), transposed to the entries' bits of all pixels, the pairs
-// listed by pixel, 64 pairs at a time composited (run-wise products of the
-// transmittance, run-wise sums of the colour behind), and each entry's sums
-// taken by its own lane.  13.3M Gaussians at 3840x2160: 1864M -> 519M vector
-// instructions, 2420 -> 1662 us; now bound by the 32M memory-side atomic
-// requests of the random gradient rows (973 us without them; more resident
-// waves, fewer registers and earlier loads measured the same).  A cap of 320
-// pairs (five waves a SIMD instead of four) took 2193 us in views with
-// larger footprints, 768 1764.
+// listed by pixel, evaluated 64 at a time, walked by a lane per pixel for the
+// transmittance and the colour behind, and each entry's sums taken by its own
+// lane.  Every term is the one that the walk by quadrants forms, to the bit
+// (products and sums by scans over 64 pairs instead of the walk per pixel: 519M
+// instructions and 1666 us, but gradients 3.5e-6 off); only an entry's sum
+// over its pixels has another order.  13.3M Gaussians at 3840x2160: 1823M ->
+// 602M vector instructions, 2529 -> 1672 us; now bound by the 32M memory-side
+// atomic requests of the random gradient rows (973 us without them; fewer
+// registers and earlier loads measured the same).  10,240 bytes of LDS: 16
+// waves a CU, the four a SIMD that the registers allow.  The cap, measured with
+// 1280 bytes more: 512 pairs (14 waves a CU) 1662 us, 768 (11) 1764; 320 (16)
+// 2193 in views with larger footprints, whose batches then fall to the walk by
+// quadrants.
 template <int TW, int TH>
 __global__ __launch_bounds__(kRasterWave)
 __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
@@ -1135,8 +1108,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
     float* __restrict__ d_rec) {
   constexpr int QW = TW / 2, QH = TH / 2, PXQ = QW * QH / 16, RS = 16 / QW;
   static_assert(QW * QH % 16 == 0 && 16 % QW == 0, "quadrant shape");
-  __shared__ Splat s_splat[kRasterWave];
-  __shared__ uint32_t s_id[kRasterWave];
+  __shared__ Splat s_splat[kRasterWave];       // pad1: the entry's pair
   static_assert(TW == 8 && TH == 8, "pairs");
   __shared__ PairLds s_p;
   const uint32_t item = blockIdx.x;
@@ -1195,20 +1167,22 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
   const float sc[9] = {-kLn2, -kLn2, -0.5f, -1.0f, -0.5f, 1.0f, 1.0f, 1.0f, 1.0f};
   const float rscale = rslot >= 0 ? sc[rslot] : 0.0f;
   const float qx0 = (float)(tx * TW) + 0.5f, qy0 = (float)(ty * TH) + 0.5f;
-  s_p.dI[lane] = make_float4(dI[0][0], dI[0][1], dI[0][2], 0.0f);
-  s_p.xy[lane] = make_float2(fx, fy[0]);
+  s_p.dI[lane] = make_float4(dI[0][0], dI[0][1], dI[0][2], __uint_as_float(lx | ly0 << 8));
+  // centre of the pixel with that record (exact: the tile's corner plus 0 .. 7)
+  auto centre_x = [&](const float4& di) { return qx0 + (float)(__float_as_uint(di.w) & 0xff); };
+  auto centre_y = [&](const float4& di) { return qy0 + (float)(__float_as_uint(di.w) >> 8); };
   for (int top = hi; top > lo; top -= kRasterWave) {
     const int bot = max(lo, top - kRasterWave);
     const int n = top - bot;
     wave_sync();
     // the entry's pixels, among those that blend in this batch
     const uint64_t active = __ballot(last[0] > bot);
-    uint32_t id = 0, plo = 0, phi = 0;
+    uint32_t plo = 0, phi = 0;
     Splat sp{};
     if (lane < n) {
-      id = a.ids[start + bot + lane];
-      s_id[lane] = id;
+      const uint32_t id = a.ids[start + bot + lane];
       sp = load_splat(a.rec, id);
+      sp.pad1 = __uint_as_float(id);
       s_splat[lane] = sp;
       splat_pixels(sp, qx0, qy0, plo, phi);
       plo &= (uint32_t)active;
@@ -1226,9 +1200,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
     const int total = __builtin_amdgcn_readlane(upto, kRasterWave - 1);
     if (total == 0) continue;
     if (total <= kPairCap) {
-      const int lrel = min(max(last[0] - bot, 0), kRasterWave);
-      s_p.pix[lane] = make_uint4(elo, ehi, (uint32_t)(upto - cnt), (uint32_t)(cnt << 16 | lrel));
-      s_p.state[lane] = make_float2(T[0], dIacc[0]);
+      const int lrel = min(max(last[0] - bot, 0), kRasterWave), first = upto - cnt;
+      s_p.pix[lane] = make_uint4(elo, ehi, (uint32_t)first, (uint32_t)lrel);
       wave_sync();
       // the pairs by pixel, last entry first
       const uint64_t above = lane == 63 ? 0ull : ~0ull << (lane + 1);
@@ -1241,50 +1214,58 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
         s_p.pair[place(s_p.pix[p])] = (uint16_t)(lane | p << 6);
       }
       wave_sync();
-      for (int i0 = 0; i0 < total; i0 += kRasterWave) {
-        const int i = min(i0 + lane, total - 1);
-        const bool valid = i0 + lane < total;
+      // a lane per pair: what of it needs no transmittance
+      for (int i = lane; i < total; i += kRasterWave) {
         const uint32_t code = s_p.pair[i];
         const int e = (int)(code & 63), p = (int)(code >> 6);
         const Splat& se = s_splat[e];
-        const uint4 pix = s_p.pix[p];
-        const float2 st = s_p.state[p], xy = s_p.xy[p];
         const float4 di = s_p.dI[p];
-        const float p2 = splat_p2(se, __fsub_rn(xy.x, se.mx), __fsub_rn(xy.y, se.my));
-        const bool pass = valid && e < (int)(pix.w & 0xffff) && splat_pass(se, p2);
-        const float aa = pass ? se.o * splat_gauss(p2) : 0.0f;
-        const float alpha = fminf(kAlphaMax, aa);
-        const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
-        const RunScan scan(max((int)pix.z - i0, 0));
-        const float Tb = st.x * scan(inv, [](float u, float v) { return u * v; });
-        const float w = alpha * Tb;
+        const float p2 = splat_p2(se, __fsub_rn(centre_x(di), se.mx), __fsub_rn(centre_y(di), se.my));
+        const bool pass = e < (int)s_p.pix[p].w && splat_pass(se, p2);
+        const float alpha = fminf(kAlphaMax, se.o * splat_gauss(p2));
         const float dIc = fmaf(di.z, se.b, fmaf(di.y, se.g, di.x * se.r));
-        const float wd = w * dIc;
-        const float sum = scan(wd, [](float u, float v) { return u + v; });
-        const float dLda = fmaf(Tb, dIc, -inv * (st.y + (sum - wd)));
-        if (valid) {
-          s_p.gw[i] = make_float2(aa < kAlphaMax ? dLda * alpha : 0.0f, w);
-          // the last pair of the pixel, or of this round
-          if (lane == kRasterWave - 1 || i + 1 == (int)pix.z + (int)(pix.w >> 16))
-            s_p.state[p] = make_float2(Tb, st.y + sum);
-        }
-        wave_sync();
+        s_p.gw[i] = pass ? make_float2(alpha, dIc) : make_float2(0.0f, 0.0f);
       }
-      // sums over an entry's pixels
-      float sG = 0.f, sGx = 0.f, sGy = 0.f, sGxx = 0.f, sGxy = 0.f, sGyy = 0.f;
+      wave_sync();
+      // a lane per pixel: its pairs one after the other, last entry first, as
+      // the walk by quadrants has them (a pair that does not blend, alpha 0,
+      // leaves T and dIacc as they are)
+      constexpr int kRead = 4;
+      for (int i = 0; __any(i < cnt); i += kRead) {
+        float2 v[kRead];
+#pragma unroll
+        for (int k = 0; k < kRead; ++k) v[k] = s_p.gw[min(first + i + k, kPairCap - 1)];
+#pragma unroll
+        for (int k = 0; k < kRead; ++k) {
+          const bool mine = i + k < cnt;
+          const float alpha = mine ? v[k].x : 0.0f, dIc = mine ? v[k].y : 0.0f;
+          const float inv = __builtin_amdgcn_rcpf(1.0f - alpha);
+          const float Tb = T[0] * inv;                 // transmittance in front of it
+          const float w = alpha * Tb;
+          const float dLda = fmaf(Tb, dIc, -inv * dIacc[0]);
+          dIacc[0] = fmaf(w, dIc, dIacc[0]);
+          T[0] = Tb;
+          // (the derivative through a clamped alpha is zero)
+          if (alpha > 0.0f)
+            s_p.gw[first + i + k] = make_float2(alpha < kAlphaMax ? dLda * alpha : 0.0f, w);
+        }
+      }
+      wave_sync();
+      // sums over an entry's pixels of what the walk by quadrants sums
+      float smx = 0.f, smy = 0.f, sG = 0.f, sGxx = 0.f, sGxy = 0.f, sGyy = 0.f;
       float sr = 0.f, sg = 0.f, sb = 0.f, sw = 0.f;
       for (uint64_t m = (uint64_t)phi << 32 | plo; m; m &= m - 1) {
         const int p = (int)__builtin_ctzll(m);
-        const float2 gw = s_p.gw[place(s_p.pix[p])], xy = s_p.xy[p];
+        const float2 gw = s_p.gw[place(s_p.pix[p])];
         const float4 di = s_p.dI[p];
-        const float dx = __fsub_rn(xy.x, sp.mx), dy = __fsub_rn(xy.y, sp.my);
-        const float Gx = gw.x * dx, Gy = gw.x * dy;
+        const float dx = __fsub_rn(centre_x(di), sp.mx), dy = __fsub_rn(centre_y(di), sp.my);
+        const float Gdy = gw.x * dy;
+        smx += fmaf(2.0f * sp.A * dx, gw.x, sp.B * Gdy);
+        smy += fmaf(2.0f * sp.C, Gdy, sp.B * dx * gw.x);
         sG += gw.x;
-        sGx += Gx;
-        sGy += Gy;
-        sGxx = fmaf(Gx, dx, sGxx);
-        sGxy = fmaf(Gx, dy, sGxy);
-        sGyy = fmaf(Gy, dy, sGyy);
+        sGxx = fmaf(dx * dx, gw.x, sGxx);
+        sGxy = fmaf(dx, Gdy, sGxy);
+        sGyy = fmaf(Gdy, dy, sGyy);
         sr = fmaf(di.x, gw.y, sr);
         sg = fmaf(di.y, gw.y, sg);
         sb = fmaf(di.z, gw.y, sb);
@@ -1294,16 +1275,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
       // through LDS, so that the 9 atomics of an entry are side by side; an
       // entry that blended nowhere adds nothing
       float* out = reinterpret_cast<float*>(s_p.gw);
-      const float hB = 0.5f * sp.B;
-      const float comp[9] = {-2.0f * kLn2 * fmaf(sp.A, sGx, hB * sGy),
-                             -2.0f * kLn2 * fmaf(sp.C, sGy, hB * sGx),
-                             -0.5f * sGxx,
-                             -sGxy,
-                             -0.5f * sGyy,
-                             sG * __builtin_amdgcn_rcpf(sp.o),
-                             sr,
-                             sg,
-                             sb};
+      const float comp[9] = {-kLn2 * smx, -kLn2 * smy, -0.5f * sGxx, -sGxy, -0.5f * sGyy,
+                             sG * __builtin_amdgcn_rcpf(sp.o), sr, sg, sb};
 #pragma unroll
       for (int k = 0; k < 9; ++k) out[lane * 9 + k] = comp[k];
       const uint64_t adds = __ballot(sw != 0.0f);
@@ -1311,11 +1284,10 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
 #pragma unroll
       for (int k = 0; k < 9; ++k) {
         const int f = k * kRasterWave + lane, e = f / 9;
-        if (adds >> e & 1) atomicAdd(d_rec + (int64_t)s_id[e] * GS_DREC_STRIDE + (f - 9 * e), out[f]);
+        if (adds >> e & 1)
+          atomicAdd(d_rec + (int64_t)__float_as_uint(s_splat[e].pad1) * GS_DREC_STRIDE + (f - 9 * e),
+                    out[f]);
       }
-      const float2 st = s_p.state[lane];
-      T[0] = st.x;
-      dIacc[0] = st.y;
       continue;
     }
     // many pairs: quadrant by quadrant
@@ -1382,7 +1354,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
       // rows whose entry no pixel of theirs passed add nothing
       const uint64_t rows = __ballot(any);
       if (rslot >= 0 && ((rows >> (16 * q)) & 0xffffull) != 0)
-        atomicAdd(d_rec + (int64_t)s_id[j] * GS_DREC_STRIDE + rslot, rscale * tot);
+        atomicAdd(d_rec + (int64_t)__float_as_uint(sp.pad1) * GS_DREC_STRIDE + rslot, rscale * tot);
     }
   }
 }
