@@ -1257,6 +1257,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
       for (uint64_t m = (uint64_t)phi << 32 | plo; m; m &= m - 1) {
         const int p = (int)__builtin_ctzll(m);
         const float2 gw = s_p.gw[place(s_p.pix[p])];
+        if (gw.y == 0.0f) continue;      // not blended: nothing of the pixel, were it infinite
         const float4 di = s_p.dI[p];
         const float dx = __fsub_rn(centre_x(di), sp.mx), dy = __fsub_rn(centre_y(di), sp.my);
         const float Gdy = gw.x * dy;
