@@ -1292,6 +1292,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_chunked_q(
       continue;
     }
     // many pairs: quadrant by quadrant
+    wave_sync();
     uint32_t qm = 0;
 #pragma unroll
     for (int g = 0; g < 4; ++g)
