@@ -189,18 +189,22 @@ def timed_steps(tr, order, first, steps):
 
 def fwd_kernel_name(tile, fwd_waves, sched="default", chunk=0):
     """The forward kernel(s) the library launches for this plan."""
+    from paper_2509_12138_amd import ops
     if sched.endswith("+split") and chunk:
         return f"k_raster_fwd_part<{tile[0]}, {tile[1]}>+k_raster_fwd_join<{tile[0]}, {tile[1]}>"
-    return f"k_raster_fwd<{tile[0]}, {tile[1]}, {fwd_waves}>"
+    nw = ops.forward_waves(tuple(tile), sched, chunk, fwd_waves)
+    return f"k_raster_fwd<{tile[0]}, {tile[1]}, {nw}>"
 
 
 def bwd_kernel_name(tile, chunk, recompute, deterministic):
     """The backward kernel the library launches for this plan."""
+    from paper_2509_12138_amd import ops
     if chunk and not recompute:
         if tuple(tile) == (8, 8) and not deterministic:
             return f"k_raster_bwd_chunked_q<{tile[0]}, {tile[1]}>"   # quadrant lane groups
         return f"k_raster_bwd_chunked<{tile[0]}, {tile[1]}>"
-    return f"k_raster_bwd<{tile[0]}, {tile[1]}, {'true' if recompute else 'false'}>"
+    nk = ops.backward_blocks(tuple(tile), deterministic)
+    return f"k_raster_bwd<{tile[0]}, {tile[1]}, {nk}, {'true' if recompute else 'false'}>"
 
 
 def count_work(tr, views, W, H, tile):
@@ -361,6 +365,9 @@ def batched_main(args):
         tile, sched, chunk, fwd_waves, det = best[1]
         tr.set_plan(*best[1])
         plan_source = "autotuner"
+    else:
+        from paper_2509_12138_amd import autotune
+        fwd_waves = autotune.normalize((tile, sched, chunk, fwd_waves, det))[3]
     need = tr.fit_capacity()
     tr.prepare()
     log(f"{tr.S} slots, {tr.G} view groups, max duplicates per step {need}; graphs captured")
@@ -497,8 +504,10 @@ def main():
 
     tune_entry = None
     if args.no_autotune or (args.tile and args.schedule is not None and args.chunk is not None):
-        plan = (tuple(int(x) for x in (args.tile or "16x16").split("x")), args.schedule or "default",
-                args.chunk or 0, args.fwd_waves or 1, bool(args.deterministic))
+        from paper_2509_12138_amd import autotune
+        plan = autotune.normalize(
+            (tuple(int(x) for x in (args.tile or "16x16").split("x")), args.schedule or "default",
+             args.chunk or 0 if stored else 0, args.fwd_waves or 1, bool(args.deterministic)))
     else:
         from paper_2509_12138_amd import autotune
         t0 = time.perf_counter()

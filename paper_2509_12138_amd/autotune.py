@@ -17,6 +17,8 @@ import time
 import numpy as np
 import torch
 
+from . import ops
+
 # (tile, schedule, backward chunk, forward waves per tile, deterministic
 # gradients); every tile shape here has a compiled rasteriser.  A fixed set
 # of plans (the full-size parity tests run each); the tuner itself searches
@@ -35,10 +37,14 @@ CANDIDATES = [
 
 
 def normalize(plan):
-    """Plans of older caches lack the trailing fields: fill the defaults."""
+    """Plans of older caches lack the trailing fields: fill the defaults.
+    Forward waves of 0 or 1, which leave the number to the library, become the
+    number it launches, so that a plan's fields say what runs."""
     tile, sched, chunk = plan[0], plan[1], plan[2]
     nw = plan[3] if len(plan) > 3 else 1
     det = bool(plan[4]) if len(plan) > 4 else False
+    if nw <= 1:
+        nw = max(1, ops.forward_waves(tuple(tile), sched, int(chunk), int(nw)))
     return (tuple(tile), sched, int(chunk), int(nw), det)
 
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "gsmi", "autotune.json")
@@ -91,17 +97,19 @@ SCHEDULES = ["lpt", "default", "persistent", "lpt+split"]
 
 
 def valid_waves(tile):
-    """Forward waves per tile that divide the tile's pixels per lane."""
+    """Forward waves per tile that can be asked for and are launches of their
+    own: the numbers that divide the tile's pixels per lane, less 1 where the
+    library then launches more."""
     px = tile[0] * tile[1] // 64
-    return [w for w in (1, 2, 4) if px % w == 0]
+    return sorted({ops.forward_waves(tile, "lpt", 0, w) for w in (1, 2, 4) if px % w == 0})
 
 
 def valid(plan):
     tile, sched, chunk, nw, det = plan
-    if sched == "persistent" and nw > 1:
-        return False                                   # the queue takes one wave per tile
-    if sched.endswith("+split") and (chunk == 0 or nw != 1):
-        return False                                   # split: chunked, joined by one wave
+    if sched == "persistent":
+        return nw == 1                                 # the queue takes one wave per tile
+    if sched.endswith("+split"):
+        return chunk > 0 and nw == 1                   # split: chunked, joined by one wave
     return nw in valid_waves(tile)
 
 

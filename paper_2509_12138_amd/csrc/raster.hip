@@ -1783,10 +1783,34 @@ struct Launch {
   TileSched sch;
   ChunkDev ch;
   int64_t max_items;
-  int fwd_waves;
+  int fwd_waves, bwd_blocks;
 };
 
-static Launch make_launch(const RasterDev& a, const gs_raster_plan* plan) {
+// Whether the plan's forward composites chunk items and joins them.
+static bool split_forward(const gs_raster_plan* plan) {
+  return plan && plan->fwd_split && plan->chunk > 0 && plan->checkpoints;
+}
+
+// Waves per tile of the forward.  Where the plan leaves the choice (fwd_waves
+// 0 or 1, no queue): the most that the tile's pixels allow, one 8x8 block each
+// for 16x16 tiles.  A wave's time is its list's length times its visits' cost,
+// and both the pixels per lane and the entries that reach its box fall with
+// more waves (one against the most): 1920x1080 in 16x16 tiles 946 / 225 us, 32
+// images of 640x360 1526 / 508, 333x251 224 / 65, 128x128 137 / 48.
+static int forward_waves(int tw, int th, const gs_raster_plan* plan) {
+  if (split_forward(plan) || (plan && plan->queue)) return 1;
+  if (plan && plan->fwd_waves > 1) return plan->fwd_waves;
+  const int px = tw * th / kRasterWave;
+  return px % 4 == 0 ? 4 : (px % 2 == 0 ? 2 : 1);
+}
+
+// 8x8 blocks that a wave of the whole-list backward takes: one, or all of its
+// tile where gradients are stored.
+static int backward_blocks(int tw, int th, const gs_raster_plan* plan) {
+  return plan && plan->dup_grads ? tw * th / kRasterWave : 1;
+}
+
+static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, const gs_raster_plan* plan) {
   Launch L;
   L.sch.order = plan ? plan->tile_order : nullptr;
   L.sch.queue = plan ? plan->queue : nullptr;
@@ -1795,7 +1819,8 @@ static Launch make_launch(const RasterDev& a, const gs_raster_plan* plan) {
   L.ch.items = plan ? plan->chunk_items : nullptr;
   L.ch.ck = plan && plan->chunk > 0 ? reinterpret_cast<float4*>(plan->checkpoints) : nullptr;
   L.max_items = plan ? plan->max_items : 0;
-  L.fwd_waves = plan && plan->fwd_waves > 1 ? plan->fwd_waves : 0;
+  L.fwd_waves = forward_waves(tiling->tile_w, tiling->tile_h, plan);
+  L.bwd_blocks = backward_blocks(tiling->tile_w, tiling->tile_h, plan);
   if (L.sch.queue) {
     int64_t w = plan->persistent_waves > 0 ? plan->persistent_waves : (int64_t)device_cu_count() * 16;
     L.blocks = (unsigned)std::min<int64_t>(w, std::max<int64_t>(a.n_tiles, 1));
@@ -1807,18 +1832,12 @@ static Launch make_launch(const RasterDev& a, const gs_raster_plan* plan) {
   return L;
 }
 
-// Waves per tile where the plan leaves the choice (fwd_waves 0 or 1, no
-// queue): the most that the tile's pixels allow, one 8x8 block each for 16x16
-// tiles.  A wave's time is its list's length times its visits' cost, and both
-// the pixels per lane and the entries that reach its box fall with more
-// waves: 1920x1080 in 16x16 tiles 1224 us on one wave per tile, 357 us on
-// four; 32 images of 640x360 1780 -> 640 us; 128x128 158 -> 50 us.
 template <int TW, int TH>
 static void launch_fwd(const RasterDev& a, const Launch& L, float* image, float* T_final,
                        int32_t* n_contrib, hipStream_t s) {
   constexpr int PXT = TileGeom<TW, TH>::PX;
   constexpr int kMost = PXT % 4 == 0 ? 4 : (PXT % 2 == 0 ? 2 : 1);
-  const int nw = L.sch.queue ? 1 : (L.fwd_waves ? L.fwd_waves : kMost);
+  const int nw = L.fwd_waves;
 #define GS_FWD_LAUNCH(NW)                                                                       \
   hipLaunchKernelGGL((k_raster_fwd<TW, TH, NW>), dim3(L.blocks), dim3(NW * kRasterWave), 0, s, a, \
                      L.sch, L.ch, image, T_final, n_contrib)
@@ -1867,7 +1886,8 @@ static void launch_bwd(const RasterDev& a, const Launch& L, const float* T_final
     constexpr int NB = TW * TH / 64;
     const bool rec = mode == GS_BWD_RECOMPUTE;
     // (a queue's grid is persistent and takes the waves of a tile as items)
-    int64_t waves = a.dup_grads || L.sch.queue ? L.blocks : (int64_t)L.blocks * NB;
+    const bool per_tile = L.bwd_blocks > 1;
+    int64_t waves = per_tile || L.sch.queue ? L.blocks : (int64_t)L.blocks * NB;
     int lg_share = 0;
     if (!L.sch.queue)
       while (lg_share < kBwdShareLgMax && 2 * waves <= kBwdShareWavesPerCu * device_cu_count()) {
@@ -1878,8 +1898,8 @@ static void launch_bwd(const RasterDev& a, const Launch& L, const float* T_final
 #define GS_BWD_LAUNCH(NK, REC)                                                                \
   hipLaunchKernelGGL((k_raster_bwd<TW, TH, NK, REC>), blocks, dim3(kRasterWave), 0, s, a,     \
                      L.sch, lg_share, T_final, n_contrib, d_image, d_rec)
-    if (a.dup_grads && rec) GS_BWD_LAUNCH(NB, true);
-    else if (a.dup_grads) GS_BWD_LAUNCH(NB, false);
+    if (per_tile && rec) GS_BWD_LAUNCH(NB, true);
+    else if (per_tile) GS_BWD_LAUNCH(NB, false);
     else if (rec) GS_BWD_LAUNCH(1, true);
     else GS_BWD_LAUNCH(1, false);
 #undef GS_BWD_LAUNCH
@@ -1957,6 +1977,16 @@ using namespace gsmi;
 
 extern "C" {
 
+int32_t gs_raster_fwd_waves(const gs_tiling* tiling, const gs_raster_plan* plan) {
+  if (!tiling || !raster_shape_supported(tiling->tile_w, tiling->tile_h)) return 0;
+  return forward_waves(tiling->tile_w, tiling->tile_h, plan);
+}
+
+int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, const gs_raster_plan* plan) {
+  if (!tiling || !raster_shape_supported(tiling->tile_w, tiling->tile_h)) return 0;
+  return backward_blocks(tiling->tile_w, tiling->tile_h, plan);
+}
+
 gs_status gs_raster_fwd(const gs_projected* proj, const gs_views* views, const gs_tiling* tiling,
                         const uint32_t* ids, const uint32_t* tile_ranges, const float bg[3],
                         float* image, float* T_final, int32_t* n_contrib,
@@ -1971,8 +2001,8 @@ gs_status gs_raster_fwd(const gs_projected* proj, const gs_views* views, const g
   hipStream_t s = as_stream(stream);
   st = plan_prepare(plan, tiling, s, "gs_raster_fwd");
   if (st != GS_OK) return st;
-  const Launch L = make_launch(a, plan);
-  const bool split = plan && plan->fwd_split && L.ch.ck != nullptr;
+  const Launch L = make_launch(a, tiling, plan);
+  const bool split = split_forward(plan);
   GS_REQUIRE(!split || (plan->chunk_last && T_final),
              "gs_raster_fwd: fwd_split needs chunk_last and the stored state (T_final, n_contrib)");
 #define GS_FWD_CASE(a_, b_)                                                          \
@@ -2012,7 +2042,7 @@ gs_status gs_raster_bwd(const gs_projected* proj, const gs_views* views, const g
   }
   st = plan_prepare(plan, tiling, s, "gs_raster_bwd");
   if (st != GS_OK) return st;
-  const Launch L = make_launch(a, plan);
+  const Launch L = make_launch(a, tiling, plan);
 #define GS_BWD_CASE(a_, b_)                                                   \
   if (tiling->tile_w == a_ && tiling->tile_h == b_)                           \
     launch_bwd<a_, b_>(a, L, T_final, n_contrib, d_image, mode, d_rec, s);    \

@@ -113,6 +113,30 @@ def tiling_struct(width, height, tile=(16, 16)):
     return _lib.gs_tiling(width, height, tile[0], tile[1])
 
 
+def _plan_kind(mode, chunk, fwd_waves, deterministic):
+    """A gs_raster_plan that tells the library which kernels a schedule stands for (its pointers
+    are compared with NULL only)."""
+    set_ = C.c_void_p(1)
+    plan = _lib.gs_raster_plan(chunk=int(chunk), fwd_waves=int(fwd_waves))
+    plan.queue = set_ if mode == "persistent" else None
+    plan.checkpoints = set_ if chunk else None
+    plan.fwd_split = int(mode.endswith("+split"))
+    plan.dup_grads = set_ if deterministic else None
+    return plan
+
+
+def forward_waves(tile, mode="default", chunk=0, fwd_waves=1):
+    """Waves per tile that the forward of this schedule launches (set_schedule's arguments)."""
+    return _lib.load().gs_raster_fwd_waves(
+        C.byref(tiling_struct(*tile, tile)), C.byref(_plan_kind(mode, chunk, fwd_waves, False)))
+
+
+def backward_blocks(tile, deterministic=False):
+    """8x8 pixel blocks that a wave of the whole-list backward takes."""
+    return _lib.load().gs_raster_bwd_blocks(
+        C.byref(tiling_struct(*tile, tile)), C.byref(_plan_kind("default", 0, 1, deterministic)))
+
+
 # --------------------------------------------------------------------------
 # Buffers of one rasterisation configuration
 # --------------------------------------------------------------------------
@@ -214,8 +238,10 @@ class RasterBuffers:
         (longest first, pulled from an atomic queue by a persistent grid).
         chunk > 0 (a multiple of 64) cuts the backward's tile lists into
         chunk-entry work items (stored mode), using forward checkpoints.
-        fwd_waves (1, 2, 4) splits each tile's pixels over that many waves in
-        the forward.  deterministic: per-entry gradient slots summed per pair
+        fwd_waves (2, 4) splits each tile's pixels over that many waves in the
+        forward; 0 or 1 leaves the number to the library (see forward_waves):
+        one with "persistent" and with split, else the most of 4 that the tile's
+        pixels allow.  deterministic: per-entry gradient slots summed per pair
         instead of atomics (bitwise reproducible gradients).  split (chunked
         plans; also a "+split" suffix of the mode, e.g. "lpt+split"): the
         forward composites the chunk items in parallel and joins them per

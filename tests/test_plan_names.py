@@ -1,0 +1,84 @@
+"""Raster plans say what runs (no GPU): forward waves of 0 or 1 leave the number to the library, so
+the tuner never times one launch under two names, its plans carry the launched number, and the
+kernel names that bench.py prints are instances the library holds."""
+import importlib.util
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2509_12138_amd import _lib, autotune, ops
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib():
+    if not os.path.exists(_lib.LIB_PATH):
+        from paper_2509_12138_amd import build
+        build.build()
+    return _lib.load()
+
+
+@pytest.mark.parametrize("stored", [True, False])
+@pytest.mark.parametrize("seed", range(4))
+def test_search_times_a_launch_once(seed, stored):
+    rng = random.Random(seed)
+    timed = {}
+
+    def measure(plan):
+        plan = autotune.normalize(plan)
+        if not stored and plan[2]:
+            return None
+        assert autotune.valid(plan), plan
+        return timed.setdefault(plan, rng.uniform(1, 2))
+
+    autotune.staged_search(measure, stored)
+    launches = [(t, s, c, ops.forward_waves(t, s, c, w), d) for t, s, c, w, d in timed]
+    assert len(set(launches)) == len(launches)
+    assert launches == list(timed)                     # the plans name what they launch
+
+
+@pytest.mark.parametrize("tile,most", [((16, 16), 4), ((8, 8), 1), ((16, 8), 2), ((8, 16), 2),
+                                       ((32, 8), 4), ((32, 16), 4), ((16, 32), 4)])
+def test_launched_waves(tile, most):
+    assert ops.forward_waves(tile, "lpt", 64, 1) == ops.forward_waves(tile) == most
+    assert ops.forward_waves(tile, "lpt", 64, most) == most
+    assert ops.forward_waves(tile, "persistent", 64, 1) == 1
+    assert ops.forward_waves(tile, "lpt+split", 64, 1) == 1
+    assert ops.forward_waves(tile, "lpt+split", 0, 1) == most      # no chunks, no split
+    # a plan of an older cache, and one stored with the library's choice
+    assert autotune.normalize((list(tile), "lpt", 64))[3] == most
+    assert autotune.normalize((tile, "persistent", 0, 1, False))[3] == 1
+    if most > 1:
+        assert ops.forward_waves(tile, "lpt", 64, 2) == 2
+        assert autotune.normalize((tile, "lpt", 64, 2, False))[3] == 2
+
+
+def test_bench_names_are_instances():
+    nm = shutil.which("nm")
+    if nm is None:
+        pytest.skip("no nm")
+    out = subprocess.run([nm, "-C", "--defined-only", _lib.LIB_PATH], check=True,
+                         capture_output=True, text=True).stdout
+    spec = importlib.util.spec_from_file_location("bench", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    names = set()
+    for tile in autotune.TILES:
+        for waves in (1, 2, 4):
+            if tile[0] * tile[1] // 64 % waves == 0:
+                for sched, chunk in (("lpt", 64), ("default", 0), ("persistent", 0), ("lpt+split", 64)):
+                    names.update(bench.fwd_kernel_name(tile, 1 if sched == "persistent" else waves,
+                                                       sched, chunk).split("+"))
+        for chunk in (0, 64):
+            for recompute in (False, True):
+                for det in (False, True):
+                    names.add(bench.bwd_kernel_name(tile, chunk, recompute, det))
+    missing = [n for n in sorted(names) if "gsmi::__device_stub__" + n not in out
+               and "gsmi::" + n + "(" not in out]
+    assert not missing, missing
+    assert bench.fwd_kernel_name((16, 16), 1, "lpt", 64) == "k_raster_fwd<16, 16, 4>"
+    assert bench.bwd_kernel_name((16, 16), 0, False, False) == "k_raster_bwd<16, 16, 1, false>"
