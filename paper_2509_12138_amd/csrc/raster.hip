@@ -1804,10 +1804,21 @@ static int forward_waves(int tw, int th, const gs_raster_plan* plan) {
   return px % 4 == 0 ? 4 : (px % 2 == 0 ? 2 : 1);
 }
 
+// The grid of a queue's plan, at most.
+static int64_t queue_waves(const gs_raster_plan* plan) {
+  return plan->persistent_waves > 0 ? plan->persistent_waves : (int64_t)device_cu_count() * 16;
+}
+
 // 8x8 blocks that a wave of the whole-list backward takes: one, or all of its
-// tile where gradients are stored.
-static int backward_blocks(int tw, int th, const gs_raster_plan* plan) {
-  return plan && plan->dup_grads ? tw * th / kRasterWave : 1;
+// tile where gradients are stored, and with a queue of so few waves that their
+// number and not the longest lists bounds the call: every block stages the
+// tile's whole list.  A wave per block / per tile: 1920x1080, 16 tiles a wave
+// 2302 / 1952 us, 32 4234 / 3564, but 8 tiles 1273 / 1628; 640x360, 14 tiles a
+// wave 1778 / 1562, 4 tiles 514 / 838.
+constexpr int64_t kQueueTilesPerWave = 12;
+static int backward_blocks(int tw, int th, int64_t n_tiles, const gs_raster_plan* plan) {
+  const bool per_tile = plan && (plan->dup_grads || (plan->queue && n_tiles > kQueueTilesPerWave * queue_waves(plan)));
+  return per_tile ? tw * th / kRasterWave : 1;
 }
 
 static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, const gs_raster_plan* plan) {
@@ -1820,10 +1831,9 @@ static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, const gs_
   L.ch.ck = plan && plan->chunk > 0 ? reinterpret_cast<float4*>(plan->checkpoints) : nullptr;
   L.max_items = plan ? plan->max_items : 0;
   L.fwd_waves = forward_waves(tiling->tile_w, tiling->tile_h, plan);
-  L.bwd_blocks = backward_blocks(tiling->tile_w, tiling->tile_h, plan);
+  L.bwd_blocks = backward_blocks(tiling->tile_w, tiling->tile_h, a.n_tiles, plan);
   if (L.sch.queue) {
-    int64_t w = plan->persistent_waves > 0 ? plan->persistent_waves : (int64_t)device_cu_count() * 16;
-    L.blocks = (unsigned)std::min<int64_t>(w, std::max<int64_t>(a.n_tiles, 1));
+    L.blocks = (unsigned)std::min<int64_t>(queue_waves(plan), std::max<int64_t>(a.n_tiles, 1));
   } else if (L.sch.order) {
     L.blocks = (unsigned)std::max<int64_t>(a.n_tiles, 1);
   } else {
@@ -1885,7 +1895,8 @@ static void launch_bwd(const RasterDev& a, const Launch& L, const float* T_final
     // whole lists: a wave per 8x8 block, or per tile where gradients are stored
     constexpr int NB = TW * TH / 64;
     const bool rec = mode == GS_BWD_RECOMPUTE;
-    // (a queue's grid is persistent and takes the waves of a tile as items)
+    // (a queue's grid is persistent and takes the blocks of a tile as items;
+    // more waves than tiles measured slower: 336 tiles 183 us, 207 on 1344 waves)
     const bool per_tile = L.bwd_blocks > 1;
     int64_t waves = per_tile || L.sch.queue ? L.blocks : (int64_t)L.blocks * NB;
     int lg_share = 0;
@@ -1977,14 +1988,19 @@ using namespace gsmi;
 
 extern "C" {
 
-int32_t gs_raster_fwd_waves(const gs_tiling* tiling, const gs_raster_plan* plan) {
+static int64_t call_tiles(const gs_tiling* t, int32_t n_slots) {
+  return ceil_div(t->width, t->tile_w) * ceil_div(t->height, t->tile_h) * n_slots;
+}
+
+int32_t gs_raster_fwd_waves(const gs_tiling* tiling, int32_t n_slots, const gs_raster_plan* plan) {
+  (void)n_slots;
   if (!tiling || !raster_shape_supported(tiling->tile_w, tiling->tile_h)) return 0;
   return forward_waves(tiling->tile_w, tiling->tile_h, plan);
 }
 
-int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, const gs_raster_plan* plan) {
+int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, int32_t n_slots, const gs_raster_plan* plan) {
   if (!tiling || !raster_shape_supported(tiling->tile_w, tiling->tile_h)) return 0;
-  return backward_blocks(tiling->tile_w, tiling->tile_h, plan);
+  return backward_blocks(tiling->tile_w, tiling->tile_h, call_tiles(tiling, n_slots), plan);
 }
 
 gs_status gs_raster_fwd(const gs_projected* proj, const gs_views* views, const gs_tiling* tiling,

@@ -125,16 +125,21 @@ def _plan_kind(mode, chunk, fwd_waves, deterministic):
     return plan
 
 
-def forward_waves(tile, mode="default", chunk=0, fwd_waves=1):
-    """Waves per tile that the forward of this schedule launches (set_schedule's arguments)."""
+def forward_waves(tile, mode="default", chunk=0, fwd_waves=1, size=None, n_slots=1):
+    """Waves per tile that the forward of this schedule (set_schedule's arguments) launches for
+    n_slots images of size = (width, height)."""
     return _lib.load().gs_raster_fwd_waves(
-        C.byref(tiling_struct(*tile, tile)), C.byref(_plan_kind(mode, chunk, fwd_waves, False)))
+        C.byref(tiling_struct(*(size or tile), tile)), n_slots,
+        C.byref(_plan_kind(mode, chunk, fwd_waves, False)))
 
 
-def backward_blocks(tile, deterministic=False):
+def backward_blocks(tile, mode="default", deterministic=False, persistent_waves=0, size=None,
+                    n_slots=1):
     """8x8 pixel blocks that a wave of the whole-list backward takes."""
-    return _lib.load().gs_raster_bwd_blocks(
-        C.byref(tiling_struct(*tile, tile)), C.byref(_plan_kind("default", 0, 1, deterministic)))
+    plan = _plan_kind(mode, 0, 1, deterministic)
+    plan.persistent_waves = persistent_waves
+    return _lib.load().gs_raster_bwd_blocks(C.byref(tiling_struct(*(size or tile), tile)), n_slots,
+                                            C.byref(plan))
 
 
 # --------------------------------------------------------------------------

@@ -82,3 +82,15 @@ def test_bench_names_are_instances():
     assert not missing, missing
     assert bench.fwd_kernel_name((16, 16), 1, "lpt", 64) == "k_raster_fwd<16, 16, 4>"
     assert bench.bwd_kernel_name((16, 16), 0, False, False) == "k_raster_bwd<16, 16, 1, false>"
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (8, 8), (32, 16)])
+@pytest.mark.parametrize("waves", [1, 64, 4096])
+def test_queue_of_few_waves_takes_tiles(tile, waves):
+    # 12 tiles a wave is the line between a wave per 8x8 block and one per tile
+    nb = tile[0] * tile[1] // 64
+    for tiles, blocks in ((12 * waves, 1), (12 * waves + 1, nb)):
+        size = (tile[0] * tiles, tile[1])
+        assert ops.backward_blocks(tile, "persistent", persistent_waves=waves, size=size) == blocks
+        assert ops.backward_blocks(tile, "lpt", persistent_waves=waves, size=size) == 1
+        assert ops.backward_blocks(tile, "lpt", True, size=size) == nb
