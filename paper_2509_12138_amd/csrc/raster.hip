@@ -27,18 +27,25 @@ constexpr int kRasterWave = 64;
 constexpr int kFwdSlots = kRasterWave + 2;
 
 // XCD-aware tile order: work-group i runs on XCD (i mod 8), and the XCDs take
-// groups of kXcdTiles consecutive tiles in turn: neighbours that share
-// Gaussians share an L2, and an image's middle rows, whose lists are the
-// longest, do not all fall to two XCDs.
-// An eighth of the image to each XCD instead: 1M Gaussians at 1920x1080, whole
-// forward 389 us, groups of 4, 8 or 32 tiles 223-227 us.
+// runs of consecutive tiles in turn: neighbours that share Gaussians share an
+// L2.  Of a few images the runs are kXcdTiles long, so that an image's middle
+// rows, whose lists are the longest, do not all fall to two XCDs (an eighth of
+// the image to each instead: 1M Gaussians at 1920x1080, whole forward 389 us,
+// runs of 4, 8 or 32 tiles 223-227 us; two images 368 / 309, six 802 / 779).
+// Of a multiple of 8 images each XCD takes whole ones: the XCDs' shares are
+// equal then, and an image's Gaussians stay in one L2 (runs of 8 tiles / whole
+// images: backward of 32 images of 640x360 2861 / 2672 us, with stored sums
+// 4910 / 4215; 64 of 128x128, forward 118 / 87).
 constexpr int64_t kXcdTiles = 8;
 
-__device__ __forceinline__ int64_t tile_of_block(int64_t i) {
-  const int64_t j = i >> 3;
-  return (j / kXcdTiles * 8 + (i & 7)) * kXcdTiles + j % kXcdTiles;
+__device__ __forceinline__ int64_t tile_of_block(uint32_t i, uint32_t run) {
+  const uint32_t j = i >> 3;
+  return (int64_t)(j / run * 8 + (i & 7)) * run + j % run;
 }
-static int64_t xcd_blocks(int64_t n_tiles) { return ceil_div(n_tiles, 8 * kXcdTiles) * 8 * kXcdTiles; }
+static int64_t xcd_run(int64_t n_tiles, int64_t tiles_per_slot) {
+  const int64_t slots = n_tiles / std::max<int64_t>(tiles_per_slot, 1);
+  return slots > 0 && slots % 8 == 0 ? slots / 8 * tiles_per_slot : kXcdTiles;
+}
 
 // A projected record as three 16-byte words (mean, conic, opacity, rgb).
 struct RawSplat {
@@ -371,6 +378,7 @@ __device__ __forceinline__ void zero_dup_slots(const RasterDev& a, uint32_t star
 struct TileSched {
   const uint32_t* order;   // NULL: XCD-aware default order
   uint32_t* queue;         // non-NULL: persistent launch, items pulled atomically
+  uint32_t run;            // default order: consecutive tiles of an XCD (xcd_run)
 };
 
 // Chunked backward: every tile list is cut into `chunk`-entry work items;
@@ -404,7 +412,7 @@ __device__ __forceinline__ void for_each_tile(const TileSched& sch, int64_t n_ti
   } else {
     // consecutive work-groups of one XCD (ids 8 apart) share a tile
     const uint32_t j = blockIdx.x >> 3;
-    const int64_t tile = tile_of_block((int64_t)(j >> lg) * 8 + (blockIdx.x & 7));
+    const int64_t tile = tile_of_block((j >> lg) * 8 + (blockIdx.x & 7), sch.run);
     if (tile < n_tiles) body(tile, (int)(j & part));
   }
 }
@@ -1825,6 +1833,7 @@ static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, const gs_
   Launch L;
   L.sch.order = plan ? plan->tile_order : nullptr;
   L.sch.queue = plan ? plan->queue : nullptr;
+  L.sch.run = (uint32_t)xcd_run(a.n_tiles, a.tiles_per_slot);
   L.ch.chunk = plan ? plan->chunk : 0;
   L.ch.offset = plan ? plan->chunk_offset : nullptr;
   L.ch.items = plan ? plan->chunk_items : nullptr;
@@ -1837,7 +1846,8 @@ static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, const gs_
   } else if (L.sch.order) {
     L.blocks = (unsigned)std::max<int64_t>(a.n_tiles, 1);
   } else {
-    L.blocks = (unsigned)xcd_blocks(a.n_tiles);
+    const int64_t round = 8 * (int64_t)L.sch.run;
+    L.blocks = (unsigned)(ceil_div(a.n_tiles, round) * round);
   }
   return L;
 }
