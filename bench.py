@@ -196,14 +196,16 @@ def fwd_kernel_name(tile, fwd_waves, sched="default", chunk=0):
     return f"k_raster_fwd<{tile[0]}, {tile[1]}, {nw}>"
 
 
-def bwd_kernel_name(tile, chunk, recompute, deterministic, sched="default", size=None, n_slots=1):
+def bwd_kernel_name(tile, chunk, recompute, deterministic, sched="default", size=None, n_slots=1,
+                    pairs=0):
     """The backward kernel the library launches for this plan."""
     from paper_2509_12138_amd import ops
     if chunk and not recompute:
         if tuple(tile) == (8, 8) and not deterministic:
             return f"k_raster_bwd_chunked_q<{tile[0]}, {tile[1]}>"   # quadrant lane groups
         return f"k_raster_bwd_chunked<{tile[0]}, {tile[1]}>"
-    nk = ops.backward_blocks(tuple(tile), sched, deterministic, size=size, n_slots=n_slots)
+    nk = ops.backward_blocks(tuple(tile), sched, deterministic, size=size, n_slots=n_slots,
+                             pairs=pairs)
     return f"k_raster_bwd<{tile[0]}, {tile[1]}, {nk}, {'true' if recompute else 'false'}>"
 
 
@@ -407,7 +409,8 @@ def batched_main(args):
     k = "raster_bwd" if mean["raster_bwd"] >= mean["raster_fwd"] else "raster_fwd"
     per = OPS_PER_EVAL_BWD if k == "raster_bwd" else OPS_PER_EVAL_FWD
     achieved = blended * per / (total[k] * 1e-3)
-    kname = (bwd_kernel_name(tile, chunk, args.recompute, det, sched, (W, H), tr.S) if k == "raster_bwd"
+    kname = (bwd_kernel_name(tile, chunk, args.recompute, det, sched, (W, H), tr.S, tr.bufs.m)
+             if k == "raster_bwd"
              else fwd_kernel_name(tile, fwd_waves, sched, chunk))
     mpix = tr.S * W * H / ((mean["raster_fwd"] + mean["raster_bwd"]) * 1e-3) / 1e6
     out = {
@@ -557,7 +560,7 @@ def main():
     evals_fwd = evals_bwd = blended
     if dom == "raster_bwd":
         achieved = evals_bwd * OPS_PER_EVAL_BWD / (sums["raster_bwd"] * 1e-3)
-        kname = bwd_kernel_name(tile, chunk, args.recompute, deterministic, sched, (W, H))
+        kname = bwd_kernel_name(tile, chunk, args.recompute, deterministic, sched, (W, H), 1, tr.bufs.m)
         if deterministic:
             kname += "+k_dup_reduce"          # both run inside the timed gs_raster_bwd call
         roof = {"kernel": kname, "bound": "alu", "achieved": achieved / 1e12,

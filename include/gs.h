@@ -267,16 +267,17 @@ typedef struct {
   uint16_t* chunk_last;
 } gs_raster_plan;
 
-/* Which kernels a plan (or NULL) stands for in a call of n_slots images; host
- * calls, no GPU needed, and only whether the plan's pointers are NULL is
- * looked at.
+/* Which kernels a plan (or NULL) stands for in a call of n_slots images and
+ * `pairs` (image, Gaussian) pairs; host calls, no GPU needed, and only whether
+ * the plan's pointers are NULL is looked at.
  * gs_raster_fwd_waves: the waves per tile that gs_raster_fwd launches (its
  * choice where the plan leaves it; 1 for the split forward).
  * gs_raster_bwd_blocks: the 8x8 pixel blocks of a tile that one wave of
  * gs_raster_bwd takes where it walks whole tile lists.
  * Both 0 for a tile shape without a rasteriser.                            */
 int32_t gs_raster_fwd_waves(const gs_tiling* tiling, int32_t n_slots, const gs_raster_plan* plan);
-int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, int32_t n_slots, const gs_raster_plan* plan);
+int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, int32_t n_slots, int64_t pairs,
+                             const gs_raster_plan* plan);
 
 /* Upper bound on the work items of gs_chunk_items for a duplicate capacity. */
 int64_t gs_chunk_max_items(int64_t n_tiles, int64_t dup_capacity, int32_t chunk);

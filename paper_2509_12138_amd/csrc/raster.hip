@@ -1818,18 +1818,35 @@ static int64_t queue_waves(const gs_raster_plan* plan) {
 }
 
 // 8x8 blocks that a wave of the whole-list backward takes: one, or all of its
-// tile where gradients are stored, and with a queue of so few waves that their
-// number and not the longest lists bounds the call: every block stages the
-// tile's whole list.  A wave per block / per tile: 1920x1080, 16 tiles a wave
-// 2302 / 1952 us, 32 4234 / 3564, but 8 tiles 1273 / 1628; 640x360, 14 tiles a
-// wave 1778 / 1562, 4 tiles 514 / 838.
+// tile where gradients are stored, and where the number of waves and not the
+// longest lists bounds the call, since every block stages its tile's whole
+// list.  That is so
+// - with a queue of few waves.  A wave per block / per tile: 1920x1080, 16
+//   tiles a wave 2302 / 1952 us, 32 4234 / 3564, but 8 tiles 1273 / 1628;
+//   640x360, 14 tiles a wave 1778 / 1562, 4 tiles 514 / 838;
+// - of many tiles (from 64 a CU) with short lists (few pairs of an image and a
+//   Gaussian per tile; the more tiles a CU has, the less a long list stands
+//   out), earlier in longest-first order, which ends on short lists.  Images of
+//   1920x1080 in 16x16 tiles, longest first / default order: 4 images, 127 tiles
+//   a CU, 2 pairs a tile 398 / 291 and 475 / 391 us, 24 pairs 733 / 613 and 849 /
+//   940, 122 pairs 1630 / 1714 and 1815 / 2479; 16 images, 510 tiles a CU, 2
+//   pairs 1564 / 930 and 1690 / 1194, 24 pairs 2718 / 2012 and 2823 / 2502, 122
+//   pairs 5818 / 5002 and 6074 / 6387; one image of 3840x2160, 127 tiles a CU,
+//   410 pairs 4948 / 14488 and 6702 / 16139.
 constexpr int64_t kQueueTilesPerWave = 12;
-static int backward_blocks(int tw, int th, int64_t n_tiles, const gs_raster_plan* plan) {
-  const bool per_tile = plan && (plan->dup_grads || (plan->queue && n_tiles > kQueueTilesPerWave * queue_waves(plan)));
+static int backward_blocks(int tw, int th, int64_t n_tiles, int64_t pairs,
+                           const gs_raster_plan* plan) {
+  const int64_t cus = device_cu_count();
+  bool per_tile = plan && plan->dup_grads;
+  if (plan && plan->queue)
+    per_tile |= n_tiles > kQueueTilesPerWave * queue_waves(plan);
+  else if (n_tiles >= 64 * cus)
+    per_tile |= pairs / n_tiles <= n_tiles / cus / (plan && plan->tile_order ? 2 : 8);
   return per_tile ? tw * th / kRasterWave : 1;
 }
 
-static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, const gs_raster_plan* plan) {
+static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, int64_t pairs,
+                          const gs_raster_plan* plan) {
   Launch L;
   L.sch.order = plan ? plan->tile_order : nullptr;
   L.sch.queue = plan ? plan->queue : nullptr;
@@ -1840,7 +1857,7 @@ static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, const gs_
   L.ch.ck = plan && plan->chunk > 0 ? reinterpret_cast<float4*>(plan->checkpoints) : nullptr;
   L.max_items = plan ? plan->max_items : 0;
   L.fwd_waves = forward_waves(tiling->tile_w, tiling->tile_h, plan);
-  L.bwd_blocks = backward_blocks(tiling->tile_w, tiling->tile_h, a.n_tiles, plan);
+  L.bwd_blocks = backward_blocks(tiling->tile_w, tiling->tile_h, a.n_tiles, pairs, plan);
   if (L.sch.queue) {
     L.blocks = (unsigned)std::min<int64_t>(queue_waves(plan), std::max<int64_t>(a.n_tiles, 1));
   } else if (L.sch.order) {
@@ -2008,9 +2025,10 @@ int32_t gs_raster_fwd_waves(const gs_tiling* tiling, int32_t n_slots, const gs_r
   return forward_waves(tiling->tile_w, tiling->tile_h, plan);
 }
 
-int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, int32_t n_slots, const gs_raster_plan* plan) {
+int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, int32_t n_slots, int64_t pairs,
+                             const gs_raster_plan* plan) {
   if (!tiling || !raster_shape_supported(tiling->tile_w, tiling->tile_h)) return 0;
-  return backward_blocks(tiling->tile_w, tiling->tile_h, call_tiles(tiling, n_slots), plan);
+  return backward_blocks(tiling->tile_w, tiling->tile_h, call_tiles(tiling, n_slots), pairs, plan);
 }
 
 gs_status gs_raster_fwd(const gs_projected* proj, const gs_views* views, const gs_tiling* tiling,
@@ -2027,7 +2045,7 @@ gs_status gs_raster_fwd(const gs_projected* proj, const gs_views* views, const g
   hipStream_t s = as_stream(stream);
   st = plan_prepare(plan, tiling, s, "gs_raster_fwd");
   if (st != GS_OK) return st;
-  const Launch L = make_launch(a, tiling, plan);
+  const Launch L = make_launch(a, tiling, proj->m, plan);
   const bool split = split_forward(plan);
   GS_REQUIRE(!split || (plan->chunk_last && T_final),
              "gs_raster_fwd: fwd_split needs chunk_last and the stored state (T_final, n_contrib)");
@@ -2068,7 +2086,7 @@ gs_status gs_raster_bwd(const gs_projected* proj, const gs_views* views, const g
   }
   st = plan_prepare(plan, tiling, s, "gs_raster_bwd");
   if (st != GS_OK) return st;
-  const Launch L = make_launch(a, tiling, plan);
+  const Launch L = make_launch(a, tiling, proj->m, plan);
 #define GS_BWD_CASE(a_, b_)                                                   \
   if (tiling->tile_w == a_ && tiling->tile_h == b_)                           \
     launch_bwd<a_, b_>(a, L, T_final, n_contrib, d_image, mode, d_rec, s);    \

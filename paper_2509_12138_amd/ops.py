@@ -119,6 +119,7 @@ def _plan_kind(mode, chunk, fwd_waves, deterministic):
     set_ = C.c_void_p(1)
     plan = _lib.gs_raster_plan(chunk=int(chunk), fwd_waves=int(fwd_waves))
     plan.queue = set_ if mode == "persistent" else None
+    plan.tile_order = None if mode == "default" else set_
     plan.checkpoints = set_ if chunk else None
     plan.fwd_split = int(mode.endswith("+split"))
     plan.dup_grads = set_ if deterministic else None
@@ -134,12 +135,13 @@ def forward_waves(tile, mode="default", chunk=0, fwd_waves=1, size=None, n_slots
 
 
 def backward_blocks(tile, mode="default", deterministic=False, persistent_waves=0, size=None,
-                    n_slots=1):
-    """8x8 pixel blocks that a wave of the whole-list backward takes."""
+                    n_slots=1, pairs=0):
+    """8x8 pixel blocks that a wave of the whole-list backward takes for n_slots images of
+    size = (width, height) with `pairs` (image, Gaussian) pairs."""
     plan = _plan_kind(mode, 0, 1, deterministic)
     plan.persistent_waves = persistent_waves
     return _lib.load().gs_raster_bwd_blocks(C.byref(tiling_struct(*(size or tile), tile)), n_slots,
-                                            C.byref(plan))
+                                            int(pairs), C.byref(plan))
 
 
 # --------------------------------------------------------------------------

@@ -90,7 +90,25 @@ def test_queue_of_few_waves_takes_tiles(tile, waves):
     # 12 tiles a wave is the line between a wave per 8x8 block and one per tile
     nb = tile[0] * tile[1] // 64
     for tiles, blocks in ((12 * waves, 1), (12 * waves + 1, nb)):
-        size = (tile[0] * tiles, tile[1])
-        assert ops.backward_blocks(tile, "persistent", persistent_waves=waves, size=size) == blocks
-        assert ops.backward_blocks(tile, "lpt", persistent_waves=waves, size=size) == 1
-        assert ops.backward_blocks(tile, "lpt", True, size=size) == nb
+        args = dict(size=(tile[0] * tiles, tile[1]), pairs=10 ** 9)
+        assert ops.backward_blocks(tile, "persistent", persistent_waves=waves, **args) == blocks
+        assert ops.backward_blocks(tile, "lpt", persistent_waves=waves, **args) == 1
+        assert ops.backward_blocks(tile, "lpt", True, **args) == nb
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (8, 8), (32, 16)])
+def test_many_tiles_of_short_lists_take_tiles(tile):
+    # the rule's lines on a device of 256 CUs (the number a host without one assumes)
+    from paper_2509_12138_amd.ops import backward_blocks
+    if pytest.importorskip("torch").cuda.is_available():
+        pytest.skip("the CU count is the device's")
+    nb = tile[0] * tile[1] // 64
+    for per_cu, slots in ((63, 1), (64, 1), (64, 4), (512, 32)):
+        tiles = 256 * per_cu
+        size = (tile[0] * tiles // slots, tile[1])
+        for mode, div in (("lpt", 2), ("default", 8)):
+            line = per_cu // div
+            args = dict(size=size, n_slots=slots)
+            few = nb if per_cu >= 64 else 1
+            assert backward_blocks(tile, mode, pairs=tiles * line, **args) == few
+            assert backward_blocks(tile, mode, pairs=tiles * (line + 1), **args) == 1
