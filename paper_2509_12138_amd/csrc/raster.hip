@@ -880,8 +880,11 @@ constexpr int64_t kBwdShareWavesPerCu = 32;
 // only: those, their reduction and the atomics are two thirds of a visit.
 // 128x128 with 64 tiles (8 waves a block): 131 -> 76 us; 333x251 with 336
 // tiles (4): 174 -> 130.
+// Four blocks a wave are compiled for five waves a SIMD (at 97 VGPRs, one too
+// many, the replaying form had four: 16 sparse images of 1920x1080 1352 -> 1249).
 template <int TW, int TH, int NK, bool RECOMPUTE>
-__global__ __launch_bounds__(kRasterWave) void k_raster_bwd(RasterDev a, TileSched sch,
+__global__ __launch_bounds__(kRasterWave)
+__attribute__((amdgpu_waves_per_eu(NK == 4 ? 5 : 1))) void k_raster_bwd(RasterDev a, TileSched sch,
                                                             int lg_share,
                                                             const float* __restrict__ T_final,
                                                             const int32_t* __restrict__ n_contrib,
@@ -1824,15 +1827,21 @@ static int64_t queue_waves(const gs_raster_plan* plan) {
 // - with a queue of few waves.  A wave per block / per tile: 1920x1080, 16
 //   tiles a wave 2302 / 1952 us, 32 4234 / 3564, but 8 tiles 1273 / 1628;
 //   640x360, 14 tiles a wave 1778 / 1562, 4 tiles 514 / 838;
-// - of many tiles (from 64 a CU) with short lists (few pairs of an image and a
-//   Gaussian per tile; the more tiles a CU has, the less a long list stands
-//   out), earlier in longest-first order, which ends on short lists.  Images of
-//   1920x1080 in 16x16 tiles, longest first / default order: 4 images, 127 tiles
-//   a CU, 2 pairs a tile 398 / 291 and 475 / 391 us, 24 pairs 733 / 613 and 849 /
-//   940, 122 pairs 1630 / 1714 and 1815 / 2479; 16 images, 510 tiles a CU, 2
-//   pairs 1564 / 930 and 1690 / 1194, 24 pairs 2718 / 2012 and 2823 / 2502, 122
-//   pairs 5818 / 5002 and 6074 / 6387; one image of 3840x2160, 127 tiles a CU,
-//   410 pairs 4948 / 14488 and 6702 / 16139.
+// - of many tiles (from 64 a CU) with few pairs of an image and a Gaussian per
+//   tile; the more tiles a CU has, the less a long list stands out.  Earlier in
+//   longest-first order, which ends on short lists.  Images of 1920x1080 in
+//   16x16 tiles, longest first / default order: 4 images, 127 tiles a CU, 2
+//   pairs a tile 398 / 291 and 475 / 391 us, 24 pairs 733 / 613 and 849 / 940,
+//   122 pairs 1630 / 1714 and 1815 / 2479; 16 images, 510 tiles a CU, 2 pairs
+//   1564 / 930 and 1690 / 1194, 24 pairs 2718 / 2012 and 2823 / 2502, 122 pairs
+//   5818 / 5002 and 6074 / 6387; of 3840x2160, one image, 127 tiles a CU, 410
+//   pairs 4948 / 14488 and 6702 / 16139; eight, 1012 and 123 in the default
+//   order 8486 / 12725.  (An object on a tenth of the image has fewer tiles at
+//   work than the call has, and would keep its blocks longer: 4 images of
+//   3840x2160 with 31 pairs a tile 1303 / 2906.  The host does not know that;
+//   the wave per tile is then as fast as the kernel without blocks was, 2896.
+//   Long lists by blocks and short ones by tiles, in two launches, gave none of
+//   the cases above its better time.)
 constexpr int64_t kQueueTilesPerWave = 12;
 static int backward_blocks(int tw, int th, int64_t n_tiles, int64_t pairs,
                            const gs_raster_plan* plan) {
@@ -1841,7 +1850,7 @@ static int backward_blocks(int tw, int th, int64_t n_tiles, int64_t pairs,
   if (plan && plan->queue)
     per_tile |= n_tiles > kQueueTilesPerWave * queue_waves(plan);
   else if (n_tiles >= 64 * cus)
-    per_tile |= pairs / n_tiles <= n_tiles / cus / (plan && plan->tile_order ? 2 : 8);
+    per_tile |= pairs / n_tiles <= n_tiles / cus / (plan && plan->tile_order ? 2 : 16);
   return per_tile ? tw * th / kRasterWave : 1;
 }
 

@@ -106,7 +106,7 @@ def test_many_tiles_of_short_lists_take_tiles(tile):
     for per_cu, slots in ((63, 1), (64, 1), (64, 4), (512, 32)):
         tiles = 256 * per_cu
         size = (tile[0] * tiles // slots, tile[1])
-        for mode, div in (("lpt", 2), ("default", 8)):
+        for mode, div in (("lpt", 2), ("default", 16)):
             line = per_cu // div
             args = dict(size=size, n_slots=slots)
             few = nb if per_cu >= 64 else 1
