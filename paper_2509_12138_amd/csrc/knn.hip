@@ -12,12 +12,14 @@
 //   k_query                          one thread per point, in cell order for
 //                                    cache locality: the 3x3x3 box around the
 //                                    point's cell, then growing Chebyshev
-//                                    shells (of cells, then of blocks of
-//                                    cells), until the k-th best distance is
-//                                    within the distance to the searched box
-//                                    (exact); the K best (distance^2, index)
-//                                    pairs stay sorted in registers, ties
-//                                    broken by index.
+//                                    shells of cells, until the k-th best
+//                                    distance is within the distance to the
+//                                    searched box (exact); the K best
+//                                    (distance^2, index) pairs stay sorted in
+//                                    registers, ties broken by index.
+//   k_query_far                      a wave for each point whose neighbours
+//                                    are beyond those shells: shells of blocks
+//                                    of cells.
 #include <math.h>
 
 #include <algorithm>
@@ -597,57 +599,128 @@ __global__ __launch_bounds__(kKnnThreads) void k_query(const float4* __restrict_
   knn_write(best, qi, k, idx, dist, mean_dist);
 }
 
-// The points that k_query left: shells of blocks of cells, of which the empty
-// ones and those beyond the K-th distance are passed over.
-template <int K>
+// The points that k_query left: a wave each, over shells of blocks of cells.
+// The lanes test a shell's blocks together (the empty ones and those beyond
+// the k-th distance are passed over), then the points of a block, and lane t
+// holds the t-th best key, which a better one moves up by a lane.  Bound by a
+// point's chain of loads, some 2000 blocks for an outlier.  A thread per point
+// and a wave per point, whole call: 30,000 points of a normal distribution,
+// k = 3 939 -> 218 us, k = 16 1720 -> 432; 300,007 of a long-tailed one, k = 16
+// 253 -> 87 ms; but where tens of thousands of points are left, a thread each
+// fills the chip (300,007 of a square, k = 32 732 -> 1019 us).
 __global__ __launch_bounds__(kKnnThreads) void k_query_far(
     const float4* __restrict__ sorted, int k, const GridParams* __restrict__ P,
     const uint32_t* __restrict__ start, const uint8_t* __restrict__ block,
     const uint32_t* __restrict__ far, int32_t* __restrict__ idx, float* __restrict__ dist,
     float* __restrict__ mean_dist) {
   const GridParams G = *P;
+  const int lane = threadIdx.x & 63;
   auto slab = [&](float x, float lo, int b) {
     const float e0 = lo + (float)(b * kBlock) * G.h, e1 = e0 + (float)kBlock * G.h;
     const float d = fmaxf(e0 - x, x - e1);
     return fmaxf(d - (1e-3f * G.h + 1e-6f * (fabsf(e0) + fabsf(e1))), 0.0f);
   };
-  for (uint32_t i = blockIdx.x * kKnnThreads + threadIdx.x; i < G.n_far;
-       i += gridDim.x * kKnnThreads) {
+  const uint32_t waves = gridDim.x * (kKnnThreads / 64);
+  for (uint32_t i = blockIdx.x * (kKnnThreads / 64) + (threadIdx.x >> 6); i < G.n_far; i += waves) {
     const float4 q = sorted[far[i]];
     const int qi = __float_as_int(q.w);
     const int bx = cell_coord(q.x, G.lo[0], G.inv_h, G.g[0]) >> kBlockShift;
     const int by = cell_coord(q.y, G.lo[1], G.inv_h, G.g[1]) >> kBlockShift;
     const int bz = cell_coord(q.z, G.lo[2], G.inv_h, G.g[2]) >> kBlockShift;
-    uint64_t best[K];
-#pragma unroll
-    for (int t = 0; t < K; ++t) best[t] = kNoNeighbour;
-#pragma unroll 1
-    for (int r = 0;; ++r) {
-      for (int z = max(bz - r, 0); z <= min(bz + r, G.bg[2] - 1); ++z)
-        for (int y = max(by - r, 0); y <= min(by + r, G.bg[1] - 1); ++y) {
-          const bool whole = abs(z - bz) == r || abs(y - by) == r;
-          for (int x = bx - r; x <= bx + r; x += whole ? 1 : 2 * r) {
-            if (x < 0 || x >= G.bg[0]) continue;
-            if (!block[((int64_t)z * G.bg[1] + y) * G.bg[0] + x]) continue;
-            const float fx = slab(q.x, G.lo[0], x), fy = slab(q.y, G.lo[1], y),
-                        fz = slab(q.z, G.lo[2], z);
-            if (fmaf(fx, fx, fmaf(fy, fy, fz * fz)) * 0.9999f > knn_bound(best)) continue;
-            const int x0 = x * kBlock, x1 = min(x0 + kBlock, G.g[0]);
-            for (int cz = z * kBlock; cz < min((z + 1) * kBlock, G.g[2]); ++cz)
-              for (int cy = y * kBlock; cy < min((y + 1) * kBlock, G.g[1]); ++cy) {
-                const int64_t row = ((int64_t)cz * G.g[1] + cy) * G.g[0];
-                knn_scan(best, q, qi, sorted, start[row + x0], start[row + x1]);
-              }
+    uint64_t best = kNoNeighbour;
+    uint64_t kth = kNoNeighbour;              // lane k - 1's
+    auto visit = [&](int x, int y, int z) {   // the points of a block
+      const int x0 = x * kBlock, x1 = min(x0 + kBlock, G.g[0]);
+      // the start and end of row l of its kBlock^2 rows of cells, in lane l
+      const int cy = y * kBlock + (lane & (kBlock - 1)), cz = z * kBlock + (lane >> kBlockShift);
+      uint32_t r0 = 0, r1 = 0;
+      if (lane < kBlock * kBlock && cy < G.g[1] && cz < G.g[2]) {
+        const int64_t row = ((int64_t)cz * G.g[1] + cy) * G.g[0];
+        r0 = start[row + x0];
+        r1 = start[row + x1];
+      }
+      for (uint64_t rows = __ballot(r1 > r0); rows; rows &= rows - 1) {
+        const int l = (int)__builtin_ctzll(rows);
+        const uint32_t j0 = __builtin_amdgcn_readlane(r0, l), j1 = __builtin_amdgcn_readlane(r1, l);
+        for (uint32_t j = j0; j < j1; j += 64) {
+          uint64_t key = kNoNeighbour;
+          if (j + lane < j1) {
+            const float4 p = sorted[j + lane];
+            const int pj = __float_as_int(p.w);
+            const float dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
+            const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            if (d2 <= INFINITY && pj != qi) key = knn_key(d2, pj);
+          }
+          for (uint64_t todo = __ballot(key < kth); todo; todo &= todo - 1) {
+            const int c = (int)__builtin_ctzll(todo);
+            const uint64_t n = __shfl(key, c, 64);
+            if (n >= kth) continue;           // one before it moved the k-th below it
+            const uint64_t below = __shfl_up(best, 1, 64);
+            if (n < best) best = lane > 0 && n < below ? below : n;
+            kth = __shfl(best, k - 1, 64);
           }
         }
+      }
+    };
+    // the blocks [xa, xb] x [ya, yb] x [za, zb] of the grid, one of the three
+    // ranges a single block
+    auto face = [&](int xa, int xb, int ya, int yb, int za, int zb) {
+      const int nx = xb - xa + 1, ny = yb - ya + 1, nz = zb - za + 1;
+      if (nx <= 0 || ny <= 0 || nz <= 0) return;
+      const int64_t blocks = (int64_t)nx * ny * nz;
+      for (int64_t b0 = 0; b0 < blocks; b0 += 64) {
+        const uint32_t f = (uint32_t)min(b0 + lane, blocks - 1);
+        const int x = xa + (int)(f % nx), y = ya + (int)(f / nx % ny), z = za + (int)(f / nx / ny);
+        const bool hit = b0 + lane < blocks &&
+                         block[((int64_t)z * G.bg[1] + y) * G.bg[0] + x] != 0;
+        const float fx = slab(q.x, G.lo[0], x), fy = slab(q.y, G.lo[1], y),
+                    fz = slab(q.z, G.lo[2], z);
+        const float reach = fmaf(fx, fx, fmaf(fy, fy, fz * fz)) * 0.9999f;
+        for (uint64_t todo = __ballot(hit); todo; todo &= todo - 1) {
+          const int c = (int)__builtin_ctzll(todo);
+          if (__shfl(reach, c, 64) > __uint_as_float((uint32_t)(kth >> 32))) continue;
+          visit(__builtin_amdgcn_readlane(x, c), __builtin_amdgcn_readlane(y, c),
+                __builtin_amdgcn_readlane(z, c));
+        }
+      }
+    };
+#pragma unroll 1
+    for (int r = 0;; ++r) {
+      // the shell of blocks at Chebyshev distance r, face by face
+      const int x0 = max(bx - r, 0), x1 = min(bx + r, G.bg[0] - 1);
+      const int y0 = max(by - r, 0), y1 = min(by + r, G.bg[1] - 1);
+      const int yi0 = max(by - r + 1, 0), yi1 = min(by + r - 1, G.bg[1] - 1);
+      const int zi0 = max(bz - r + 1, 0), zi1 = min(bz + r - 1, G.bg[2] - 1);
+#pragma unroll 1
+      for (int f = 0; f < (r ? 6 : 1); ++f) {
+        const int d = f & 1 ? r : -r;
+        const bool fz = f < 2, fy = f >= 2 && f < 4, fx = f >= 4;
+        const int at = fz ? bz + d : (fy ? by + d : bx + d);
+        if (at < 0 || at >= (fz ? G.bg[2] : (fy ? G.bg[1] : G.bg[0]))) continue;
+        face(fx ? at : x0, fx ? at : x1, fy ? at : (fx ? yi0 : y0), fy ? at : (fx ? yi1 : y1),
+             fz ? at : zi0, fz ? at : zi1);
+      }
       const int r1 = r + 1;
-      const float wall = fminf(
+      const float wall = fmaxf(fminf(
           knn_wall(q.x, G.lo[0], G.h, G.g[0], (bx - r) * kBlock, (bx + r1) * kBlock - 1),
           fminf(knn_wall(q.y, G.lo[1], G.h, G.g[1], (by - r) * kBlock, (by + r1) * kBlock - 1),
-                knn_wall(q.z, G.lo[2], G.h, G.g[2], (bz - r) * kBlock, (bz + r1) * kBlock - 1)));
-      if (knn_done(best, k, wall)) break;    // (true once the whole grid is searched)
+                knn_wall(q.z, G.lo[2], G.h, G.g[2], (bz - r) * kBlock, (bz + r1) * kBlock - 1))), 0.0f);
+      // (true once the whole grid is searched)
+      if (__uint_as_float((uint32_t)(kth >> 32)) <= wall * wall * 0.9999f || wall == INFINITY) break;
     }
-    knn_write(best, qi, k, idx, dist, mean_dist);
+    const bool has = best != kNoNeighbour;
+    const float d = sqrtf(__uint_as_float((uint32_t)(best >> 32)));
+    if (lane < k) {
+      const int64_t o = (int64_t)qi * k + lane;
+      if (idx) idx[o] = has ? (int)(uint32_t)best : -1;
+      if (dist) dist[o] = d;
+    }
+    if (mean_dist) {                          // nearest first
+      const int found = (int)__builtin_popcountll(__ballot(lane < k && has));
+      float sum = 0.0f;
+      for (int t = 0; t < found; ++t) sum += lane_f(d, t);
+      if (lane == 0) mean_dist[qi] = found ? sum / (float)found : 0.0f;
+    }
   }
 }
 
@@ -748,19 +821,21 @@ gs_status gs_knn(const float* pts, int64_t n, int32_t k, void* ws, size_t ws_byt
   // (the cells of the points are not needed any more: their array takes the
   // list of far points)
   uint32_t* far = cell;
-  const unsigned nb_far = (unsigned)std::min<int64_t>(L.nb_pts, 4 * (int64_t)device_cu_count());
+  const unsigned nb_far =
+      (unsigned)std::min<int64_t>(ceil_div(n, kKnnThreads / 64), 8 * (int64_t)device_cu_count());
   auto query = [&](auto KK) {
     constexpr int K = decltype(KK)::value;
     hipLaunchKernelGGL(k_query<K>, dim3(nb), dim3(kKnnThreads), 0, s, sorted, n, k, P, count, far,
                        idx, dist, mean_dist);
-    hipLaunchKernelGGL(k_query_far<K>, dim3(nb_far), dim3(kKnnThreads), 0, s, sorted, k, P, count,
-                       block, far, idx, dist, mean_dist);
   };
   if (k <= 4) query(std::integral_constant<int, 4>{});
   else if (k <= 8) query(std::integral_constant<int, 8>{});
   else if (k <= 16) query(std::integral_constant<int, 16>{});
   else query(std::integral_constant<int, 32>{});
   GS_LAUNCH_CHECK("gs_knn/query");
+  hipLaunchKernelGGL(k_query_far, dim3(nb_far), dim3(kKnnThreads), 0, s, sorted, k, P, count,
+                     block, far, idx, dist, mean_dist);
+  GS_LAUNCH_CHECK("gs_knn/far");
   return GS_OK;
 }
 
