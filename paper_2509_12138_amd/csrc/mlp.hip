@@ -30,6 +30,8 @@
 //   gs_mlp_apply     network output -> initial Gaussian parameters
 #include <math.h>
 
+#include <algorithm>
+
 #include "gs_device.h"
 
 namespace gsmi {
@@ -654,16 +656,14 @@ __device__ __forceinline__ void rotm_to_quat(const float R[9], float q[4]) {
 // points: 1483 -> 545 us).
 constexpr int kNb = 16;
 
-__global__ __launch_bounds__(256) void k_mlp_features(const float* __restrict__ pts,
-                                                      const float* __restrict__ nrm, int64_t n,
-                                                      const int32_t* __restrict__ idx,
-                                                      const float* __restrict__ dist,
-                                                      uint16_t* __restrict__ x,
-                                                      float* __restrict__ dbar) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void point_feature(const float* __restrict__ pts,
+                                              const float* __restrict__ nrm, int64_t n,
+                                              const int32_t* __restrict__ idx,
+                                              const float* __restrict__ dist,
+                                              uint16_t* __restrict__ x, float* __restrict__ dbar,
+                                              int64_t e) {
   const int64_t i = e / kNb;
   const int k = threadIdx.x % kNb;
-  if (i >= n) return;
   const int j = idx[e];
   const float d = j >= 0 ? dist[e] : 0.0f;
   // the sum in list order: every lane adds the 16 values one after the other
@@ -695,6 +695,20 @@ __global__ __launch_bounds__(256) void k_mlp_features(const float* __restrict__ 
 #pragma unroll
   for (int a = 0; a < 3; ++a)
     xr[a] = (uint32_t)f2bf(f[2 * a]) | ((uint32_t)f2bf(f[2 * a + 1]) << 16);
+}
+
+// A launch holds at most 2^32 - 1 threads, so the grid is bounded and walks on.
+constexpr int64_t kFeatureBlocks = 1 << 18;
+
+__global__ __launch_bounds__(256) void k_mlp_features(const float* __restrict__ pts,
+                                                      const float* __restrict__ nrm, int64_t n,
+                                                      const int32_t* __restrict__ idx,
+                                                      const float* __restrict__ dist,
+                                                      uint16_t* __restrict__ x,
+                                                      float* __restrict__ dbar) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n * kNb;
+       e += (int64_t)gridDim.x * 256)
+    point_feature(pts, nrm, n, idx, dist, x, dbar, e);
 }
 
 // ---------------------------------------------------------------- targets
@@ -842,7 +856,8 @@ gs_status gs_mlp_features(const float* pts, const float* normals, int64_t n, con
   GS_REQUIRE(pts && normals && knn_idx && knn_dist && x_bf16 && dbar,
              "gs_mlp_features: NULL argument");
   GS_REQUIRE(((uintptr_t)x_bf16 & 15) == 0, "gs_mlp_features: x must be 16-byte aligned");
-  hipLaunchKernelGGL(k_mlp_features, dim3((unsigned)ceil_div(n * kNb, 256)), dim3(256), 0,
+  hipLaunchKernelGGL(k_mlp_features,
+                     dim3((unsigned)std::min(ceil_div(n * kNb, 256), kFeatureBlocks)), dim3(256), 0,
                      as_stream(stream), pts, normals, n, knn_idx, knn_dist, x_bf16, dbar);
   GS_LAUNCH_CHECK("gs_mlp_features");
   return GS_OK;
