@@ -1802,17 +1802,25 @@ static bool split_forward(const gs_raster_plan* plan) {
   return plan && plan->fwd_split && plan->chunk > 0 && plan->checkpoints;
 }
 
+// Whether a launch of `waves` waves for each of n_tiles tiles (and the rounding
+// of the default order) holds at most 2^32 - 1 threads.
+static bool launch_fits(int64_t n_tiles, int64_t waves) {
+  return (n_tiles + 64) * waves * kRasterWave < (int64_t(1) << 32);
+}
+
 // Waves per tile of the forward.  Where the plan leaves the choice (fwd_waves
 // 0 or 1, no queue): the most that the tile's pixels allow, one 8x8 block each
 // for 16x16 tiles.  A wave's time is its list's length times its visits' cost,
 // and both the pixels per lane and the entries that reach its box fall with
 // more waves (one against the most): 1920x1080 in 16x16 tiles 946 / 225 us, 32
 // images of 640x360 1526 / 508, 333x251 224 / 65, 128x128 137 / 48.
-static int forward_waves(int tw, int th, const gs_raster_plan* plan) {
+static int forward_waves(int tw, int th, int64_t n_tiles, const gs_raster_plan* plan) {
   if (split_forward(plan) || (plan && plan->queue)) return 1;
   if (plan && plan->fwd_waves > 1) return plan->fwd_waves;
   const int px = tw * th / kRasterWave;
-  return px % 4 == 0 ? 4 : (px % 2 == 0 ? 2 : 1);
+  int nw = px % 4 == 0 ? 4 : (px % 2 == 0 ? 2 : 1);
+  while (nw > 1 && !launch_fits(n_tiles, nw)) nw /= 2;
+  return nw;
 }
 
 // The grid of a queue's plan, at most.
@@ -1846,7 +1854,7 @@ constexpr int64_t kQueueTilesPerWave = 12;
 static int backward_blocks(int tw, int th, int64_t n_tiles, int64_t pairs,
                            const gs_raster_plan* plan) {
   const int64_t cus = device_cu_count();
-  bool per_tile = plan && plan->dup_grads;
+  bool per_tile = (plan && plan->dup_grads) || !launch_fits(n_tiles, tw * th / kRasterWave);
   if (plan && plan->queue)
     per_tile |= n_tiles > kQueueTilesPerWave * queue_waves(plan);
   else if (n_tiles >= 64 * cus)
@@ -1865,7 +1873,7 @@ static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, int64_t p
   L.ch.items = plan ? plan->chunk_items : nullptr;
   L.ch.ck = plan && plan->chunk > 0 ? reinterpret_cast<float4*>(plan->checkpoints) : nullptr;
   L.max_items = plan ? plan->max_items : 0;
-  L.fwd_waves = forward_waves(tiling->tile_w, tiling->tile_h, plan);
+  L.fwd_waves = forward_waves(tiling->tile_w, tiling->tile_h, a.n_tiles, plan);
   L.bwd_blocks = backward_blocks(tiling->tile_w, tiling->tile_h, a.n_tiles, pairs, plan);
   if (L.sch.queue) {
     L.blocks = (unsigned)std::min<int64_t>(queue_waves(plan), std::max<int64_t>(a.n_tiles, 1));
@@ -2029,9 +2037,8 @@ static int64_t call_tiles(const gs_tiling* t, int32_t n_slots) {
 }
 
 int32_t gs_raster_fwd_waves(const gs_tiling* tiling, int32_t n_slots, const gs_raster_plan* plan) {
-  (void)n_slots;
   if (!tiling || !raster_shape_supported(tiling->tile_w, tiling->tile_h)) return 0;
-  return forward_waves(tiling->tile_w, tiling->tile_h, plan);
+  return forward_waves(tiling->tile_w, tiling->tile_h, call_tiles(tiling, n_slots), plan);
 }
 
 int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, int32_t n_slots, int64_t pairs,

@@ -112,3 +112,17 @@ def test_many_tiles_of_short_lists_take_tiles(tile):
             few = nb if per_cu >= 64 else 1
             assert backward_blocks(tile, mode, pairs=tiles * line, **args) == few
             assert backward_blocks(tile, mode, pairs=tiles * (line + 1), **args) == 1
+
+
+def test_launches_hold_their_threads():
+    # a launch takes at most 2^32 - 1 threads, 64 a wave: 16x16 tiles of one 65536x65536 image are
+    # 2^24, of which four waves each are one thread too many
+    big, n = (65536, 65536), 10 ** 12
+    below = (65536, 65520 - 16)
+    assert ops.forward_waves((16, 16), size=big) == 2 and ops.forward_waves((16, 16), size=below) == 4
+    assert ops.forward_waves((16, 16), size=big, n_slots=2) == 1
+    assert ops.backward_blocks((16, 16), size=big, pairs=n) == 4
+    assert ops.backward_blocks((16, 16), size=below, pairs=n) == 1
+    assert ops.forward_waves((32, 16), size=big) == 4
+    assert ops.backward_blocks((32, 16), size=big, pairs=n) == 8      # 2^23 tiles of 8 blocks
+    assert ops.backward_blocks((8, 8), size=big, pairs=n) == 1
