@@ -1005,8 +1005,6 @@ __device__ __forceinline__ int row_slot9(int l) {
 //
 // A lane owns pixel p = lane: quadrant p / 16 (2 x 2 of them), in it column
 // p % 4 and row p % 16 / 4.
-__device__ __forceinline__ int quad_x(int p) { return ((p >> 2) & 4) | (p & 3); }
-__device__ __forceinline__ int quad_y(int p) { return ((p >> 3) & 4) | ((p >> 2) & 3); }
 
 // The pixels (bit p) of the 8x8 block with pixel-centre origin (x0, y0) that
 // may pass the alpha test: of every row the interval in which A dx^2 + B dx dy
