@@ -424,7 +424,8 @@ gs_status gs_adam(const gs_adam_group* groups, int32_t n_groups, float beta1,
                   float beta2, float eps, int32_t step, int32_t zero_grad,
                   void* stream);
 
-/* Workspace for gs_knn on n points.                                         */
+/* Workspace for gs_knn on n points: about 92 bytes a point (1.5 GB for 16
+ * million), 64 of them the counts of a grid of up to 16 cells a point.     */
 size_t gs_knn_workspace_bytes(int64_t n, int32_t k);
 
 /* Exact k nearest neighbours of every point among the other points

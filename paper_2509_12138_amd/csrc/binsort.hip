@@ -454,9 +454,10 @@ __global__ __launch_bounds__(256) void k_depth_keys(const float* __restrict__ re
 // The depth presort of up to kSmallSort pairs in one work-group: a bitonic
 // sort of (key, pair index) words in LDS, whose order is that of the stable
 // radix passes.  Those are 12 launches of 2 to 8 us that a few blocks of keys
-// do not fill: 4096 pairs 54 us, here 35, bound by the LDS (78 steps that read
-// and write up to 32 KB); at twice the pairs the steps would cost more than
-// the passes.
+// do not fill; this is bound by the LDS (78 steps at 4096 pairs, that read and
+// write up to 32 KB).  The whole bin/sort call, here / by the passes: 256 pairs
+// 35 / 68 us, 1024 46 / 76, 2048 53 / 79, 3000 67 / 82, 4096 68 / 84, but 6000
+// 100 / 83 and 8192 101 / 82, as the steps run over the next power of two.
 constexpr int kSmallSort = 4096;
 constexpr int kSmallSortThreads = 1024;
 
