@@ -65,13 +65,19 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_scatter(const uint32_t*
   if (t < n_tiles) order[base[b] + local] = (uint32_t)t;
 }
 
-// Adds the wave's bucket numbers to the LDS counts h, one atomic per distinct
-// bucket (most tiles of a wave share a few: empty ones, background), and
-// returns each lane's place: the count before it.  b < 0: not counted.
+// Adds the wave's bucket numbers to the LDS counts h and returns each lane's
+// place: the count before it.  b < 0: not counted.  One atomic for each of the
+// kShared first buckets that the wave holds (most tiles of a wave share a few:
+// empty ones, background), then one a lane for the rest.  An atomic for every
+// bucket that it holds / this: 8160 tiles of an image 12.7 / 9.0 us, but of
+// random lengths 18.4 / 10.3 (one a lane from the start: 13.4 and 8.8).
+constexpr int kShared = 2;
 __device__ __forceinline__ uint32_t wave_bucket_add(uint32_t* h, int b) {
   uint32_t place = 0;
   uint64_t todo = __ballot(b >= 0);
-  while (todo) {
+#pragma unroll
+  for (int i = 0; i < kShared; ++i) {
+    if (!todo) break;
     const int lead = (int)__builtin_ctzll(todo);
     const int b0 = __builtin_amdgcn_readlane(b, lead);
     const uint64_t same = __ballot(b == b0);
@@ -84,6 +90,7 @@ __device__ __forceinline__ uint32_t wave_bucket_add(uint32_t* h, int b) {
       place = (uint32_t)__builtin_amdgcn_readlane((int)base, lead) + rank;
     }
   }
+  if (todo >> (threadIdx.x & 63) & 1) place = atomicAdd(&h[b], 1u);
   return place;
 }
 
@@ -91,9 +98,9 @@ __device__ __forceinline__ uint32_t wave_bucket_add(uint32_t* h, int b) {
 // counts in LDS, the descending-cost starts, then every tile's slot from an
 // LDS cursor per bucket (no workspace, one launch).  Bound by its chain of
 // loads and LDS atomics, so kOrderEach ranges a thread are loaded together and
-// a wave issues one atomic per bucket it holds (one atomic a tile, whose
-// lanes meet in a few buckets and queue there: 29,440 tiles 50 us, now 36; 8160
-// 13.4, now 12.7).  More tiles than kOrderOneMax take the three grids above,
+// a wave's tiles of one bucket share an atomic (one atomic a tile, whose lanes
+// meet in a few buckets and queue there: 29,440 tiles of images 50 us, so 36;
+// 8160 13.4, so 9.0).  More tiles than kOrderOneMax take the three grids above,
 // which need a cleared workspace: 29,440 tiles 18 us.
 constexpr int kOrderOneThreads = 1024;
 constexpr int64_t kOrderOneMax = 16384;
