@@ -187,12 +187,14 @@ def timed_steps(tr, order, first, steps):
     return wall * 1000.0 / steps, mean, total, event_views
 
 
-def fwd_kernel_name(tile, fwd_waves, sched="default", chunk=0):
+def fwd_kernel_name(tile, fwd_waves, sched="default", chunk=0, size=None, n_slots=1, pairs=10 ** 9):
     """The forward kernel(s) the library launches for this plan."""
     from paper_2509_12138_amd import ops
     if sched.endswith("+split") and chunk:
-        return f"k_raster_fwd_part<{tile[0]}, {tile[1]}>+k_raster_fwd_join<{tile[0]}, {tile[1]}>"
-    nw = ops.forward_waves(tuple(tile), sched, chunk, fwd_waves)
+        many = "true" if ops.join_many(tuple(tile), size, n_slots, pairs) else "false"
+        return (f"k_raster_fwd_part<{tile[0]}, {tile[1]}>+"
+                f"k_raster_fwd_join<{tile[0]}, {tile[1]}, {many}>")
+    nw = ops.forward_waves(tuple(tile), sched, chunk, fwd_waves, size, n_slots)
     return f"k_raster_fwd<{tile[0]}, {tile[1]}, {nw}>"
 
 
@@ -411,7 +413,7 @@ def batched_main(args):
     achieved = blended * per / (total[k] * 1e-3)
     kname = (bwd_kernel_name(tile, chunk, args.recompute, det, sched, (W, H), tr.S, tr.bufs.m)
              if k == "raster_bwd"
-             else fwd_kernel_name(tile, fwd_waves, sched, chunk))
+             else fwd_kernel_name(tile, fwd_waves, sched, chunk, (W, H), tr.S, tr.bufs.m))
     mpix = tr.S * W * H / ((mean["raster_fwd"] + mean["raster_bwd"]) * 1e-3) / 1e6
     out = {
         "metric": METRIC,
@@ -569,7 +571,8 @@ def main():
                 "unit_desc": f"{OPS_PER_EVAL_BWD} FP32 VALU issue slots per blended (pixel, Gaussian)"}
     else:
         achieved = evals_fwd * OPS_PER_EVAL_FWD / (sums["raster_fwd"] * 1e-3)
-        roof = {"kernel": fwd_kernel_name(tile, fwd_waves, sched, chunk), "bound": "alu",
+        roof = {"kernel": fwd_kernel_name(tile, fwd_waves, sched, chunk, (W, H), 1, tr.bufs.m),
+                "bound": "alu",
                 "achieved": achieved / 1e12,
                 "peak": PEAK_VALU_OPS / 1e12, "unit": "TOP/s", "frac": achieved / PEAK_VALU_OPS,
                 "traffic": None, "units_per_launch": evals_fwd / len(timed_views),

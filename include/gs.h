@@ -272,10 +272,13 @@ typedef struct {
  * the plan's pointers are NULL is looked at.
  * gs_raster_fwd_waves: the waves per tile that gs_raster_fwd launches (its
  * choice where the plan leaves it; 1 for the split forward).
+ * gs_raster_join_many: whether the split forward's join visits a stopping
+ * chunk's entries with all lanes (1) or pixel by pixel (0).
  * gs_raster_bwd_blocks: the 8x8 pixel blocks of a tile that one wave of
  * gs_raster_bwd takes where it walks whole tile lists.
- * Both 0 for a tile shape without a rasteriser.                            */
+ * All 0 for a tile shape without a rasteriser.                            */
 int32_t gs_raster_fwd_waves(const gs_tiling* tiling, int32_t n_slots, const gs_raster_plan* plan);
+int32_t gs_raster_join_many(const gs_tiling* tiling, int32_t n_slots, int64_t pairs);
 int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, int32_t n_slots, int64_t pairs,
                              const gs_raster_plan* plan);
 

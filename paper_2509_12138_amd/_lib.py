@@ -91,6 +91,7 @@ SIGNATURES = {
                             vp, i32, vp, P(gs_raster_plan), vp]),
     "gs_raster_count": (i32, [P(gs_projected), P(gs_views), P(gs_tiling), vp, vp, vp, vp]),
     "gs_raster_fwd_waves": (i32, [P(gs_tiling), i32, P(gs_raster_plan)]),
+    "gs_raster_join_many": (i32, [P(gs_tiling), i32, i64]),
     "gs_raster_bwd_blocks": (i32, [P(gs_tiling), i32, i64, P(gs_raster_plan)]),
     "gs_tile_order_workspace_bytes": (sz, [i64]),
     "gs_chunk_max_items": (i64, [i64, i64, i32]),

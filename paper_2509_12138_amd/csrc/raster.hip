@@ -1494,7 +1494,9 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_part(RasterDev a, Ch
 // keep D chunks' loads in flight: a long list's join is a chain of
 // dependent loads otherwise (lists of 450 chunks at 4K: D 4 -> 8, 945 -> 776
 // us).
-template <int TW, int TH>
+// MANY: with few large splats most pixels of a tile stop in the same chunk, and
+// all lanes visit its entries after all (join_many).
+template <int TW, int TH, bool MANY>
 __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
     RasterDev a, TileSched sch, ChunkDev ch, const uint16_t* __restrict__ clast,
     float* __restrict__ image, float* __restrict__ T_final, int32_t* __restrict__ n_contrib) {
@@ -1569,6 +1571,52 @@ __global__ __launch_bounds__(kRasterWave) void k_raster_fwd_join(
           s_splat[lane] = s;
         }
         wave_sync();
+        if constexpr (MANY) {
+          // a pixel that is done has a NaN row coordinate: it passes no test
+          const float x0 = (float)(L.tx * TW) + 0.5f, y0 = (float)(L.ty * TH) + 0.5f;
+          float fyk[PX];
+#pragma unroll
+          for (int k = 0; k < PX; ++k) fyk[k] = fix[k] && cs[k] == nc ? L.fy[k] : __builtin_nanf("");
+          uint64_t todo = __ballot(b0 + lane < hi_pos &&
+                                   splat_may_hit(s, x0, x0 + (float)(TW - 1), y0, y0 + (float)(TH - 1)));
+          while (todo) {
+            const int j = (int)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            const Splat sp = s_splat[j];
+            float p2[PX];
+            splat_p2_column<PX>(sp, __fsub_rn(L.fx, sp.mx), fyk, p2);
+            bool pass[PX], any = false;
+#pragma unroll
+            for (int k = 0; k < PX; ++k) {
+              pass[k] = splat_pass(sp, p2[k]);
+              any = any || pass[k];
+            }
+            if (!__any(any)) continue;
+#pragma unroll
+            for (int k = 0; k < PX; ++k) {
+              if (!pass[k]) continue;
+              const float alpha = fminf(kAlphaMax, sp.o * splat_gauss(p2[k]));
+              const float Tn = T[k] * (1.0f - alpha);
+              if (Tn < kTMin) {            // the pixel stops; this entry is not blended
+                fyk[k] = __builtin_nanf("");
+                cs[k] = c;
+                continue;
+              }
+              const float w = alpha * T[k];
+              C[k][0] = fmaf(sp.r, w, C[k][0]);
+              C[k][1] = fmaf(sp.g, w, C[k][1]);
+              C[k][2] = fmaf(sp.b, w, C[k][2]);
+              const float wl = alpha * Tl[k];
+              Lc[k][0] = fmaf(sp.r, wl, Lc[k][0]);
+              Lc[k][1] = fmaf(sp.g, wl, Lc[k][1]);
+              Lc[k][2] = fmaf(sp.b, wl, Lc[k][2]);
+              Tl[k] = Tl[k] * (1.0f - alpha);
+              T[k] = Tn;
+              last[k] = b0 + j + 1;
+            }
+          }
+          continue;
+        }
 #pragma unroll
         for (int k = 0; k < PX; ++k) {
           uint64_t todo = __ballot(fix[k] && cs[k] == nc);
@@ -1793,6 +1841,7 @@ struct Launch {
   ChunkDev ch;
   int64_t max_items;
   int fwd_waves, bwd_blocks;
+  bool join_many;
 };
 
 // Whether the plan's forward composites chunk items and joins them.
@@ -1860,6 +1909,16 @@ static int backward_blocks(int tw, int th, int64_t n_tiles, int64_t pairs,
   return per_tile ? tw * th / kRasterWave : 1;
 }
 
+// Whether the join visits a stopping chunk's entries with all lanes: up to a
+// pair of an image and a Gaussian per 16 pixels, which then are large splats,
+// and with several pixels a lane.  Whole split forward, all lanes / pixel by
+// pixel, 16x16 tiles of 1920x1080: 20K Gaussians 145 / 178 us, 80K 215 / 235,
+// 160K 268 / 269, 1M 699 / 498; 32x16: 20K 240 / 329, 160K 488 / 520, 1M 1547 /
+// 1006; 8x8, 20K: 84 / 80.
+static bool join_many(int tw, int th, int64_t n_tiles, int64_t pairs) {
+  return tw * th > 64 && pairs * 16 <= n_tiles * tw * th;
+}
+
 static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, int64_t pairs,
                           const gs_raster_plan* plan) {
   Launch L;
@@ -1873,6 +1932,7 @@ static Launch make_launch(const RasterDev& a, const gs_tiling* tiling, int64_t p
   L.max_items = plan ? plan->max_items : 0;
   L.fwd_waves = forward_waves(tiling->tile_w, tiling->tile_h, a.n_tiles, plan);
   L.bwd_blocks = backward_blocks(tiling->tile_w, tiling->tile_h, a.n_tiles, pairs, plan);
+  L.join_many = join_many(tiling->tile_w, tiling->tile_h, a.n_tiles, pairs);
   if (L.sch.queue) {
     L.blocks = (unsigned)std::min<int64_t>(queue_waves(plan), std::max<int64_t>(a.n_tiles, 1));
   } else if (L.sch.order) {
@@ -1914,8 +1974,13 @@ static void launch_fwd_split(const RasterDev& a, const Launch& L, uint16_t* chun
                              float* image, float* T_final, int32_t* n_contrib, hipStream_t s) {
   hipLaunchKernelGGL((k_raster_fwd_part<TW, TH>), dim3((unsigned)L.max_items), dim3(kRasterWave),
                      0, s, a, L.ch, chunk_last);
-  hipLaunchKernelGGL((k_raster_fwd_join<TW, TH>), dim3(L.blocks), dim3(kRasterWave), 0, s, a,
-                     L.sch, L.ch, chunk_last, image, T_final, n_contrib);
+  constexpr bool kMany = TW * TH > 64;
+  if (kMany && L.join_many)
+    hipLaunchKernelGGL((k_raster_fwd_join<TW, TH, kMany>), dim3(L.blocks), dim3(kRasterWave), 0, s,
+                       a, L.sch, L.ch, chunk_last, image, T_final, n_contrib);
+  else
+    hipLaunchKernelGGL((k_raster_fwd_join<TW, TH, false>), dim3(L.blocks), dim3(kRasterWave), 0, s,
+                       a, L.sch, L.ch, chunk_last, image, T_final, n_contrib);
 }
 
 template <int TW, int TH>
@@ -2037,6 +2102,11 @@ static int64_t call_tiles(const gs_tiling* t, int32_t n_slots) {
 int32_t gs_raster_fwd_waves(const gs_tiling* tiling, int32_t n_slots, const gs_raster_plan* plan) {
   if (!tiling || !raster_shape_supported(tiling->tile_w, tiling->tile_h)) return 0;
   return forward_waves(tiling->tile_w, tiling->tile_h, call_tiles(tiling, n_slots), plan);
+}
+
+int32_t gs_raster_join_many(const gs_tiling* tiling, int32_t n_slots, int64_t pairs) {
+  if (!tiling || !raster_shape_supported(tiling->tile_w, tiling->tile_h)) return 0;
+  return join_many(tiling->tile_w, tiling->tile_h, call_tiles(tiling, n_slots), pairs);
 }
 
 int32_t gs_raster_bwd_blocks(const gs_tiling* tiling, int32_t n_slots, int64_t pairs,

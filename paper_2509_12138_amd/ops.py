@@ -134,6 +134,12 @@ def forward_waves(tile, mode="default", chunk=0, fwd_waves=1, size=None, n_slots
         C.byref(_plan_kind(mode, chunk, fwd_waves, False)))
 
 
+def join_many(tile, size=None, n_slots=1, pairs=0):
+    """Whether the split forward's join visits a stopping chunk's entries with all lanes."""
+    return bool(_lib.load().gs_raster_join_many(C.byref(tiling_struct(*(size or tile), tile)), n_slots,
+                                                int(pairs)))
+
+
 def backward_blocks(tile, mode="default", deterministic=False, persistent_waves=0, size=None,
                     n_slots=1, pairs=0):
     """8x8 pixel blocks that a wave of the whole-list backward takes for n_slots images of

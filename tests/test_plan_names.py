@@ -71,8 +71,9 @@ def test_bench_names_are_instances():
         for waves in (1, 2, 4):
             if tile[0] * tile[1] // 64 % waves == 0:
                 for sched, chunk in (("lpt", 64), ("default", 0), ("persistent", 0), ("lpt+split", 64)):
-                    names.update(bench.fwd_kernel_name(tile, 1 if sched == "persistent" else waves,
-                                                       sched, chunk).split("+"))
+                    for pairs in (0, 10 ** 9):
+                        names.update(bench.fwd_kernel_name(tile, 1 if sched == "persistent" else waves,
+                                                           sched, chunk, pairs=pairs).split("+"))
         for chunk in (0, 64):
             for recompute in (False, True):
                 for det in (False, True):
@@ -126,3 +127,12 @@ def test_launches_hold_their_threads():
     assert ops.forward_waves((32, 16), size=big) == 4
     assert ops.backward_blocks((32, 16), size=big, pairs=n) == 8      # 2^23 tiles of 8 blocks
     assert ops.backward_blocks((8, 8), size=big, pairs=n) == 1
+
+
+@pytest.mark.parametrize("tile", [(16, 16), (16, 8), (32, 16), (8, 8)])
+def test_join_of_few_large_splats(tile):
+    # a pair per 16 pixels of the tiles is the line; 8x8 tiles always go pixel by pixel
+    size = (tile[0] * 10, tile[1] * 7)
+    line = 3 * size[0] * size[1] // 16
+    assert ops.join_many(tile, size, 3, line) == (tile != (8, 8))
+    assert not ops.join_many(tile, size, 3, line + 1)
