@@ -6,7 +6,13 @@ duration the same run's kernel trace records (joined on the dispatch id).
 
     python -m paper_2509_12138_amd.kcounters --run DIR [--run DIR ...] \
         --kernel 'k_raster_bwd_chunked<16, 16>' [--kernel ...] \
-        [--copy-fetch CF.csv --copy-write CW.csv] [--out FILE.json] [--plan P]
+        [--copy-fetch CF.csv --copy-write CW.csv] [--out FILE.json] [--plan P] \
+        --command 'python3 -u bench.py ...' [--after k_ssim]
+
+The bench renders its targets before the trained plan exists, with other
+Gaussians and the default plan but partly the same kernel instances: --after
+leaves out every dispatch before the first one of the named kernel, which only
+the steps launch.  A record names the command that it was taken on.
 
 Rates per kernel (mean over its dispatches, counters summed over the
 chip's counter instances, as rocprofv3 reports them):
@@ -44,8 +50,20 @@ def short(name):
     return n.replace("void ", "").replace("gsmi::", "").strip()
 
 
-def load_run(d):
-    """(durations ns by dispatch id, {dispatch id: (kernel, {counter: value})})."""
+def first_dispatch(rows, kernel):
+    """Dispatch id of the first launch of `kernel` (a name without template arguments) among the
+    rows of a rocprofv3 CSV; 0 without a name."""
+    if not kernel:
+        return 0
+    ids = [int(r["Dispatch_Id"]) for r in rows if short(r["Kernel_Name"]).split("<")[0] == kernel]
+    if not ids:
+        raise SystemExit(f"no dispatch of {kernel}")
+    return min(ids)
+
+
+def load_run(d, after=None):
+    """(durations ns by dispatch id, {dispatch id: (kernel, {counter: value})}) of the dispatches
+    from the first one of kernel `after` on."""
     trace = glob.glob(os.path.join(d, "**", "*kernel_trace.csv"), recursive=True)
     pmc = glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True)
     if not trace or not pmc:
@@ -54,7 +72,11 @@ def load_run(d):
     for r in csv.DictReader(open(trace[0])):
         dur[r["Dispatch_Id"]] = int(r["End_Timestamp"]) - int(r["Start_Timestamp"])
     ctr = collections.defaultdict(lambda: [None, {}])
-    for r in csv.DictReader(open(pmc[0])):
+    rows = list(csv.DictReader(open(pmc[0])))
+    begin = first_dispatch(rows, after)
+    for r in rows:
+        if int(r["Dispatch_Id"]) < begin:
+            continue
         e = ctr[r["Dispatch_Id"]]
         e[0] = short(r["Kernel_Name"])
         e[1][r["Counter_Name"]] = e[1].get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
@@ -134,9 +156,10 @@ def main():
     ap.add_argument("--out")
     ap.add_argument("--db", help="merge the entries into this JSON table, keyed kernel|plan")
     ap.add_argument("--plan", default="", help="tile,schedule,chunk,fwd_waves,deterministic")
-    ap.add_argument("--command", default="", help="the bench command the passes profiled")
+    ap.add_argument("--command", required=True, help="the bench command the passes profiled")
+    ap.add_argument("--after", help="only dispatches from this kernel's first one on")
     args = ap.parse_args()
-    runs = [load_run(d) for d in args.run]
+    runs = [load_run(d, args.after) for d in args.run]
     ff = copy_factor(args.copy_fetch, "FETCH_SIZE") if args.copy_fetch else None
     wf = copy_factor(args.copy_write, "WRITE_SIZE") if args.copy_write else None
     res = summarise(runs, args.kernel, ff, wf)

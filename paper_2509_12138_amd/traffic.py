@@ -7,7 +7,8 @@ of each counter: factor = bytes the copy moved / bytes the counter reported.
 
     python -m paper_2509_12138_amd.traffic --kernel k_raster_bwd_chunked \
         --fetch F.csv --write W.csv --copy-fetch CF.csv --copy-write CW.csv \
-        --plan 16x16,lpt,64,4,1 --out paper_2509_12138_amd/hbm_traffic.json
+        --plan 16x16,lpt,64,4,1 --after k_ssim --command 'python3 -u bench.py ...' \
+        --out paper_2509_12138_amd/hbm_traffic.json
 
 The entry records the kernel, the plan and a hash of the kernel's source
 file; bench.py reports the traffic only while that hash still matches.
@@ -40,14 +41,20 @@ def source_hash(kernels):
     return h.hexdigest()[:16]
 
 
-def counter_kib(path, kernel, counter):
-    """Mean counter value over the dispatches of `kernel`: a plain name
-    matches every instantiation, a name with template arguments (e.g.
+def counter_kib(path, kernel, counter, after=None):
+    """Mean counter value over the dispatches of `kernel` from the first one of
+    kernel `after` on (kcounters.first_dispatch): a plain name matches every
+    instantiation, a name with template arguments (e.g.
     "k_raster_fwd<16, 16, 4>") only that one."""
+    from .kcounters import first_dispatch
     vals = []
     want = kernel.replace(" ", "")
     with open(path) as f:
-        for r in csv.DictReader(f):
+        rows = list(csv.DictReader(f))
+        begin = first_dispatch(rows, after)
+        for r in rows:
+            if int(r["Dispatch_Id"]) < begin:
+                continue
             name = r["Kernel_Name"].split("(")[0].replace("void ", "").strip()
             full = name.split("::")[-1].replace(" ", "")
             base = full.split("<")[0]
@@ -73,14 +80,15 @@ def main(argv=None):
     ap.add_argument("--copy-write", required=True)
     ap.add_argument("--plan", required=True,
                     help="tile,schedule,chunk,fwd_waves,deterministic e.g. 16x16,lpt,64,4,1")
-    ap.add_argument("--command", default="", help="the command the counters were taken on")
+    ap.add_argument("--command", required=True, help="the command the counters were taken on")
+    ap.add_argument("--after", help="only dispatches from this kernel's first one on")
     ap.add_argument("--out", required=True)
     a = ap.parse_args(argv)
     f_kib = w_kib = 0.0
     nf = nw = []
     for k in a.kernel.split("+"):
-        fk, n1 = counter_kib(a.fetch, k, "FETCH_SIZE")
-        wk, n2 = counter_kib(a.write, k, "WRITE_SIZE")
+        fk, n1 = counter_kib(a.fetch, k, "FETCH_SIZE", a.after)
+        wk, n2 = counter_kib(a.write, k, "WRITE_SIZE", a.after)
         f_kib += fk
         w_kib += wk
         nf = nf + [n1]
